@@ -198,7 +198,7 @@ ntc_status ntc_decode_backward_workspace(const ntc_latents *lat, const ntc_mlp *
  * per spatial bin of samples in LDS and then with FP32 atomics (their
  * summation order is not deterministic). workspace [device, 256-byte
  * aligned] of at least ntc_decode_backward_workspace bytes (it grows with
- * n: 4 (3 n_levels + 1) bytes per sample plus the partial sums). */
+ * n: 68 bytes per sample with four levels, plus the partial sums). */
 ntc_status ntc_decode_backward(const ntc_latents *lat, const ntc_mlp *mlp, const float *uv, int64_t n,
                                const float *grad_out, float *const *grad_W, float *const *grad_b,
                                float *const *grad_latents, void *workspace, size_t ws_bytes,

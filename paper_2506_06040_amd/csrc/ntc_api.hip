@@ -586,11 +586,14 @@ ntc_status ntc_decode_backward(const ntc_latents *lat, const ntc_mlp *mlp, const
   a.n_params = lay.n_params;
   a.n_blocks = lay.n_blocks;
   a.n_feat = lay.n_feat;
-  a.bin_tex = lay.bin_tex;
+  a.dx_stride = lay.dx_stride;
+  a.runs = (int4 *)(ws + lay.runs_off);
+  a.bin_shift = lay.bin_shift;
   a.bins_x = lay.bins_x;
-  a.bins_y = lay.bins_y;
   a.n_bins = lay.n_bins;
+  a.n_runs = lay.n_runs;
   a.bin_lds = lay.bin_lds;
+  a.bin_cells = lay.bin_cells;
   hipError_t e = launch_backward(a, s, grad_W, grad_b, hs);
   if (e != hipSuccess) return hip_fail(e, "backward launch");
   return ok();

@@ -7,16 +7,15 @@
 // products on the matrix cores too, and so are the weight gradients
 // D_l A_l^T over the chunk's samples, accumulated in registers per
 // wavefront. dx = W_0^T D_0, the gradient of the sample's latent features, is
-// written to the workspace. Activations are never stored in global memory.
+// written to the workspace with the sample's coordinates. Activations are never stored in global memory.
 // At the end every wavefront writes its FP32 partial sums; a second kernel
 // adds the partials of all wavefronts in FP64 and rounds once to FP32.
-// Pass 2 (latent gradients, clamp addressing): the samples are grouped by
-// spatial bin (a square of level-0 texels) with a counting sort; one
-// workgroup per bin spreads dx onto the four bilinear taps of every level,
+// Pass 2 (latent gradients): the samples are grouped by spatial bin (a square
+// of level-0 texels) with a counting sort; a workgroup takes up to kBinRun
+// samples of a bin, spreads dx onto the four bilinear taps of every level,
 // adding into LDS copies of the texels the bin's samples can reach, and then
 // adds those windows to the latent gradients with one atomic per texel and
-// channel (taps outside a window fall back to a global atomic). With wrap
-// addressing every tap is a global atomic.
+// channel (taps outside a window go straight to a global atomic).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -53,24 +52,34 @@ static int backward_groups(int64_t n) {
 
 static int backward_blocks(int64_t n) { return kBwdWaves * backward_groups(n); }
 
-// Spatial bins of the latent-gradient scatter: squares of kBinTex (or a
+// Spatial bins of the latent-gradient scatter: squares of 2^kBinShift (or a
 // larger power of two, keeping at most kMaxBins bins) level-0 texels.
-constexpr int kBinTex = 32;
+constexpr int kBinShift = 5;
 constexpr int kMaxBins = 4096;
 constexpr int kBinSamplesPerBlock = 4096;  // samples per workgroup of the count / scatter passes
-constexpr int kBinWindowFloats = 12288;    // largest LDS of one bin's texel windows (48 KB)
+constexpr int kBinRun = 1120;              // samples of a bin taken by one workgroup of the accumulation
+constexpr int kAccThreads = 512;           // threads of that workgroup
+constexpr int kBinWindowFloats = 12288;    // largest LDS of a bin's texel window (48 KB)
+constexpr int kBinWindowCells = 4096;      // largest number of cells of one window
 
-// LDS (floats) for the texel windows of one bin: per level at most
-// bin_tex W_k / W_0 + 4 texels along each axis (the range of positions plus
-// one texel of margin below and two above), 3 channels, capped.
-static int bin_window_floats(const LatArgs &lat, int bin_tex) {
-  int64_t total = 0;
+// LDS of one bin: floats and cells of its largest texel window.
+// A bin spans 2^shift cells of level 0 (one more at a clamped edge, which
+// also has a cell before the first texel), and on the others at most its
+// scaled size and four cells (the ends, the shift, the edge); a window has
+// one texel more than cells along each axis.
+static void bin_window(const LatArgs &lat, int shift, int &floats, int &cells) {
+  int64_t most_f = 0, most_c = 0;
   for (int k = 0; k < lat.n_levels; ++k) {
-    const int64_t nc = (int64_t)bin_tex * lat.lv[k].w / lat.lv[0].w + 4;
-    const int64_t nr = (int64_t)bin_tex * lat.lv[k].h / lat.lv[0].h + 4;
-    total += 3 * std::min<int64_t>(nc, lat.lv[k].w) * std::min<int64_t>(nr, lat.lv[k].h);
+    auto axis = [&](int n, int n0) {
+      const int64_t c = k == 0 ? ((int64_t)1 << shift) + 1 : ((int64_t)n << shift) / n0 + 4;
+      return std::min<int64_t>(c, n + 1);
+    };
+    const int64_t nc = axis(lat.lv[k].w, lat.lv[0].w), nr = axis(lat.lv[k].h, lat.lv[0].h);
+    most_f = std::max(most_f, 3 * (nc + 1) * (nr + 1));
+    most_c = std::max(most_c, nc * nr);
   }
-  return (int)std::min<int64_t>(total, kBinWindowFloats);
+  floats = (int)std::min<int64_t>(most_f, kBinWindowFloats);
+  cells = (int)std::min<int64_t>(most_c, kBinWindowCells);
 }
 
 static size_t align256(size_t v) { return (v + 255) / 256 * 256; }
@@ -80,27 +89,31 @@ BwdLayout backward_layout(const MlpShape &s, const LatArgs &lat, int64_t n) {
   L.n_blocks = backward_blocks(n);
   L.n_params = n_params_of(s);
   L.n_feat = 3 * lat.n_levels;
-  if (lat.address == 0 && n < ((int64_t)1 << 31)) {  // sample indices of the bins are int32
-    int t = kBinTex;
+  L.dx_stride = (L.n_feat + 2 + 3) & ~3;
+  if (n < ((int64_t)1 << 31)) {  // sample indices of the bins are int32
+    int t = kBinShift;
     const int w = lat.lv[0].w, h = lat.lv[0].h;
-    while ((int64_t)((w + t - 1) / t) * ((h + t - 1) / t) > kMaxBins) t *= 2;
-    L.bin_tex = t;
-    L.bins_x = (w + t - 1) / t;
-    L.bins_y = (h + t - 1) / t;
-    L.n_bins = L.bins_x * L.bins_y;
-    L.bin_lds = bin_window_floats(lat, t);
+    auto bins = [&](int len) { return (len + (1 << t) - 1) >> t; };
+    while ((int64_t)bins(w) * bins(h) > kMaxBins) ++t;
+    L.bin_shift = t;
+    L.bins_x = bins(w);
+    L.n_bins = bins(w) * bins(h);
+    L.n_runs = L.n_bins + (int32_t)(n / kBinRun);
+    bin_window(lat, t, L.bin_lds, L.bin_cells);
   }
   size_t off = 0;
   L.wpart_off = off;
   off = align256(off + (size_t)L.n_blocks * L.n_params * sizeof(float));
   L.dx_off = off;
-  off = align256(off + (size_t)n * L.n_feat * sizeof(float));
+  off = align256(off + (size_t)n * L.dx_stride * sizeof(float));
   L.count_off = off;
   off = align256(off + (size_t)L.n_bins * sizeof(int32_t));
   L.cursor_off = off;
   off = align256(off + (size_t)L.n_bins * sizeof(int32_t));
   L.perm_off = off;
   off = align256(off + (size_t)(L.n_bins ? n : 0) * sizeof(int32_t));
+  L.runs_off = off;
+  off = align256(off + (size_t)(L.n_bins ? 1 + L.n_runs : 0) * sizeof(int4));
   L.total = off + 256;
   return L;
 }
@@ -452,12 +465,17 @@ void backward_mfma_kernel(BackwardArgs a) {
         const float w = slot >= 0 ? W0s[chain_unit(s, h) * M::S0 + slot] : 0.0f;
         z = mfma32(w, del[s >> 4][s & 15], z);
       }
+      // the row of a.dx: the feature gradients, then u, v
       if (valid) {
-        float *out = a.dx + smp * a.n_feat;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int row = 8 * (i >> 2) + 4 * h + (i & 3);
-          if (row < a.n_feat) out[row] = z[i];
+        for (int j = 0; j < 2; ++j) {
+          const int row0 = 8 * j + 4 * h;
+          if (row0 >= a.dx_stride) continue;
+          float o[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            o[r] = row0 + r == a.n_feat ? uv.x : row0 + r == a.n_feat + 1 ? uv.y : z[4 * j + r];
+          *reinterpret_cast<float4 *>(a.dx + smp * a.dx_stride + row0) = make_float4(o[0], o[1], o[2], o[3]);
         }
       }
     }
@@ -507,17 +525,29 @@ void backward_mfma_kernel(BackwardArgs a) {
 // Pass 2: latent gradients
 // ---------------------------------------------------------------------------
 
-// Bin of a sample: the square of level-0 texels holding its clamped level-0
-// sampling position.
-__device__ __forceinline__ int bin_of(const BackwardArgs &a, float2 uv) {
-  const LevelArgs &L = a.lat.lv[0];
+// Sampling position on one level split into the left / top tap (not yet
+// addressed) and the bilinear fractions, as tap_coords() does.
+struct Cell {
+  int ix, iy;
+  float fx, fy;
+};
+
+__device__ __forceinline__ Cell cell_of(const LevelArgs &L, float2 uv) {
   float x = fmaf(uv.x, L.fw, -0.5f) + L.sx;
   float y = fmaf(uv.y, L.fh, -0.5f) + L.sy;
-  x = fminf(fmaxf(x, 0.0f), L.fw - 1.0f);  // NaN becomes 0
-  y = fminf(fmaxf(y, 0.0f), L.fh - 1.0f);
-  const int bx = min((int)x / a.bin_tex, a.bins_x - 1);
-  const int by = min((int)y / a.bin_tex, a.bins_y - 1);
-  return by * a.bins_x + bx;
+  x = fminf(fmaxf(x, -16777216.0f), 16777216.0f);
+  y = fminf(fmaxf(y, -16777216.0f), 16777216.0f);
+  const float xf = floorf(x), yf = floorf(y);
+  return {(int)xf, (int)yf, x - xf, y - yf};
+}
+
+// Bin of a sample: the square of level-0 texels holding its addressed
+// (clamped or wrapped) top left tap.
+__device__ __forceinline__ int bin_of(const BackwardArgs &a, float2 uv) {
+  const LevelArgs &L = a.lat.lv[0];
+  const Cell c = cell_of(L, uv);
+  return (address_coord(c.iy, L.h, a.lat.address) >> a.bin_shift) * a.bins_x +
+         (address_coord(c.ix, L.w, a.lat.address) >> a.bin_shift);
 }
 
 // Per-bin sample counts: a histogram in LDS per workgroup, added to the
@@ -536,29 +566,45 @@ __global__ __launch_bounds__(256) void bin_count_kernel(BackwardArgs a) {
     if (hist[k]) atomicAdd(&a.bin_count[k], hist[k]);
 }
 
-// Exclusive prefix sum of the counts, in place; the cursors start at the
-// same offsets. One workgroup of 1024 threads.
+// Inclusive prefix sums of one pair per thread over the 1024 threads of a
+// workgroup.
+__device__ __forceinline__ int2 scan1024(int2 v, int2 *part) {
+  const int t = threadIdx.x;
+  part[t] = v;
+  __syncthreads();
+  for (int o = 1; o < 1024; o <<= 1) {
+    const int2 u = t >= o ? part[t - o] : make_int2(0, 0);
+    __syncthreads();
+    part[t].x += u.x;
+    part[t].y += u.y;
+    __syncthreads();
+  }
+  return part[t];
+}
+
+// Exclusive prefix sum of the counts into the cursors, and the work list of
+// bin_accum_kernel: every bin's samples cut into runs of at most kBinRun,
+// as (bin, first sample, end) with the run count in front. One workgroup of
+// 1024 threads.
 __global__ __launch_bounds__(1024) void bin_scan_kernel(BackwardArgs a) {
-  __shared__ int32_t part[1024];
+  __shared__ int2 part[1024];
   const int t = threadIdx.x;
   const int per = (a.n_bins + 1023) / 1024;
   const int k0 = t * per, k1 = min(k0 + per, a.n_bins);
-  int32_t sum = 0;
-  for (int k = k0; k < k1; ++k) sum += a.bin_count[k];
-  part[t] = sum;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const int32_t v = t >= o ? part[t - o] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
+  int2 sum = make_int2(0, 0);
+  for (int k = k0; k < k1; ++k) {
+    sum.x += a.bin_count[k];
+    sum.y += (a.bin_count[k] + kBinRun - 1) / kBinRun;
   }
-  int32_t run = part[t] - sum;
+  int2 run = scan1024(sum, part);
+  if (t == 1023) a.runs[0] = make_int4(run.y, 0, 0, 0);
+  run.x -= sum.x;
+  run.y -= sum.y;
   for (int k = k0; k < k1; ++k) {
     const int32_t c = a.bin_count[k];
-    a.bin_count[k] = run;
-    a.bin_cursor[k] = run;
-    run += c;
+    a.bin_cursor[k] = run.x;
+    for (int i = 0; i < c; i += kBinRun) a.runs[1 + run.y++] = make_int4(k, run.x + i, run.x + min(i + kBinRun, c), 0);
+    run.x += c;
   }
 }
 
@@ -589,214 +635,281 @@ __global__ __launch_bounds__(256) void bin_scatter_kernel(BackwardArgs a) {
     if (key[i] >= 0) a.perm[base[key[i]] + rank[i]] = (int32_t)(s0 + threadIdx.x + 256 * i);
 }
 
-// Texel window of one level reachable from one bin: columns [c0, c0 + nc),
-// rows [r0, r0 + nr); lds: offset in floats, or -1 when the window does not
-// fit the workgroup's LDS (that level's taps then go to global atomics).
+// Cells (left / top taps) of one level that one bin's samples fall into:
+// columns c0 .. c0 + nc - 1, rows r0 .. r0 + nr - 1, before addressing (a
+// clamped level's cells start at -1, a wrapped level's may pass either end).
+// They touch the (nc + 1) x (nr + 1) texels from (c0, r0).
 struct BinWindow {
-  int c0, nc, r0, nr, lds;
+  int c0, nc, r0, nr;
 };
 
-// Texel range along one axis of level k reached by level-0 positions in
-// [p_lo, p_hi): the position maps linearly between levels; one texel of
-// margin on each side absorbs rounding (a tap outside the range still takes
-// the global path, so the range need not be exact).
-__device__ __forceinline__ void window_axis(float p_lo, float p_hi, bool open_lo, bool open_hi, float f0, float s0,
-                                            float fk, float sk, int n, int &c0, int &nc) {
+// Cells along one axis of level k for the level-0 cells [p, p + len) of a
+// bin: the position maps linearly between levels. The range need not be
+// exact: a sample that rounding puts outside it takes the global path.
+__device__ __forceinline__ void window_axis(int k, int p, int len, int n0, float f0, float s0, int n, float fk,
+                                            float sk, int mode, int &c0, int &nc) {
   const float q = fk / f0;
-  const float x_lo = (p_lo + 0.5f - s0) * q - 0.5f + sk;
-  const float x_hi = (p_hi + 0.5f - s0) * q - 0.5f + sk;
-  int lo = open_lo ? 0 : (int)floorf(fminf(fmaxf(x_lo, 0.0f), (float)(n - 1))) - 1;
-  int hi = open_hi ? n - 1 : (int)floorf(fminf(fmaxf(x_hi, 0.0f), (float)(n - 1))) + 2;
-  lo = max(lo, 0);
-  hi = min(hi, n - 1);
+  int lo = k == 0 ? p : (int)floorf(((float)p + 0.5f - s0) * q - 0.5f + sk);
+  int hi = k == 0 ? p + len - 1 : (int)floorf(((float)(p + len) + 0.5f - s0) * q - 0.5f + sk);
+  if (mode == 1) {
+    if (hi - lo + 1 >= n) {
+      lo = 0;
+      hi = n - 1;
+    }
+  } else {
+    lo = p == 0 ? -1 : min(max(lo, -1), n - 1);
+    hi = p + len >= n0 ? n - 1 : min(max(hi, lo), n - 1);
+  }
   c0 = lo;
   nc = hi - lo + 1;
 }
 
-// Sub-bin of a sample inside its bin: 8 x 8 squares of bin_tex / 8 level-0
-// texels (the same clamped position as bin_of).
-__device__ __forceinline__ int sub_of(const BackwardArgs &a, float2 uv, int bx, int by) {
-  const LevelArgs &L = a.lat.lv[0];
-  float x = fmaf(uv.x, L.fw, -0.5f) + L.sx;
-  float y = fmaf(uv.y, L.fh, -0.5f) + L.sy;
-  x = fminf(fmaxf(x, 0.0f), L.fw - 1.0f);
-  y = fminf(fmaxf(y, 0.0f), L.fh - 1.0f);
-  const int st = a.bin_tex >> 3;
-  const int sx = min(((int)x - bx * a.bin_tex) / st, 7), sy = min(((int)y - by * a.bin_tex) / st, 7);
-  return 8 * max(sy, 0) + max(sx, 0);
+// i modulo n for |i| <= 2^25, with rn about 1 / n: the quotient is off by at
+// most one (an integer division takes several times as long).
+__device__ __forceinline__ int wrap_near(int i, int n, float rn) {
+  int r = i - n * (int)floorf((float)i * rn);
+  r += r < 0 ? n : 0;
+  return r >= n ? r - n : r;
 }
 
-// Bilinear-tap gradients of one level, accumulated while consecutive samples
-// keep the same taps (a lane walks the samples of one sub-bin, which share
-// the taps of the coarse levels most of the time) and added to the LDS
-// window (or, outside it, to the gradient texture) when they change.
-struct TapCache {
-  int ix, iy;      // unclamped left / top tap of the cached contributions
-  float g[4][3];   // per tap, per channel
-};
+// Offset of cell coordinate i in a window axis (outside [0, nc): not in it).
+__device__ __forceinline__ int window_coord(int i, int c0, int n, float rn, int mode) {
+  return mode == 1 ? wrap_near(i - c0, n, rn) : min(max(i, -1), n - 1) - c0;
+}
 
-__device__ __forceinline__ void cache_flush(TapCache &c, const BackwardArgs &a, int k, const BinWindow &wk,
-                                            float *win) {
-  if (c.ix == INT_MIN) return;
-  const LevelArgs &L = a.lat.lv[k];
-  const int i0 = address_coord(c.ix, L.w, 0), i1 = address_coord(c.ix + 1, L.w, 0);
-  const int j0 = address_coord(c.iy, L.h, 0), j1 = address_coord(c.iy + 1, L.h, 0);
-  const int ii[4] = {i0, i1, i0, i1};
-  const int jj[4] = {j0, j0, j1, j1};
+// Latent gradients of one level and one run of a bin's samples (at most
+// kBinRun): one workgroup each.
+//
+// LDS float atomics bound the first form of this kernel (all levels of a bin
+// in one workgroup, taps added to the window as they came): ds_add_f32 takes
+// about 4.4 cycles per lane on gfx950 (SQ_LDS_IDX_ACTIVE), some 25 of them
+// per sample. Here no float is added atomically in LDS. The run's samples
+// are sorted by cell (a counting sort: integer LDS atomics, which are fast,
+// and a scan), each carrying its fractions and its three gradient values;
+// then every cell is summed in registers by the lanes that own it (several
+// lanes per cell on the coarse levels) and its four taps are added to the
+// window with plain reads and writes. Cells of one parity class (even or odd
+// column, even or odd row) share no texel, so the four classes are taken one
+// after the other with a barrier between them. At the end the window is added
+// to the gradients, one global atomic per touched value. What is left is
+// latency: a chain of about ten short steps between barriers, some 1 us each,
+// which is why the levels are workgroups of their own (one workgroup taking
+// all levels in turn: 90 us in place of the 57 below).
+// 2^20 random samples on 1024^2..128^2 levels: 57 us (241 us with the LDS
+// float atomics); 2^18 samples, wrapped 512^2..64^2 levels: 23 us (660 us
+// with a global atomic per tap and channel).
+// LDS: the window (bin_lds floats), five arrays of kBinRun floats, the cell
+// counts: 40 KB with bins of 32 x 32 cells, so that four workgroups share a
+// compute unit.
+template <int kCtrl>
+__device__ __forceinline__ float dpp_add(float x) {
+  return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, true));
+}
+
+// Sum of the payloads start, start + step, ... < end of one cell per tap and
+// channel.
+__device__ __forceinline__ void cell_sum(const float *pay, int start, int end, int step, float (&g)[4][3]) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int col = ii[q] - wk.c0, row = jj[q] - wk.r0;
-    if (wk.lds >= 0 && (unsigned)col < (unsigned)wk.nc && (unsigned)row < (unsigned)wk.nr) {
-      float *p = win + wk.lds + 3 * (row * wk.nc + col);
-      atomicAdd(p + 0, c.g[q][0]);
-      atomicAdd(p + 1, c.g[q][1]);
-      atomicAdd(p + 2, c.g[q][2]);
-    } else {
-      float *p = a.grad_lat[k] + ((int64_t)jj[q] * L.w + ii[q]) * 3;
-      unsafeAtomicAdd(p + 0, c.g[q][0]);
-      unsafeAtomicAdd(p + 1, c.g[q][1]);
-      unsafeAtomicAdd(p + 2, c.g[q][2]);
+  for (int q = 0; q < 4; ++q) g[q][0] = g[q][1] = g[q][2] = 0.0f;
+  for (int j = start; j < end; j += step) {
+    const float x = pay[j], y = pay[kBinRun + j];
+    const float gx = 1.0f - x, gy = 1.0f - y;
+    const float w[4] = {gx * gy, x * gy, gx * y, x * y};
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) {
+      const float z = pay[(2 + ch) * kBinRun + j];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) g[q][ch] = fmaf(w[q], z, g[q][ch]);
     }
   }
-  c.ix = INT_MIN;
 }
 
-// One bin per workgroup. The bin's samples are sorted by sub-bin in LDS (in
-// rounds of kBinChunk); thread t then walks the samples of sub-bin t % 64
-// with stride 4 (t / 64 the phase), so the 64 lanes of a wavefront work in
-// 64 different places of the bin and each lane's consecutive samples are
-// neighbours. LDS: the texel windows (bin_lds floats), then the sorted
-// sample indices and the sub-bin counts.
-constexpr int kBinChunk = 2048;
-constexpr int kSubBins = 64;
+// Adds a cell's sums to its four texels; p: the top left one, tc texels a row.
+__device__ __forceinline__ void cell_add(float *p, int tc, const float (&g)[4][3]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) p[3 * ((q & 1) + (q >> 1) * tc) + ch] += g[q][ch];
+}
 
-__global__ __launch_bounds__(256) void bin_accum_kernel(BackwardArgs a) {
+__global__ __launch_bounds__(kAccThreads) void bin_accum_kernel(BackwardArgs a) {
+  constexpr int kT = kAccThreads, kWaves = kT / 64;
   extern __shared__ float win[];
-  int32_t *sorted = reinterpret_cast<int32_t *>(win + a.bin_lds);
-  int32_t *sub_start = sorted + kBinChunk;      // [kSubBins + 1]
-  int32_t *sub_cursor = sub_start + kSubBins + 1;  // [kSubBins]
-  const int bin = blockIdx.x;
-  const int start = a.bin_count[bin];
-  const int end = bin + 1 < a.n_bins ? a.bin_count[bin + 1] : (int)a.n;
-  if (start >= end) return;
-  const int bx = bin % a.bins_x, by = bin / a.bins_x;
-  const int n_levels = a.lat.n_levels;
-  const int tid = threadIdx.x;
-  BinWindow wk[kMaxLevels];
-  int used = 0;
+  float *pay = win + a.bin_lds;                                   // [5][kBinRun]
+  int32_t *cnt = reinterpret_cast<int32_t *>(pay + 5 * kBinRun);  // [bin_cells + 1]
+  __shared__ int32_t wsum[kWaves];
+  // the levels of one run are neighbours on one XCD (workgroups go to the 8
+  // XCDs in turn), whose L2 then holds the run's rows for all of them
+  const int n_levels = a.lat.n_levels, mode = a.lat.address;
+  const int k = (int)(blockIdx.x >> 3) % n_levels;
+  const int item = ((int)(blockIdx.x >> 3) / n_levels) * 8 + (int)(blockIdx.x & 7);
+  if (item >= a.runs[0].x) return;
+  const int4 run = a.runs[1 + item];
+  const int bx = run.x % a.bins_x, by = run.x / a.bins_x;
+  const int m = run.z - run.y;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const LevelArgs &L0 = a.lat.lv[0];
+
+  const LevelArgs &L = a.lat.lv[k];
+
+  // this thread's samples: tid, tid + kT, ...
+  constexpr int kPer = (kBinRun + kT - 1) / kT;
+  float d[kPer][3];
+  float2 uv[kPer];
 #pragma unroll
-  for (int k = 0; k < kMaxLevels; ++k) {
-    wk[k].lds = -1;
-    wk[k].c0 = wk[k].r0 = wk[k].nc = wk[k].nr = 0;
-    if (k < n_levels) {
-      const LevelArgs &L = a.lat.lv[k];
-      window_axis((float)(bx * a.bin_tex), (float)((bx + 1) * a.bin_tex), bx == 0, bx == a.bins_x - 1, L0.fw, L0.sx,
-                  L.fw, L.sx, L.w, wk[k].c0, wk[k].nc);
-      window_axis((float)(by * a.bin_tex), (float)((by + 1) * a.bin_tex), by == 0, by == a.bins_y - 1, L0.fh, L0.sy,
-                  L.fh, L.sy, L.h, wk[k].r0, wk[k].nr);
-      const int sz = 3 * wk[k].nc * wk[k].nr;
-      if (used + sz <= a.bin_lds) {
-        wk[k].lds = used;
-        used += sz;
+  for (int i = 0; i < kPer; ++i) {
+    const float *g = a.dx + (int64_t)a.perm[run.y + min(tid + kT * i, m - 1)] * a.dx_stride;
+    uv[i] = make_float2(g[a.n_feat], g[a.n_feat + 1]);
+#pragma unroll
+    for (int ch = 0; ch < 3; ++ch) d[i][ch] = g[3 * k + ch];
+  }
+  const int lw = L.w, lh = L.h;
+  const float rw = 1.0f / L.fw, rh = 1.0f / L.fh;
+  BinWindow wk;
+  window_axis(k, bx << a.bin_shift, 1 << a.bin_shift, L0.w, L0.fw, L0.sx, lw, L.fw, L.sx, mode, wk.c0, wk.nc);
+  window_axis(k, by << a.bin_shift, 1 << a.bin_shift, L0.h, L0.fh, L0.sy, lh, L.fh, L.sy, mode, wk.r0, wk.nr);
+  const int tc = wk.nc + 1, size = 3 * tc * (wk.nr + 1), cells = wk.nc * wk.nr;
+  const bool fits = size <= a.bin_lds && cells <= a.bin_cells;
+  if (fits) {
+    for (int i = tid; i < size; i += kT) win[i] = 0.0f;
+    for (int i = tid; i < cells; i += kT) cnt[i] = 0;
+  }
+  __syncthreads();
+  // cell and rank of every sample
+  int cell[kPer], rank[kPer];
+  float fx[kPer], fy[kPer];
+  bool direct = false;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const Cell c = cell_of(L, uv[i]);
+    fx[i] = c.fx;
+    fy[i] = c.fy;
+    const int col = window_coord(c.ix, wk.c0, lw, rw, mode), line = window_coord(c.iy, wk.r0, lh, rh, mode);
+    const bool in = fits && (unsigned)col < (unsigned)wk.nc && (unsigned)line < (unsigned)wk.nr;
+    cell[i] = in ? line * wk.nc + col : -1;
+    if (tid + kT * i >= m) {
+      cell[i] = -1;
+    } else if (in) {
+      rank[i] = atomicAdd(&cnt[cell[i]], 1);
+    } else {
+      direct = true;
+    }
+  }
+  if (direct) {  // samples outside the window go straight to the gradients
+#pragma unroll 1
+    for (int j = tid; j < m; j += kT) {
+      const float *g = a.dx + (int64_t)a.perm[run.y + j] * a.dx_stride;
+      const Cell c = cell_of(L, make_float2(g[a.n_feat], g[a.n_feat + 1]));
+      const int col = window_coord(c.ix, wk.c0, lw, rw, mode), row = window_coord(c.iy, wk.r0, lh, rh, mode);
+      if (fits && (unsigned)col < (unsigned)wk.nc && (unsigned)row < (unsigned)wk.nr) continue;
+#pragma unroll 1
+      for (int q = 0; q < 4; ++q) {
+        const int ti = address_coord(c.ix + (q & 1), lw, mode), tj = address_coord(c.iy + (q >> 1), lh, mode);
+        const float w = ((q & 1) ? c.fx : 1.0f - c.fx) * ((q >> 1) ? c.fy : 1.0f - c.fy);
+        float *p = a.grad_lat[k] + ((int64_t)tj * lw + ti) * 3;
+#pragma unroll
+        for (int ch = 0; ch < 3; ++ch) unsafeAtomicAdd(p + ch, w * g[3 * k + ch]);
       }
     }
   }
-  for (int i = tid; i < used; i += 256) win[i] = 0.0f;
-  const int sub = tid & (kSubBins - 1), phase = tid >> 6;
-  for (int c0 = start; c0 < end; c0 += kBinChunk) {
-    const int m = min(kBinChunk, end - c0);
-    // counting sort of this round's samples by sub-bin
-    if (tid <= kSubBins) sub_start[tid] = 0;
-    __syncthreads();
-    for (int i = tid; i < m; i += 256) atomicAdd(&sub_start[1 + sub_of(a, a.uv[a.perm[c0 + i]], bx, by)], 1);
-    __syncthreads();
-    if (tid < 64) {  // inclusive scan of the 64 counts (one wavefront)
-      int v = sub_start[1 + tid];
+  if (!fits) return;
+  __syncthreads();
+  // exclusive scan of the counts
+  const int per = (cells + kT - 1) / kT;
+  const int e0 = min(tid * per, cells), e1 = min(e0 + per, cells);
+  int sum = 0;
+  for (int e = e0; e < e1; ++e) sum += cnt[e];
+  int v = sum;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(v, o, 64);
-        if (tid >= o) v += t;
-      }
-      sub_start[1 + tid] = v;
-    }
-    __syncthreads();
-    if (tid < kSubBins) sub_cursor[tid] = sub_start[tid];
-    __syncthreads();
-    for (int i = tid; i < m; i += 256) {
-      const int s = a.perm[c0 + i];
-      const int key = sub_of(a, a.uv[s], bx, by);
-      sorted[atomicAdd(&sub_cursor[key], 1)] = s;
-    }
-    __syncthreads();
-    // this thread's samples: sub-bin `sub`, every fourth
-    TapCache cache[kMaxLevels];
-#pragma unroll
-    for (int k = 0; k < kMaxLevels; ++k) cache[k].ix = INT_MIN;
-    const int j1 = sub_start[sub + 1];
-    for (int j = sub_start[sub] + phase; j < j1; j += 4) {
-      const int s = sorted[j];
-      const float2 uv = a.uv[s];
-      const float *g = a.dx + (int64_t)s * a.n_feat;
-#pragma unroll
-      for (int k = 0; k < kMaxLevels; ++k) {
-        if (k < n_levels) {
-          const LevelArgs &L = a.lat.lv[k];
-          float x = fmaf(uv.x, L.fw, -0.5f) + L.sx;
-          float y = fmaf(uv.y, L.fh, -0.5f) + L.sy;
-          x = fminf(fmaxf(x, -16777216.0f), 16777216.0f);
-          y = fminf(fmaxf(y, -16777216.0f), 16777216.0f);
-          const float xf = floorf(x), yf = floorf(y);
-          const float fx = x - xf, fy = y - yf;
-          const int ix = (int)xf, iy = (int)yf;
-          if (ix != cache[k].ix || iy != cache[k].iy) {
-            cache_flush(cache[k], a, k, wk[k], win);
-            cache[k].ix = ix;
-            cache[k].iy = iy;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-              for (int ch = 0; ch < 3; ++ch) cache[k].g[q][ch] = 0.0f;
-          }
-          const float gx = 1.0f - fx, gy = 1.0f - fy;
-          const float w[4] = {gx * gy, fx * gy, gx * fy, fx * fy};
-          const float d[3] = {g[3 * k], g[3 * k + 1], g[3 * k + 2]};
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int ch = 0; ch < 3; ++ch) cache[k].g[q][ch] = fmaf(w[q], d[ch], cache[k].g[q][ch]);
-        }
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < kMaxLevels; ++k)
-      if (k < n_levels) cache_flush(cache[k], a, k, wk[k], win);
-    __syncthreads();
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(v, o, 64);
+    if (lane >= o) v += t;
   }
+  if (lane == 63) wsum[wave] = v;
+  __syncthreads();
+  v -= sum;
 #pragma unroll
-  for (int k = 0; k < kMaxLevels; ++k) {
-    if (k < n_levels && wk[k].lds >= 0) {
-      const int nc = wk[k].nc, cnt = 3 * nc * wk[k].nr;
-      float *G = a.grad_lat[k];
-      const int w = a.lat.lv[k].w;
-      for (int i = tid; i < cnt; i += 256) {
-        const float v = win[wk[k].lds + i];
-        if (v != 0.0f) {
-          const int texel = i / 3, ch = i - 3 * texel;
-          const int r = texel / nc, c = texel - r * nc;
-          unsafeAtomicAdd(G + ((int64_t)(wk[k].r0 + r) * w + wk[k].c0 + c) * 3 + ch, v);
+  for (int w = 0; w < kWaves - 1; ++w) v += w < wave ? wsum[w] : 0;
+  for (int e = e0; e < e1; ++e) {
+    const int c = cnt[e];
+    cnt[e] = v;
+    v += c;
+  }
+  if (tid == kT - 1) cnt[cells] = v;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    if (cell[i] >= 0) {
+      const int at = cnt[cell[i]] + rank[i];
+      pay[at] = fx[i];
+      pay[kBinRun + at] = fy[i];
+      pay[2 * kBinRun + at] = d[i][0];
+      pay[3 * kBinRun + at] = d[i][1];
+      pay[4 * kBinRun + at] = d[i][2];
+    }
+  }
+  __syncthreads();
+  float g[4][3];
+  if (cells <= kT) {
+    // every cell at once, 2^ts lanes each (at most 16, a DPP row), then the
+    // classes one after the other
+    int ts = 0;
+    while (ts < 4 && (cells << (ts + 1)) <= kT) ++ts;
+    const int e = tid >> ts, row = (int)(((float)e + 0.5f) * (1.0f / (float)wk.nc)), col = e - row * wk.nc;
+    const int start = e < cells ? cnt[e] : 0, end = e < cells ? cnt[e + 1] : 0;
+    cell_sum(pay, start + (tid & ((1 << ts) - 1)), end, 1 << ts, g);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int ch = 0; ch < 3; ++ch) {
+        if (ts > 0) g[q][ch] = dpp_add<0xB1>(g[q][ch]);   // quad_perm 1,0,3,2
+        if (ts > 1) g[q][ch] = dpp_add<0x4E>(g[q][ch]);   // quad_perm 2,3,0,1
+        if (ts > 2) g[q][ch] = dpp_add<0x141>(g[q][ch]);  // row_half_mirror
+        if (ts > 3) g[q][ch] = dpp_add<0x140>(g[q][ch]);  // row_mirror
+      }
+    const int own = (tid & ((1 << ts) - 1)) == 0 && end > start ? (col & 1) + 2 * (row & 1) : -1;
+#pragma unroll 1
+    for (int par = 0; par < 4; ++par) {
+      if (own == par) cell_add(win + 3 * (row * tc + col), tc, g);
+      __syncthreads();
+    }
+  } else {
+#pragma unroll 1
+    for (int par = 0; par < 4; ++par) {
+      const int pc = par & 1, pr = par >> 1;
+      const int ncol = (wk.nc + 1 - pc) >> 1, count = ncol * ((wk.nr + 1 - pr) >> 1);
+      const float rcol = 1.0f / (float)ncol;
+      for (int e = tid; e < count; e += kT) {
+        const int er = (int)(((float)e + 0.5f) * rcol);
+        const int row = pr + 2 * er, col = pc + 2 * (e - er * ncol);
+        const int start = cnt[row * wk.nc + col], end = cnt[row * wk.nc + col + 1];
+        if (end > start) {
+          cell_sum(pay, start, end, 1, g);
+          cell_add(win + 3 * (row * tc + col), tc, g);
         }
       }
+      __syncthreads();
+    }
+  }
+  // the window's touched values, a row of texels per wavefront
+  for (int r = wave; r <= wk.nr; r += kWaves) {
+    float *G = a.grad_lat[k] + (int64_t)address_coord(wk.r0 + r, lh, mode) * lw * 3;
+    for (int i = lane; i < 3 * tc; i += 64) {
+      const float x = win[3 * r * tc + i];
+      const int c = i / 3;
+      const int cg = mode == 1 ? wrap_near(wk.c0 + c, lw, rw) : min(max(wk.c0 + c, 0), lw - 1);
+      if (x != 0.0f) unsafeAtomicAdd(G + 3 * cg + (i - 3 * c), x);
     }
   }
 }
 
-// Wrap addressing: every tap of every sample is a global atomic.
+// Too many samples for the bins' 32-bit indices: every tap of every sample is
+// a global atomic.
 __global__ __launch_bounds__(256) void scatter_direct_kernel(BackwardArgs a) {
   const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (s >= a.n) return;
   const float2 uv = a.uv[s];
-  const float *g = a.dx + s * a.n_feat;
+  const float *g = a.dx + s * a.dx_stride;
 #pragma unroll
   for (int k = 0; k < kMaxLevels; ++k) {
     if (k < a.lat.n_levels) {
@@ -1034,8 +1147,8 @@ hipError_t launch_backward(const BackwardArgs &a, const MlpShape &s, float *cons
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(256), 2 * a.n_bins * sizeof(int32_t), st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(bin_accum_kernel, dim3(a.n_bins), dim3(256),
-                     (size_t)a.bin_lds * sizeof(float) + (kBinChunk + 2 * kSubBins + 1) * sizeof(int32_t), st, a);
+  hipLaunchKernelGGL(bin_accum_kernel, dim3((unsigned)((a.n_runs + 7) / 8 * 8 * a.lat.n_levels)), dim3(kAccThreads),
+                     (size_t)(a.bin_lds + 5 * kBinRun + a.bin_cells + 1) * sizeof(float), st, a);
   return hipGetLastError();
 }
 

@@ -94,14 +94,15 @@ hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t st);
 
 // Backward. Workspace (256-byte aligned sections): per-block FP32 partial
 // sums of the weight gradients, the feature gradient dL/dx of every sample,
-// and for clamp addressing the spatial bins of the latent-gradient scatter
-// (per-bin counts, then start offsets; running cursors; sample indices
-// grouped by bin).
+// and the spatial bins of the latent-gradient scatter (per-bin counts;
+// running cursors; sample indices grouped by bin; runs of samples of one bin).
 struct BwdLayout {
   int32_t n_blocks, n_params, n_feat;
-  int32_t bin_tex, bins_x, bins_y, n_bins;  // n_bins = 0: no binning (wrap addressing)
-  int32_t bin_lds;                          // LDS floats of one bin's texel windows
-  size_t wpart_off, dx_off, count_off, cursor_off, perm_off, total;
+  int32_t dx_stride;                  // floats of a row of dx (a multiple of 4)
+  int32_t bin_shift, bins_x, n_bins;  // bins of 2^bin_shift level-0 texels; n_bins = 0: no binning (2^31 samples or more)
+  int32_t n_runs;                     // largest number of sample runs of the bins
+  int32_t bin_lds, bin_cells;         // LDS floats and cells of a bin's largest texel window
+  size_t wpart_off, dx_off, count_off, cursor_off, perm_off, runs_off, total;
 };
 BwdLayout backward_layout(const MlpShape &s, const LatArgs &lat, int64_t n);
 
@@ -113,15 +114,16 @@ struct BackwardArgs {
   const float *grad_out;
   float *grad_lat[kMaxLevels];
   float *wpart;          // [n_blocks][n_params] FP32 per-block partial sums
-  float *dx;             // [n][n_feat] dL/d(feature) of every sample
+  float *dx;             // [n][dx_stride]: dL/d(feature) of every sample, then its u, v: 64 bytes a sample with 4 levels
   int32_t *bin_count;    // [n_bins]
   int32_t *bin_cursor;   // [n_bins]
   int32_t *perm;         // [n]
+  int4 *runs;            // [1 + n_runs]: the number of runs, then (bin, first, end) of each in perm
   int64_t n;
   int32_t n_params;
   int32_t n_blocks;
-  int32_t n_feat;
-  int32_t bin_tex, bins_x, bins_y, n_bins, bin_lds;
+  int32_t n_feat, dx_stride;
+  int32_t bin_shift, bins_x, n_bins, n_runs, bin_lds, bin_cells;
   int32_t dims[kMaxLayers + 1];
   int32_t n_layers;
 };

@@ -281,3 +281,41 @@ def test_forward_float_latents(dims, sizes, address):
                          out_dtype=torch.float16).cpu().numpy().astype(np.float64)
         assert np.all(np.abs(o16 - ref) <= 2.0 ** -11 * np.abs(ref) + 1e-7), n
     print(f"[forward float latents {dims} {address}] ok", flush=True)
+
+
+@pytest.mark.parametrize("sizes,address,span,hot", [
+    ([(128, 96), (64, 48), (32, 24), (16, 12)], "wrap", (-2.0, 3.0), 0),      # several bins, windows past both ends
+    ([(100, 70), (52, 36), (24, 20)], "wrap", (0.0, 1.0), 0),                 # last bins cut off, inexact ratios
+    ([(33, 31), (65, 90)], "wrap", (-0.5, 1.5), 0),                           # a level finer than level 0
+    ([(33, 65), (65, 90)], "clamp", (-0.5, 1.5), 0),
+    ([(4, 4), (4, 8), (8, 4), (4, 4)], "wrap", (-1.0, 2.0), 0),               # windows as large as the level
+    ([(4, 4)], "clamp", (-9.0, 10.0), 0),                                     # most positions beyond the edges
+    ([(64, 64), (32, 32), (16, 16), (8, 8)], "wrap", (0.0, 1.0), 3),          # one bin of more than one run
+    ([(2304, 2112), (64, 64)], "clamp", (0.0, 1.0), 2),                       # bins wider than 32 texels
+])
+def test_backward_latent_bins(sizes, address, span, hot):
+    """Latent gradients over the edges of the scatter's bins and windows: both
+    address modes, sizes that are no multiple of a bin, coordinates outside
+    the unit square, and most samples in one place. Every hidden unit is
+    active for every sample (small weights, biases of 3), so no ReLU decision
+    depends on rounding."""
+    rng = np.random.default_rng(len(sizes) + sizes[0][0] + sizes[0][1])
+    lat_np = I.f32_pyramid(rng, sizes)
+    Ws, bs = I.xavier_mlp(rng, (3 * len(sizes) + 2, 16, 16, 3), bias="normal")
+    Ws = [(0.1 * w).astype(np.float32) for w in Ws]
+    bs = [bs[0] + np.float32(3), bs[1] + np.float32(3), bs[2]]
+    far = max(abs(span[0]), abs(span[1]), 1.0)
+    top = np.abs(Ws[0]).sum(1) * far
+    assert np.all(bs[0] - top > 0) and np.all(bs[1] - np.abs(Ws[1]) @ (bs[0] + top) > 0)
+    n = 1283 * (hot + 1)
+    uv = span[0] + rng.random((n, 2)) * (span[1] - span[0])
+    if hot:
+        uv[: 1281 * hot] = 0.4 + rng.random((1281 * hot, 2)) * (8.0 / sizes[0][0])
+    uv = uv[rng.permutation(n)].astype(np.float32)
+    shift = I.PAPER_SHIFT[:len(sizes)]
+    olat = O.Latents(lat_np, shift=shift, address=O.WRAP if address == "wrap" else O.CLAMP)
+    g = rng.standard_normal((n, 3)).astype(np.float32).astype(np.float64)
+    _, _, gl = _gpu_direct(lat_np, Ws, bs, uv, g, shift, address=address)
+    _, _, ol = O.backward(olat, O.Mlp(Ws, bs), uv, g)
+    for k in range(len(sizes)):
+        _close(f"bins dlat{k}", gl[k], ol[k])
