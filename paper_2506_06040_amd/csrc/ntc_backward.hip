@@ -37,20 +37,27 @@ static inline int n_params_of(const MlpShape &s) {
   return n;
 }
 
-// Matrix-core backward: workgroups of kBwdWaves wavefronts (one per SIMD),
+// Matrix-core backward: workgroups of 4 or 8 wavefronts (one or two per SIMD),
 // each wavefront taking kBwdChunk samples per step; one row of partial
 // weight-gradient sums per wavefront.
-constexpr int kBwdWaves = 4;
 constexpr int kBwdChunk = 32;
 constexpr int kBwdMaxGroups = 256;
 
-static int backward_groups(int64_t n) {
+// Wavefronts per workgroup: two per SIMD (256 registers each) cover each
+// other's waits; the 64-wide networks of four layers need the registers of
+// one per SIMD for their gradient accumulators.
+static constexpr int backward_waves(int mt, int n_layers) { return mt == 2 && n_layers > 3 ? 4 : 8; }
+
+static int backward_groups(int64_t n, int waves) {
   const int64_t chunks = (n + kBwdChunk - 1) / kBwdChunk;
-  const int64_t g = (chunks + kBwdWaves - 1) / kBwdWaves;
+  const int64_t g = (chunks + waves - 1) / waves;
   return (int)(g > kBwdMaxGroups ? kBwdMaxGroups : (g < 1 ? 1 : g));
 }
 
-static int backward_blocks(int64_t n) { return kBwdWaves * backward_groups(n); }
+static int backward_blocks(const MlpShape &s, int64_t n) {
+  const int waves = backward_waves(s.hid > 32 ? 2 : 1, s.n_layers);
+  return waves * backward_groups(n, waves);
+}
 
 // Spatial bins of the latent-gradient scatter: squares of 2^kBinShift (or a
 // larger power of two, keeping at most kMaxBins bins) level-0 texels.
@@ -86,7 +93,7 @@ static size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 BwdLayout backward_layout(const MlpShape &s, const LatArgs &lat, int64_t n) {
   BwdLayout L{};
-  L.n_blocks = backward_blocks(n);
+  L.n_blocks = backward_blocks(s, n);
   L.n_params = n_params_of(s);
   L.n_feat = 3 * lat.n_levels;
   L.dx_stride = (L.n_feat + 2 + 3) & ~3;
@@ -166,45 +173,94 @@ __global__ __launch_bounds__(64 * kReduceWaves) void reduce_f64_kernel(ReduceArg
 }
 
 // ---------------------------------------------------------------------------
-// Pass 1 on the matrix cores (FP32 operands, v_mfma_f32_32x32x2f32)
+// Pass 1 on the matrix cores (FP32 operands and accumulation)
 //
-// A wavefront takes 32 samples per step (the 32 columns of the matrix
-// tiles). Every product is a 32 x 32 tile of units x samples: the weights
-// are the A operand (row = output unit, one float per lane), the layer input
-// the B operand. In the accumulator a lane holds rows 8 j + 4 h + r (j, r < 4,
-// h = lane / 32) of sample lane % 32; K-step t of a product whose input is
-// such a tile takes element t of it (lane half h supplying unit
-// 8 (t / 4) + 4 h + t % 4 of the tile), so layers chain in registers in both
-// directions and the ReLU mask of a delta is the activation at the same
-// register. The first layer's K-slots hold per lane half two levels'
-// features: slot 2 s + h is channel s % 3 of level 2 h + s / 3 (s < 6), u
-// or v (s = 6), the constant 1 that carries the bias (s = 7, h = 0) or
-// padding. Weight gradients contract over the samples: each step writes the
-// deltas and the layer inputs transposed to LDS ([unit][sample], even
-// samples first) and accumulates D A^T over 16 K-steps of two samples;
-// bias gradients are row sums of the staged deltas.
+// A wavefront takes 32 samples per step. The products over hidden units are
+// v_mfma_f32_32x32x2 tiles of units x samples: the weights are the A operand
+// (row = output unit, one float per lane), the layer input the B operand. In
+// the accumulator a lane holds rows 8 j + 4 h + r (j, r < 4, h = lane / 32)
+// of sample lane % 32; K-step t of a product whose input is such a tile takes
+// element t of it (lane half h supplying unit 8 (t / 4) + 4 h + t % 4 of the
+// tile), so layers chain in registers in both directions. The first layer's
+// K-slots hold per lane half two levels' features: slot 2 s + h is channel
+// s % 3 of level 2 h + s / 3 (s < 6), u or v (s = 6), the constant 1 that
+// carries the bias (s = 7, h = 0) or padding.
+//
+// Products with at most 16 output rows (the output layer, the feature
+// gradients) take v_mfma_f32_16x16x1_4b, half the matrix time of a padded
+// 32-row tile: block b = lane / 16 multiplies its own 16 columns, which are
+// samples 16 (b % 2) .. + 15 and the units of lane half b / 2, so an
+// accumulator tile is its B operand as it stands; blocks b and b + 2 are added
+// at the end, and a lane then holds rows 4 (lane / 16) + r of samples
+// lane % 16 and 16 + lane % 16.
+//
+// Weight gradients contract over the samples: the deltas and layer inputs
+// are written to LDS as [unit][sample] and read back with a unit per lane,
+// 32x32x2 tiles for hidden layers (lane half h: samples 16 h ..), 16x16x4
+// tiles where one side has at most 16 rows (lane / 16 = g: samples 8 g ..).
+// The buffers are [sample / 4][unit][sample % 4] with a pad of one unit, so
+// that neither the writes (32 samples of a unit) nor the reads (float4s of
+// consecutive units) meet bank conflicts and every offset is an immediate.
+// Bias gradients are row sums of the staged deltas.
+//
+// Matrix time bounds both kernels, and the vector instructions add to it:
+// FP32 matrix and vector work of one SIMD hardly overlap (64 instructions
+// less per step were worth 10 us of 2^20 samples). Hence the float4 weight
+// reads, the 16-row products (280 in place of 344 units of 64 matrix cycles
+// per step of 14-64-64-8) and two wavefronts per SIMD, which cover each
+// other's texel loads and LDS round trips. 2^20 random samples, 14-64-64-8,
+// 1024^2..128^2 levels: backward 558 -> 363 us (95 TFLOP/s of products that
+// count), forward 188 -> 145 us, against one wavefront per SIMD, padded
+// 32-row output tiles and level parameters fetched per lane.
 // ---------------------------------------------------------------------------
 typedef float bf32x16 __attribute__((ext_vector_type(16)));
 typedef float bf32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kStS = 36;  // row stride (floats) of the transposed staging
+// i modulo n for |i| <= 2^25, with rn about 1 / n: the quotient is off by at
+// most one (an integer division takes several times as long).
+__device__ __forceinline__ int wrap_near(int i, int n, float rn) {
+  int r = i - n * (int)floorf((float)i * rn);
+  r += r < 0 ? n : 0;
+  return r >= n ? r - n : r;
+}
+
+// Level parameters in LDS, so that a lane half reads its two levels' own
+// without holding them in registers or choosing among scalars:
+// [h][j] = grid pointer, w, h | fw, fh, sx, sy | 1 / fw, 1 / fh.
+struct LevelSel {
+  const float *grid;
+  int w, h;
+  float fw, fh, sx, sy;
+  float rw, rh;
+};
+constexpr int kLevelFloats = sizeof(LevelSel) / sizeof(float) + 2;  // a multiple of 4
+
+__device__ __forceinline__ void load_levels(float *tab, const LatArgs &lat, int tid) {
+  if (tid < kMaxLevels) {
+    const LevelArgs &A = lat.lv[tid];
+    *reinterpret_cast<LevelSel *>(tab + kLevelFloats * tid) = {A.grid, A.w,  A.h,         A.fw,       A.fh,
+                                                               A.sx,   A.sy, 1.0f / A.fw, 1.0f / A.fh};
+  }
+}
 
 template <int MT, int NL>
 struct BwdMap {
+  static constexpr int waves = backward_waves(MT, NL);
   static constexpr int HP = 32 * MT;        // padded hidden width
-  static constexpr int S0 = 17;             // row stride of the first layer (16 K-slots)
-  static constexpr int SH = HP + 1;         // row stride of the other layers
+  static constexpr int S0 = 20;             // row stride of the first layer (K-slots, lane half 0's 8 first)
+  static constexpr int SH = HP + 4;         // row stride of the other layers (float4 reads of 8 rows: no conflicts)
   static constexpr int NH = NL - 2;         // hidden-to-hidden layers
   static constexpr int oW0 = 0;
   static constexpr int oWh = oW0 + HP * S0;
-  static constexpr int oWo = oWh + NH * HP * SH;
-  static constexpr int oB = (oWo + 32 * SH + 3) & ~3;  // bias fragments [layer 1..NL-1][mt][h][16]
-  static constexpr int nB = (NH * MT + 1) * 32;
-  static constexpr int oStage = (oB + nB + 3) & ~3;
-  static constexpr int stage_rows = HP + (HP > 32 ? HP : 32);
-  static constexpr int stage = stage_rows * kStS;    // Dt then At, per wavefront
-  static constexpr int total = oStage + kBwdWaves * stage;
-  __device__ static int bias(int l, int mt) { return oB + ((l - 1) * MT + mt) * 32; }  // l = 1 .. NL - 1
+  static constexpr int oWo = oWh + NH * HP * SH;         // 16 output rows
+  static constexpr int oB = oWo + 16 * SH;               // bias fragments [layer 1..NL-2][mt][h][16]
+  static constexpr int oBo = oB + NH * MT * 32;          // output biases [16]
+  static constexpr int oLv = oBo + 16;                   // level parameters
+  static constexpr int oStage = oLv + kLevelFloats * kMaxLevels;
+  static constexpr int SQ = 4 * (HP + 1);                // stride of a staged group of 4 samples
+  static constexpr int stage = 2 * 8 * SQ;               // per wavefront: two buffers of HP units
+  static constexpr int total = oStage + waves * stage;
+  __device__ static int bias(int l, int mt) { return oB + ((l - 1) * MT + mt) * 32; }  // l = 1 .. NL - 2
 };
 
 // Unit of the previous layer's tile fed to K-step s by lane half h.
@@ -226,276 +282,454 @@ __device__ __forceinline__ bf32x16 mfma32(float a, float b, bf32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-template <int MT, int NL>
-__global__ __launch_bounds__(64 * kBwdWaves) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void backward_mfma_kernel(BackwardArgs a) {
+// Weights and biases into LDS, zero-padded, shared by the workgroup's
+// T threads. W(l), b(l): element functions of layer l's matrix and bias.
+template <int MT, int NL, int T, class FW, class FB>
+__device__ __forceinline__ void load_weights(float *lds, int tid, int n_levels, FW W, FB b) {
   using M = BwdMap<MT, NL>;
   constexpr int HP = M::HP;
-  extern __shared__ float bwd_lds[];
-  float *lds = bwd_lds;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, h = lane >> 5, c32 = lane & 31;
-  const int wave = tid >> 6;
-  const int hid = a.dims[1], n_out = a.dims[NL], d0 = a.dims[0];
-  const int n_levels = a.lat.n_levels;
-
-  // ---- weights into LDS, zero-padded (every wavefront of the group shares them)
-  for (int i = tid; i < HP * 16; i += 64 * kBwdWaves) {
+  for (int i = tid; i < HP * 16; i += T) {
     const int row = i >> 4, k = i & 15;
     const int f = slot_feature(k >> 1, k & 1, n_levels);
-    float v = 0.0f;
-    if (row < hid) v = f >= 0 ? a.W[0][row * d0 + f] : (f == -2 ? a.b[0][row] : 0.0f);
-    lds[M::oW0 + row * M::S0 + k] = v;
+    lds[M::oW0 + row * M::S0 + 8 * (k & 1) + (k >> 1)] = f >= 0 ? W(0, row, f) : (f == -2 ? b(0, row) : 0.0f);
   }
 #pragma unroll
   for (int l = 1; l <= M::NH; ++l)
-    for (int i = tid; i < HP * HP; i += 64 * kBwdWaves) {
-      const int row = i / HP, col = i % HP;
-      lds[M::oWh + (l - 1) * HP * M::SH + row * M::SH + col] = (row < hid && col < hid) ? a.W[l][row * hid + col] : 0.0f;
-    }
-  for (int i = tid; i < 32 * HP; i += 64 * kBwdWaves) {
-    const int row = i / HP, col = i % HP;
-    lds[M::oWo + row * M::SH + col] = (row < n_out && col < hid) ? a.W[NL - 1][row * hid + col] : 0.0f;
-  }
-  for (int i = tid; i < M::nB; i += 64 * kBwdWaves) {
+    for (int i = tid; i < HP * HP; i += T)
+      lds[M::oWh + (l - 1) * HP * M::SH + (i / HP) * M::SH + i % HP] = W(l, i / HP, i % HP);
+  for (int i = tid; i < 16 * HP; i += T) lds[M::oWo + (i / HP) * M::SH + i % HP] = W(NL - 1, i / HP, i % HP);
+  for (int i = tid; i < M::NH * MT * 32; i += T) {
     const int g = i / 32, e = i % 32;  // g = (l - 1) MT + mt, e = 16 h + 4 j + r
-    const int l = g / MT + 1 < NL - 1 ? g / MT + 1 : NL - 1;
-    const int mt = l == NL - 1 ? 0 : g % MT;
-    const int row = 32 * mt + 8 * ((e & 15) >> 2) + 4 * (e >> 4) + (e & 3);
-    const int rows = l == NL - 1 ? n_out : hid;
-    lds[M::oB + i] = row < rows ? a.b[l][row] : 0.0f;
+    lds[M::oB + i] = b(g / MT + 1, 32 * (g % MT) + 8 * ((e & 15) >> 2) + 4 * (e >> 4) + (e & 3));
   }
-  float *Dt = lds + M::oStage + wave * M::stage;
-  float *At = Dt + HP * kStS;
-  // the staging rows a layer input does not fill stay zero (first-layer K-slots 16..31)
-  for (int i = lane; i < M::stage; i += 64) Dt[i] = 0.0f;
+  if (tid < 16) lds[M::oBo + tid] = b(NL - 1, tid);
+}
+
+// Features of a lane half's K-slots: the values of sample_f32(), with the
+// loads of both levels in flight together (the level parameters come from
+// LDS, the address mode is one uniform branch).
+__device__ __forceinline__ void first_slots(const float *tab, int mode, float2 uv, int h, float (&x)[8]) {
+  LevelSel L[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) L[j] = *reinterpret_cast<const LevelSel *>(tab + kLevelFloats * (2 * h + j));
+  float fx[2], fy[2];
+  int i0[2], i1[2], j0[2], j1[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    float px = fmaf(uv.x, L[j].fw, -0.5f) + L[j].sx;
+    float py = fmaf(uv.y, L[j].fh, -0.5f) + L[j].sy;
+    px = fminf(fmaxf(px, -16777216.0f), 16777216.0f);
+    py = fminf(fmaxf(py, -16777216.0f), 16777216.0f);
+    const float xf = floorf(px), yf = floorf(py);
+    fx[j] = px - xf;
+    fy[j] = py - yf;
+    i0[j] = (int)xf;
+    j0[j] = (int)yf;
+  }
+  if (mode == 1) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      i0[j] = wrap_near(i0[j], L[j].w, L[j].rw);
+      j0[j] = wrap_near(j0[j], L[j].h, L[j].rh);
+      i1[j] = i0[j] + 1 == L[j].w ? 0 : i0[j] + 1;
+      j1[j] = j0[j] + 1 == L[j].h ? 0 : j0[j] + 1;
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      i1[j] = min(max(i0[j] + 1, 0), L[j].w - 1);
+      j1[j] = min(max(j0[j] + 1, 0), L[j].h - 1);
+      i0[j] = min(max(i0[j], 0), L[j].w - 1);
+      j0[j] = min(max(j0[j], 0), L[j].h - 1);
+    }
+  }
+  float t[2][4][3];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const auto *p = (const __attribute__((address_space(1))) float *)L[j].grid +
+                      ((int64_t)((q >> 1) ? j1[j] : j0[j]) * L[j].w + ((q & 1) ? i1[j] : i0[j])) * 3;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) t[j][q][c] = p[c];
+    }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const float gx = 1.0f - fx[j], gy = 1.0f - fy[j];
+    const float w[4] = {gx * gy, fx[j] * gy, gx * fy[j], fx[j] * fy[j]};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      float v = 0.0f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v = fmaf(w[q], t[j][q][c], v);
+      x[3 * j + c] = v;
+    }
+  }
+  x[6] = h ? uv.y : uv.x;
+  x[7] = h ? 0.0f : 1.0f;
+}
+
+// max(z, 0), 0 for NaN, as a median with an infinity that the compiler does
+// not see: fmaxf() costs a second instruction that quiets NaN first.
+__device__ __forceinline__ float relu(float z) {
+  float inf;
+  asm("s_mov_b32 %0, 0x7f800000" : "=s"(inf));
+  return __builtin_amdgcn_fmed3f(z, 0.0f, inf);
+}
+
+// ReLU outputs of tile mt of the first layer, and of hidden layer l from its
+// input tiles.
+template <int MT, int NL>
+__device__ __forceinline__ bf32x16 first_tile(const float *lds, int mt, int c32, int h, const float (&x)[8]) {
+  using M = BwdMap<MT, NL>;
+  bf32x16 z = {};
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const bf32x4 w = *reinterpret_cast<const bf32x4 *>(lds + M::oW0 + (32 * mt + c32) * M::S0 + 8 * h + 4 * q);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z = mfma32(w[r], x[4 * q + r], z);
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z[i] = relu(z[i]);
+  return z;
+}
+
+template <int MT, int NL>
+__device__ __forceinline__ bf32x16 hidden_tile(const float *lds, int l, int mt, int c32, int h,
+                                               const bf32x16 (&in)[MT]) {
+  using M = BwdMap<MT, NL>;
+  const float *Wl = lds + M::oWh + (l - 1) * M::HP * M::SH;
+  const bf32x4 *bp = reinterpret_cast<const bf32x4 *>(lds + M::bias(l, mt) + 16 * h);
+  const bf32x4 b0 = bp[0], b1 = bp[1], b2 = bp[2], b3 = bp[3];
+  bf32x16 z = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3],
+               b2[0], b2[1], b2[2], b2[3], b3[0], b3[1], b3[2], b3[3]};
+#pragma unroll
+  for (int q = 0; q < 4 * MT; ++q) {
+    const bf32x4 w = *reinterpret_cast<const bf32x4 *>(Wl + (32 * mt + c32) * M::SH + 8 * q + 4 * h);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z = mfma32(w[r], in[q >> 2][4 * (q & 3) + r], z);
+  }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) z[i] = relu(z[i]);
+  return z;
+}
+
+// Outputs of 32 samples as rows16 gives them, spread over the lanes: with at
+// most 8 rows the lanes that hold rows 8 .. 15 take the second samples of the
+// others (one value per lane and row instead of two, half of them padding).
+struct OutRows {
+  int n, row0, smp[2];  // vectors of 4 rows from row0, of samples smp[..]
+  bf32x4 z[2];
+};
+__device__ __forceinline__ OutRows spread_rows(int n_out, int g16, int c16, const bf32x4 &first, const bf32x4 &second) {
+  OutRows o;
+  o.z[0] = first;
+  o.z[1] = second;
+  o.n = 2;
+  o.row0 = 4 * g16;
+  o.smp[0] = c16;
+  o.smp[1] = 16 + c16;
+  if (n_out <= 8) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {  // lanes 32 .. 63 get `second` of lanes 0 .. 31
+      const auto t = __builtin_amdgcn_permlane32_swap(__float_as_uint(first[r]), __float_as_uint(second[r]), false, false);
+      o.z[0][r] = __uint_as_float(t[0]);
+    }
+    o.n = 1;
+    o.row0 = 4 * (g16 & 1);
+    o.smp[0] = 16 * (g16 >> 1) + c16;
+  }
+  return o;
+}
+
+// Product of a 16-row matrix (wt(q): this lane's elements for K-steps 4 q ..
+// 4 q + 3) with MT accumulator tiles, plus `bias` rows: rows 4 (lane / 16) + r of samples
+// lane % 16 (first) and 16 + lane % 16 (second).
+template <int MT, class FW>
+__device__ __forceinline__ void rows16(FW wt, const bf32x16 (&in)[MT], bf32x4 bias, bf32x4 &first, bf32x4 &second) {
+  bf32x16 z = {bias[0], bias[1], bias[2], bias[3], bias[0], bias[1], bias[2], bias[3], 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+  for (int q = 0; q < 4 * MT; ++q) {
+    const bf32x4 w = wt(q);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      z = __builtin_amdgcn_mfma_f32_16x16x1f32(w[r], in[q >> 2][4 * (q & 3) + r], z, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    first[r] = z[r] + z[8 + r];
+    second[r] = z[4 + r] + z[12 + r];
+  }
+}
+
+template <int MT, int NL>
+__global__ __launch_bounds__((64 * backward_waves(MT, NL)))
+__attribute__((amdgpu_waves_per_eu((backward_waves(MT, NL) / 4), (backward_waves(MT, NL) / 4))))
+void backward_mfma_kernel(BackwardArgs a) {
+  using M = BwdMap<MT, NL>;
+  constexpr int HP = M::HP, NH1 = M::NH > 0 ? M::NH : 1;
+  extern __shared__ float bwd_lds[];
+  float *lds = bwd_lds;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, h = lane >> 5, c32 = lane & 31, c16 = lane & 15, g16 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hid = a.dims[1], n_out = a.dims[NL], d0 = a.dims[0];
+  const int n_levels = a.lat.n_levels;
+
+  load_weights<MT, NL, 64 * M::waves>(
+      lds, tid, n_levels,
+      [&](int l, int row, int col) {
+        const int rows = l == NL - 1 ? n_out : hid, cols = l == 0 ? d0 : hid;
+        return row < rows && col < cols ? a.W[l][row * cols + col] : 0.0f;
+      },
+      [&](int l, int row) { return row < (l == NL - 1 ? n_out : hid) ? a.b[l][row] : 0.0f; });
+  load_levels(lds + M::oLv, a.lat, tid);
+  float *Dt = lds + M::oStage + wave * M::stage;  // deltas
+  float *At = Dt + 8 * M::SQ;                     // layer inputs
   __syncthreads();
 
-  const float *W0s = lds + M::oW0;
-  const float *Wo = lds + M::oWo;
   const bf32x16 zero = {};
 
-  // weight-gradient accumulators: first layer [mt] (columns = K-slots), hidden
-  // layers [l][mt][nt], output [nt]; bias gradients of rows `lane` (hidden)
-  bf32x16 g0[MT], gh[M::NH > 0 ? M::NH : 1][MT][MT], go[MT];
-  float gbh[M::NH > 0 ? M::NH : 1], gbo = 0.0f;
+  // weight-gradient accumulators: first layer (16-row tiles, columns =
+  // K-slots), hidden layers [l][mt][nt], output layer (16-column tiles); bias
+  // gradients of rows `lane`
+  bf32x4 g0[2 * MT] = {}, go[2 * MT] = {};
+  bf32x16 gh[NH1][MT][MT];
+  float gbh[NH1], gbo = 0.0f;
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    g0[i] = zero;
-    go[i] = zero;
+  for (int l = 0; l < NH1; ++l) {
+    gbh[l] = 0.0f;
 #pragma unroll
-    for (int l = 0; l < (M::NH > 0 ? M::NH : 1); ++l)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
       for (int j = 0; j < MT; ++j) gh[l][i][j] = zero;
   }
-#pragma unroll
-  for (int l = 0; l < (M::NH > 0 ? M::NH : 1); ++l) gbh[l] = 0.0f;
 
-  // staging helpers: a tile in accumulator layout -> rows [row0, row0 + 32)
-  // of a transposed buffer (column of sample n: 16 (n % 2) + n / 2)
-  const int scol = 16 * (c32 & 1) + (c32 >> 1);
-  auto stage_tile = [&](float *buf, int row0, const bf32x16 &t) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) buf[(row0 + 8 * (i >> 2) + 4 * h + (i & 3)) * kStS + scol] = t[i];
+  // element (row, sample) of a staged buffer, and float4 q of a row
+  auto at = [](int row, int smp) { return (smp >> 2) * M::SQ + 4 * row + (smp & 3); };
+  auto quad = [](const float *buf, int row, int q) {
+    return *reinterpret_cast<const bf32x4 *>(buf + q * M::SQ + 4 * row);
   };
-  // the 16 K-step operands of row `row` (samples 2 s + h, s < 16)
-  auto stage_row = [&](const float *buf, int row, float (&v)[16]) {
-    const bf32x4 *p = reinterpret_cast<const bf32x4 *>(buf + row * kStS + 16 * h);
+  // a tile in accumulator layout -> rows [row0, row0 + 32) of a buffer
+  // (tile_at: this lane's first element)
+  auto stage_tile = [](float *buf, int tile_at, int row0, const bf32x16 &t) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const bf32x4 x = p[q];
-      v[4 * q] = x[0];
-      v[4 * q + 1] = x[1];
-      v[4 * q + 2] = x[2];
-      v[4 * q + 3] = x[3];
-    }
+    for (int i = 0; i < 16; ++i) buf[4 * (row0 + 8 * (i >> 2) + (i & 3)) + tile_at] = t[i];
+  };
+  // ReLU mask: v where the activation staged in rows [row0, row0 + 32) of At
+  // is positive (read back from LDS: its registers are free after staging)
+  auto mask_tile = [](const float *buf, int tile_at, int row0, const bf32x16 &v) {
+    bf32x16 m;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) m[i] = buf[4 * (row0 + 8 * (i >> 2) + (i & 3)) + tile_at] > 0.0f ? v[i] : 0.0f;
+    return m;
   };
   // sum over the 32 samples of staged row `row`
   auto row_sum = [&](const float *buf, int row) {
-    const bf32x4 *p = reinterpret_cast<const bf32x4 *>(buf + row * kStS);
     float sum = 0.0f;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const bf32x4 x = p[q];
+      const bf32x4 x = quad(buf, row, q);
       sum += (x[0] + x[1]) + (x[2] + x[3]);
     }
     return sum;
   };
-  // dW += Dt(MT_D tiles) At(NT_A tiles)^T over the 16 K-steps
-  auto accum_dw = [&](auto &&acc, int mtn, int ntn) {
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int mt = 0; mt < mtn; ++mt) {
-      float av[16];
-      stage_row(Dt, 32 * mt + c32, av);
-#pragma unroll
-      for (int nt = 0; nt < ntn; ++nt) {
-        float bv[16];
-        stage_row(At, 32 * nt + c32, bv);
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc(mt, nt) = mfma32(av[q], bv[q], acc(mt, nt));
-      }
-    }
-    asm volatile("" ::: "memory");
-  };
+  auto lds_order = [] { asm volatile("" ::: "memory"); };  // a wavefront's LDS accesses complete in order
 
   const int64_t n_chunks = (a.n + kBwdChunk - 1) / kBwdChunk;
-  const int64_t stride = (int64_t)gridDim.x * kBwdWaves;
-  for (int64_t chunk = (int64_t)blockIdx.x * kBwdWaves + wave; chunk < n_chunks; chunk += stride) {
+  const int64_t stride = (int64_t)gridDim.x * M::waves;
+  const int64_t first = (int64_t)blockIdx.x * M::waves + wave;
+  auto load_uv = [&](int64_t chunk) {
     const int64_t smp = chunk * kBwdChunk + c32;
-    const bool valid = smp < a.n;
-    const float2 uv = a.uv[valid ? smp : a.n - 1];
-
-    // ---- features of this lane half's K-slots
-    float x[8];
-    {
-      const float3 c0 = sample_f32(a.lat.lv[2 * h], uv.x, uv.y, a.lat.address);
-      const float3 c1 = sample_f32(a.lat.lv[2 * h + 1], uv.x, uv.y, a.lat.address);
-      x[0] = c0.x; x[1] = c0.y; x[2] = c0.z;
-      x[3] = c1.x; x[4] = c1.y; x[5] = c1.z;
-      x[6] = h ? uv.y : uv.x;
-      x[7] = h ? 0.0f : 1.0f;
-    }
+    return a.uv[smp < a.n ? smp : a.n - 1];
+  };
+  float2 uv_next = load_uv(first);
+  for (int64_t chunk = first; chunk < n_chunks; chunk += stride) {
+    const float2 uv = uv_next;
+    uv_next = load_uv(chunk + stride < n_chunks ? chunk + stride : chunk);
+    const int64_t s0 = chunk * kBwdChunk;
+    // weights, level parameters and addresses are read or computed where they
+    // are used, not held in registers across steps (opaque_zero)
+    const float *wl = lds + opaque_zero((int)chunk);
+    const int ln = lane + opaque_zero((int)chunk);
+    const int h = ln >> 5, c32 = ln & 31, c16 = ln & 15, g16 = ln >> 4;
+    const int tile_at = at(4 * h, c32);
 
     // ---- forward
+    float x[8];
+    first_slots(wl + M::oLv, a.lat.address, uv, h, x);
     bf32x16 act[NL - 1][MT];  // ReLU outputs of the hidden layers
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      bf32x16 z = zero;
+    for (int mt = 0; mt < MT; ++mt) act[0][mt] = first_tile<MT, NL>(wl, mt, c32, h, x);
 #pragma unroll
-      for (int s = 0; s < 8; ++s) z = mfma32(W0s[(32 * mt + c32) * M::S0 + 2 * s + h], x[s], z);
+    for (int l = 1; l <= M::NH; ++l)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) z[i] = fmaxf(z[i], 0.0f);
-      act[0][mt] = z;
-    }
-#pragma unroll
-    for (int l = 1; l <= M::NH; ++l) {
-      const float *Wl = lds + M::oWh + (l - 1) * HP * M::SH;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const bf32x4 *bp = reinterpret_cast<const bf32x4 *>(lds + M::bias(l, mt) + 16 * h);
-        const bf32x4 b0 = bp[0], b1 = bp[1], b2 = bp[2], b3 = bp[3];
-        bf32x16 z = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3],
-                     b2[0], b2[1], b2[2], b2[3], b3[0], b3[1], b3[2], b3[3]};
-#pragma unroll
-        for (int s = 0; s < 16 * MT; ++s)
-          z = mfma32(Wl[(32 * mt + c32) * M::SH + chain_unit(s, h)], act[l - 1][s >> 4][s & 15], z);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) z[i] = fmaxf(z[i], 0.0f);
-        act[l][mt] = z;
-      }
-    }
-    bf32x16 dout;
-    {
-      const bf32x4 *bp = reinterpret_cast<const bf32x4 *>(lds + M::bias(NL - 1, 0) + 16 * h);
-      const bf32x4 b0 = bp[0], b1 = bp[1];
-      bf32x16 z = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3], 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-      for (int s = 0; s < 16 * MT; ++s)
-        z = mfma32(Wo[c32 * M::SH + chain_unit(s, h)], act[NL - 2][s >> 4][s & 15], z);
-      // output deltas: g f (1 - f) on rows 8 j + 4 h + r < n_out (j < 2)
-      dout = zero;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int row = 8 * (i >> 2) + 4 * h + (i & 3);
-        if (row < n_out && valid) {
-          const float f = 1.0f / (1.0f + expf(-z[i]));
-          dout[i] = a.grad_out[smp * n_out + row] * f * (1.0f - f);
-        }
-      }
-    }
+      for (int mt = 0; mt < MT; ++mt) act[l][mt] = hidden_tile<MT, NL>(wl, l, mt, c32, h, act[l - 1]);
+    bf32x4 zo[2];
+    rows16<MT>([&](int q) { return *reinterpret_cast<const bf32x4 *>(wl + M::oWo + c16 * M::SH + 8 * q + 4 * h); }, act[NL - 2],
+               *reinterpret_cast<const bf32x4 *>(wl + M::oBo + 4 * g16), zo[0], zo[1]);
 
-    // ---- output layer: weight and bias gradients, delta of the last hidden layer
-    stage_tile(Dt, 0, dout);
+    // ---- output deltas g f (1 - f), staged
+    lds_order();
+    const OutRows zr = spread_rows(n_out, g16, c16, zo[0], zo[1]);
+    auto out_delta = [&](int e) {
+      float g[4];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) stage_tile(At, 32 * mt, act[NL - 2][mt]);
-    accum_dw([&](int, int nt) -> bf32x16 & { return go[nt]; }, 1, MT);
-    if (lane < 16) gbo += row_sum(Dt, lane);
+      for (int r = 0; r < 4; ++r) {
+        const int64_t smp = min(s0 + zr.smp[e], a.n - 1);
+        g[r] = a.grad_out[smp * n_out + min(zr.row0 + r, n_out - 1)];
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = zr.row0 + r;
+        const float f = 1.0f / (1.0f + expf(-zr.z[e][r]));
+        const int keep = row < n_out && s0 + zr.smp[e] < a.n ? -1 : 0;  // a select here becomes branches
+        Dt[at(row, zr.smp[e])] = __int_as_float(__float_as_int(g[r] * f * (1.0f - f)) & keep);
+      }
+    };
+    out_delta(0);
+    if (zr.n > 1) {
+      out_delta(1);
+    } else {  // rows 8 .. 15 of the padded product
+#pragma unroll
+      for (int r = 0; r < 4; ++r) Dt[at(8 + zr.row0 + r, zr.smp[0])] = 0.0f;
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) stage_tile(At, tile_at, 32 * mt, act[NL - 2][mt]);
+    lds_order();
+    // ---- output layer: delta of the last hidden layer, weight and bias gradients
     bf32x16 del[MT];
     {
-      const int tk = n_out > 8 ? 8 : 4;  // K-steps covering rows 0 .. n_out - 1
+      auto steps = [&](int t0) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        bf32x16 z = zero;
+        for (int t = t0; t < t0 + 4; ++t) {
+          const float dv = Dt[at(2 * t + h, c32)];
 #pragma unroll
-        for (int t = 0; t < 8; ++t)
-          if (t < tk) z = mfma32(Wo[(8 * (t >> 2) + 4 * h + (t & 3)) * M::SH + 32 * mt + c32], dout[t], z);
+          for (int mt = 0; mt < MT; ++mt)
+            del[mt] = mfma32(wl[M::oWo + (2 * t + h) * M::SH + 32 * mt + c32], dv, del[mt]);
+        }
+      };
 #pragma unroll
-        for (int i = 0; i < 16; ++i) del[mt][i] = act[NL - 2][mt][i] > 0.0f ? z[i] : 0.0f;
+      for (int mt = 0; mt < MT; ++mt) del[mt] = zero;
+      steps(0);
+      if (n_out > 8) steps(4);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) del[mt] = mask_tile(At, tile_at, 32 * mt, del[mt]);
+    }
+    {
+      const bf32x4 a0 = quad(Dt, c16, 2 * g16), a1 = quad(Dt, c16, 2 * g16 + 1);
+#pragma unroll
+      for (int nt = 0; nt < 2 * MT; ++nt) {
+        const bf32x4 b0 = quad(At, 16 * nt + c16, 2 * g16), b1 = quad(At, 16 * nt + c16, 2 * g16 + 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) go[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[q], b0[q], go[nt], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) go[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[q], b1[q], go[nt], 0, 0, 0);
       }
+      if (ln < 16) gbo += row_sum(Dt, ln);
     }
     // ---- hidden layers, top down
 #pragma unroll
     for (int l = M::NH; l >= 1; --l) {
-      const float *Wl = lds + M::oWh + (l - 1) * HP * M::SH;
+      const float *Wl = wl + M::oWh + (l - 1) * HP * M::SH;
+      lds_order();
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        stage_tile(Dt, 32 * mt, del[mt]);
-        stage_tile(At, 32 * mt, act[l - 1][mt]);
+        stage_tile(Dt, tile_at, 32 * mt, del[mt]);
+        stage_tile(At, tile_at, 32 * mt, act[l - 1][mt]);
       }
-      accum_dw([&](int mt, int nt) -> bf32x16 & { return gh[l - 1][mt][nt]; }, MT, MT);
-      if (lane < HP) gbh[l - 1] += row_sum(Dt, lane);
+      lds_order();
       bf32x16 nd[MT];
 #pragma unroll
+      for (int mt = 0; mt < MT; ++mt) nd[mt] = zero;
+#pragma unroll
+      for (int q = 0; q < 4 * MT; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt)
+            nd[mt] = mfma32(Wl[(8 * q + 4 * h + r) * M::SH + 32 * mt + c32], del[q >> 2][4 * (q & 3) + r], nd[mt]);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) nd[mt] = mask_tile(At, tile_at, 32 * mt, nd[mt]);
+#pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        bf32x16 z = zero;
+        bf32x4 av[4];
 #pragma unroll
-        for (int s = 0; s < 16 * MT; ++s)
-          z = mfma32(Wl[chain_unit(s, h) * M::SH + 32 * mt + c32], del[s >> 4][s & 15], z);
+        for (int q = 0; q < 4; ++q) av[q] = quad(Dt, 32 * mt + c32, 4 * h + q);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) nd[mt][i] = act[l - 1][mt][i] > 0.0f ? z[i] : 0.0f;
+        for (int nt = 0; nt < MT; ++nt)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const bf32x4 bv = quad(At, 32 * nt + c32, 4 * h + q);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) gh[l - 1][mt][nt] = mfma32(av[q][r], bv[r], gh[l - 1][mt][nt]);
+          }
       }
+      if (ln < HP) gbh[l - 1] += row_sum(Dt, ln);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) del[mt] = nd[mt];
     }
     // ---- first layer: weight gradients over the K-slots (slot 14 = bias)
+    lds_order();
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) stage_tile(Dt, 32 * mt, del[mt]);
+    for (int mt = 0; mt < MT; ++mt) stage_tile(Dt, tile_at, 32 * mt, del[mt]);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) At[(2 * s + h) * kStS + scol] = x[s];
-    accum_dw([&](int mt, int) -> bf32x16 & { return g0[mt]; }, MT, 1);
-    // ---- feature gradient dx = W0^T D0: rows = latent features
+    for (int s = 0; s < 8; ++s) At[at(2 * s + h, c32)] = x[s];
+    lds_order();
     {
-      const int f = c32;  // feature of A-operand row c32
-      const int lvl = f / 3;
-      const int slot = (lvl < n_levels && f < 12) ? 2 * (3 * (lvl & 1) + f % 3) + (lvl >> 1) : -1;
-      bf32x16 z = zero;
+      const bf32x4 b0 = quad(At, c16, 2 * g16), b1 = quad(At, c16, 2 * g16 + 1);
 #pragma unroll
-      for (int s = 0; s < 16 * MT; ++s) {
-        const float w = slot >= 0 ? W0s[chain_unit(s, h) * M::S0 + slot] : 0.0f;
-        z = mfma32(w, del[s >> 4][s & 15], z);
+      for (int mt = 0; mt < 2 * MT; ++mt) {
+        const bf32x4 a0 = quad(Dt, 16 * mt + c16, 2 * g16), a1 = quad(Dt, 16 * mt + c16, 2 * g16 + 1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g0[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[q], b0[q], g0[mt], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g0[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[q], b1[q], g0[mt], 0, 0, 0);
       }
-      // the row of a.dx: the feature gradients, then u, v
-      if (valid) {
+    }
+    // ---- feature gradient dx = W0^T D0, one row of a.dx per sample: the
+    // latent features' gradients, then u, v (slots 12 and 13)
+    {
+      const int lvl = c16 / 3;
+      const int slot = lvl < n_levels && c16 < 12 ? 8 * (lvl >> 1) + 3 * (lvl & 1) + c16 % 3 : 15;  // 15: zeros
+      bf32x4 dx[2];
+      const bf32x4 none = {};
+      rows16<MT>(
+          [&](int q) {
+            const float *w = wl + M::oW0 + (8 * q + 4 * h) * M::S0 + slot;
+            return bf32x4{w[0], w[M::S0], w[2 * M::S0], w[3 * M::S0]};
+          },
+          del, none, dx[0], dx[1]);
+      if (4 * g16 < a.dx_stride) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int row0 = 8 * j + 4 * h;
-          if (row0 >= a.dx_stride) continue;
-          float o[4];
+        for (int e = 0; e < 2; ++e) {
+          const int smp = 16 * e + c16;
+          const float u = At[at(12, smp)], v = At[at(13, smp)];
+          float4 o;
+          float *po = &o.x;
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            o[r] = row0 + r == a.n_feat ? uv.x : row0 + r == a.n_feat + 1 ? uv.y : z[4 * j + r];
-          *reinterpret_cast<float4 *>(a.dx + smp * a.dx_stride + row0) = make_float4(o[0], o[1], o[2], o[3]);
+            po[r] = 4 * g16 + r == a.n_feat ? u : 4 * g16 + r == a.n_feat + 1 ? v : dx[e][r];
+          if (s0 + smp < a.n) *reinterpret_cast<float4 *>(a.dx + (s0 + smp) * a.dx_stride + 4 * g16) = o;
         }
       }
     }
   }
 
   // ---- this wavefront's partial sums (parameters in unpadded order)
-  float *part = a.wpart + ((int64_t)blockIdx.x * kBwdWaves + wave) * a.n_params;
+  float *part = a.wpart + ((int64_t)blockIdx.x * M::waves + wave) * a.n_params;
   int off = 0;
+  {
+    const int f = slot_feature(c16 >> 1, c16 & 1, n_levels);
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < 2 * MT; ++mt)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int row = 32 * mt + 8 * (i >> 2) + 4 * h + (i & 3);
-      const int k = c32;
-      if (row < hid && k < 16) {
-        const int f = slot_feature(k >> 1, k & 1, n_levels);
-        if (f >= 0) part[off + row * d0 + f] = g0[mt][i];
-        if (f == -2) part[off + hid * d0 + row] = g0[mt][i];
+      for (int r = 0; r < 4; ++r) {
+        const int row = 16 * mt + 4 * g16 + r;
+        if (row < hid && f >= 0) part[off + row * d0 + f] = g0[mt][r];
+        if (row < hid && f == -2) part[off + hid * d0 + row] = g0[mt][r];
       }
-    }
+  }
   off += hid * d0 + hid;
 #pragma unroll
   for (int l = 0; l < M::NH; ++l) {
@@ -512,11 +746,11 @@ void backward_mfma_kernel(BackwardArgs a) {
     off += hid * hid + hid;
   }
 #pragma unroll
-  for (int nt = 0; nt < MT; ++nt)
+  for (int nt = 0; nt < 2 * MT; ++nt)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int row = 8 * (i >> 2) + 4 * h + (i & 3), col = 32 * nt + c32;
-      if (row < n_out && col < hid) part[off + row * hid + col] = go[nt][i];
+    for (int r = 0; r < 4; ++r) {
+      const int row = 4 * g16 + r, col = 16 * nt + c16;
+      if (row < n_out && col < hid) part[off + row * hid + col] = go[nt][r];
     }
   if (lane < n_out) part[off + n_out * hid + lane] = gbo;
 }
@@ -662,14 +896,6 @@ __device__ __forceinline__ void window_axis(int k, int p, int len, int n0, float
   }
   c0 = lo;
   nc = hi - lo + 1;
-}
-
-// i modulo n for |i| <= 2^25, with rn about 1 / n: the quotient is off by at
-// most one (an integer division takes several times as long).
-__device__ __forceinline__ int wrap_near(int i, int n, float rn) {
-  int r = i - n * (int)floorf((float)i * rn);
-  r += r < 0 ? n : 0;
-  return r >= n ? r - n : r;
 }
 
 // Offset of cell coordinate i in a window axis (outside [0, nc): not in it).
@@ -936,156 +1162,102 @@ __global__ __launch_bounds__(256) void scatter_direct_kernel(BackwardArgs a) {
 // 32-sample steps), ending in the sigmoid and the store. Weights come from
 // the packed FP32 image (per layer W [rows_pad][cols_pad], then b).
 // ---------------------------------------------------------------------------
+constexpr int kFwdWaves = 8;  // wavefronts per workgroup, two per SIMD
+
 template <int MT, int NL>
-__global__ __launch_bounds__(64 * kBwdWaves) void forward_mfma_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(64 * kFwdWaves) __attribute__((amdgpu_waves_per_eu(kFwdWaves / 4)))
+void forward_mfma_kernel(DecodeArgs a) {
   using M = BwdMap<MT, NL>;
-  constexpr int HP = M::HP;
   extern __shared__ float fwd_lds[];
   float *lds = fwd_lds;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, h = lane >> 5, c32 = lane & 31;
-  const int wave = tid >> 6;
+  const int lane = tid & 63, h = lane >> 5, c32 = lane & 31, c16 = lane & 15, g16 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const PackLayout &L = a.lay;
-  const int n_out = a.n_out, n_levels = a.lat.n_levels;
-  const float *W0 = reinterpret_cast<const float *>(a.packed + L.w_off[0]);
-  const float *B0 = reinterpret_cast<const float *>(a.packed + L.b_off[0]);
-  const int hid = L.rows_pad[0] < HP ? L.rows_pad[0] : HP;  // padded rows hold zero weights
+  const int n_out = a.n_out;
 
-  for (int i = tid; i < HP * 16; i += 64 * kBwdWaves) {
-    const int row = i >> 4, k = i & 15;
-    const int f = slot_feature(k >> 1, k & 1, n_levels);
-    float v = 0.0f;
-    if (row < hid) v = f >= 0 ? W0[row * L.cols_pad[0] + f] : (f == -2 ? B0[row] : 0.0f);
-    lds[M::oW0 + row * M::S0 + k] = v;
-  }
-#pragma unroll
-  for (int l = 1; l <= M::NH; ++l) {
-    const float *Wl = reinterpret_cast<const float *>(a.packed + L.w_off[l]);
-    for (int i = tid; i < HP * HP; i += 64 * kBwdWaves) {
-      const int row = i / HP, col = i % HP;
-      lds[M::oWh + (l - 1) * HP * M::SH + row * M::SH + col] =
-          (row < L.rows_pad[l] && col < L.cols_pad[l]) ? Wl[row * L.cols_pad[l] + col] : 0.0f;
-    }
-  }
-  {
-    const float *Wo = reinterpret_cast<const float *>(a.packed + L.w_off[NL - 1]);
-    for (int i = tid; i < 32 * HP; i += 64 * kBwdWaves) {
-      const int row = i / HP, col = i % HP;
-      lds[M::oWo + row * M::SH + col] =
-          (row < L.rows_pad[NL - 1] && col < L.cols_pad[NL - 1]) ? Wo[row * L.cols_pad[NL - 1] + col] : 0.0f;
-    }
-  }
-  for (int i = tid; i < M::nB; i += 64 * kBwdWaves) {
-    const int g = i / 32, e = i % 32;  // g = (l - 1) MT + mt, e = 16 h + 4 j + r
-    const int l = g / MT + 1 < NL - 1 ? g / MT + 1 : NL - 1;
-    const int mt = l == NL - 1 ? 0 : g % MT;
-    const int row = 32 * mt + 8 * ((e & 15) >> 2) + 4 * (e >> 4) + (e & 3);
-    const float *Bl = reinterpret_cast<const float *>(a.packed + L.b_off[l]);
-    lds[M::oB + i] = row < L.rows_pad[l] ? Bl[row] : 0.0f;
-  }
+  load_weights<MT, NL, 64 * kFwdWaves>(
+      lds, tid, a.lat.n_levels,
+      [&](int l, int row, int col) {  // padded rows and columns hold zero weights
+        return row < L.rows_pad[l] && col < L.cols_pad[l]
+                   ? reinterpret_cast<const float *>(a.packed + L.w_off[l])[row * L.cols_pad[l] + col]
+                   : 0.0f;
+      },
+      [&](int l, int row) {
+        return row < L.rows_pad[l] ? reinterpret_cast<const float *>(a.packed + L.b_off[l])[row] : 0.0f;
+      });
+  load_levels(lds + M::oLv, a.lat, tid);
   __syncthreads();
 
-  const float *W0s = lds + M::oW0;
-  const float *Wos = lds + M::oWo;
-  const bf32x16 zero = {};
   const int64_t n_chunks = (a.n + kBwdChunk - 1) / kBwdChunk;
-  const int64_t stride = (int64_t)gridDim.x * kBwdWaves;
-  for (int64_t chunk = (int64_t)blockIdx.x * kBwdWaves + wave; chunk < n_chunks; chunk += stride) {
+  const int64_t stride = (int64_t)gridDim.x * kFwdWaves;
+  const int64_t first = (int64_t)blockIdx.x * kFwdWaves + wave;
+  auto load_uv = [&](int64_t chunk) {
     const int64_t smp = chunk * kBwdChunk + c32;
-    const bool valid = smp < a.n;
-    const float2 uv = a.uv[valid ? smp : a.n - 1];
+    return a.uv[smp < a.n ? smp : a.n - 1];
+  };
+  float2 uv_next = load_uv(first);
+  for (int64_t chunk = first; chunk < n_chunks; chunk += stride) {
+    const float2 uv = uv_next;
+    uv_next = load_uv(chunk + stride < n_chunks ? chunk + stride : chunk);
+    const float *wl = lds + opaque_zero((int)chunk);  // as in the backward
     float x[8];
-    {
-      const float3 c0 = sample_f32(a.lat.lv[2 * h], uv.x, uv.y, a.lat.address);
-      const float3 c1 = sample_f32(a.lat.lv[2 * h + 1], uv.x, uv.y, a.lat.address);
-      x[0] = c0.x; x[1] = c0.y; x[2] = c0.z;
-      x[3] = c1.x; x[4] = c1.y; x[5] = c1.z;
-      x[6] = h ? uv.y : uv.x;
-      x[7] = h ? 0.0f : 1.0f;
-    }
-    bf32x16 act[MT];
+    first_slots(wl + M::oLv, a.lat.address, uv, h, x);
+    bf32x16 act[MT], nx[MT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      bf32x16 z = zero;
-#pragma unroll
-      for (int s = 0; s < 8; ++s) z = mfma32(W0s[(32 * mt + c32) * M::S0 + 2 * s + h], x[s], z);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) z[i] = fmaxf(z[i], 0.0f);
-      act[mt] = z;
-    }
+    for (int mt = 0; mt < MT; ++mt) act[mt] = first_tile<MT, NL>(wl, mt, c32, h, x);
 #pragma unroll
     for (int l = 1; l <= M::NH; ++l) {
-      const float *Wl = lds + M::oWh + (l - 1) * HP * M::SH;
-      bf32x16 nx[MT];
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) {
-        const bf32x4 *bp = reinterpret_cast<const bf32x4 *>(lds + M::bias(l, mt) + 16 * h);
-        const bf32x4 b0 = bp[0], b1 = bp[1], b2 = bp[2], b3 = bp[3];
-        bf32x16 z = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3],
-                     b2[0], b2[1], b2[2], b2[3], b3[0], b3[1], b3[2], b3[3]};
-#pragma unroll
-        for (int s = 0; s < 16 * MT; ++s)
-          z = mfma32(Wl[(32 * mt + c32) * M::SH + chain_unit(s, h)], act[s >> 4][s & 15], z);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) z[i] = fmaxf(z[i], 0.0f);
-        nx[mt] = z;
-      }
+      for (int mt = 0; mt < MT; ++mt) nx[mt] = hidden_tile<MT, NL>(wl, l, mt, c32, h, act);
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) act[mt] = nx[mt];
     }
-    const bf32x4 *bp = reinterpret_cast<const bf32x4 *>(lds + M::bias(NL - 1, 0) + 16 * h);
-    const bf32x4 b0 = bp[0], b1 = bp[1];
-    bf32x16 z = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3], 0, 0, 0, 0, 0, 0, 0, 0};
+    bf32x4 zo[2];
+    rows16<MT>([&](int q) { return *reinterpret_cast<const bf32x4 *>(wl + M::oWo + c16 * M::SH + 8 * q + 4 * h); }, act,
+               *reinterpret_cast<const bf32x4 *>(wl + M::oBo + 4 * g16), zo[0], zo[1]);
+    const OutRows zr = spread_rows(n_out, g16, c16, zo[0], zo[1]);
+    auto store = [&](int e) {
+      const int64_t smp = chunk * kBwdChunk + zr.smp[e];
+      const int row0 = zr.row0;
+      float f[4];
 #pragma unroll
-    for (int s = 0; s < 16 * MT; ++s) z = mfma32(Wos[c32 * M::SH + chain_unit(s, h)], act[s >> 4][s & 15], z);
-    if (valid) {
-      // rows 8 j + 4 h + r (j < 2, r < 4) of this lane's sample
+      for (int r = 0; r < 4; ++r) f[r] = 1.0f / (1.0f + expf(-zr.z[e][r]));
+      if (smp >= a.n || row0 >= n_out) return;
+      if (a.out_f16) {
+        _Float16 *o = reinterpret_cast<_Float16 *>(a.out) + smp * n_out + row0;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int row0 = 8 * j + 4 * h;
-        if (row0 >= n_out) continue;
-        float f[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) f[r] = 1.0f / (1.0f + expf(-z[4 * j + r]));
-        if (a.out_f16) {
-          _Float16 *o = reinterpret_cast<_Float16 *>(a.out) + smp * n_out + row0;
+        for (int r = 0; r < 4; ++r)
+          if (row0 + r < n_out) o[r] = (_Float16)f[r];
+      } else {
+        float *o = reinterpret_cast<float *>(a.out) + smp * n_out + row0;
+        if ((n_out & 3) == 0) {
+          *reinterpret_cast<float4 *>(o) = make_float4(f[0], f[1], f[2], f[3]);
+        } else {
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            if (row0 + r < n_out) o[r] = (_Float16)f[r];
-        } else {
-          float *o = reinterpret_cast<float *>(a.out) + smp * n_out + row0;
-          if ((n_out & 3) == 0) {
-            *reinterpret_cast<float4 *>(o) = make_float4(f[0], f[1], f[2], f[3]);
-          } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (row0 + r < n_out) o[r] = f[r];
-          }
+            if (row0 + r < n_out) o[r] = f[r];
         }
       }
-    }
+    };
+    store(0);
+    if (zr.n > 1) store(1);
   }
 }
 
 hipError_t launch_forward_f32(const DecodeArgs &a, const MlpShape &s, hipStream_t st) {
-  const int groups = backward_groups(a.n);
+  const int mt = s.hid > 32 ? 2 : 1;
   auto go = [&](auto kernel, size_t floats) {
-    hipLaunchKernelGGL(kernel, dim3(groups), dim3(64 * kBwdWaves), floats * sizeof(float), st, a);
+    hipLaunchKernelGGL(kernel, dim3(backward_groups(a.n, kFwdWaves)), dim3(64 * kFwdWaves), floats * sizeof(float), st, a);
     return hipGetLastError();
   };
-  const int mt = s.hid > 32 ? 2 : 1;
-  if (mt == 1) {
-    switch (s.n_layers) {
-      case 2: return go(forward_mfma_kernel<1, 2>, BwdMap<1, 2>::oStage);
-      case 3: return go(forward_mfma_kernel<1, 3>, BwdMap<1, 3>::oStage);
-      case 4: return go(forward_mfma_kernel<1, 4>, BwdMap<1, 4>::oStage);
-      default: return hipErrorInvalidValue;
-    }
-  }
-  switch (s.n_layers) {
-    case 2: return go(forward_mfma_kernel<2, 2>, BwdMap<2, 2>::oStage);
-    case 3: return go(forward_mfma_kernel<2, 3>, BwdMap<2, 3>::oStage);
-    case 4: return go(forward_mfma_kernel<2, 4>, BwdMap<2, 4>::oStage);
+  switch (10 * mt + s.n_layers) {
+    case 12: return go(forward_mfma_kernel<1, 2>, BwdMap<1, 2>::oStage);
+    case 13: return go(forward_mfma_kernel<1, 3>, BwdMap<1, 3>::oStage);
+    case 14: return go(forward_mfma_kernel<1, 4>, BwdMap<1, 4>::oStage);
+    case 22: return go(forward_mfma_kernel<2, 2>, BwdMap<2, 2>::oStage);
+    case 23: return go(forward_mfma_kernel<2, 3>, BwdMap<2, 3>::oStage);
+    case 24: return go(forward_mfma_kernel<2, 4>, BwdMap<2, 4>::oStage);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1099,26 +1271,20 @@ hipError_t launch_backward(const BackwardArgs &a, const MlpShape &s, float *cons
   }
   hipError_t e;
   {
-    const int groups = a.n_blocks / kBwdWaves;
+    const int mt = s.hid > 32 ? 2 : 1;
+    const int waves = backward_waves(mt, s.n_layers);
     auto go = [&](auto kernel, size_t floats) {
-      hipLaunchKernelGGL(kernel, dim3(groups), dim3(64 * kBwdWaves), floats * sizeof(float), st, a);
+      hipLaunchKernelGGL(kernel, dim3(a.n_blocks / waves), dim3(64 * waves), floats * sizeof(float), st, a);
       return hipGetLastError();
     };
-    const int mt = s.hid > 32 ? 2 : 1;
-    if (mt == 1) {
-      switch (s.n_layers) {
-        case 2: e = go(backward_mfma_kernel<1, 2>, BwdMap<1, 2>::total); break;
-        case 3: e = go(backward_mfma_kernel<1, 3>, BwdMap<1, 3>::total); break;
-        case 4: e = go(backward_mfma_kernel<1, 4>, BwdMap<1, 4>::total); break;
-        default: return hipErrorInvalidValue;
-      }
-    } else {
-      switch (s.n_layers) {
-        case 2: e = go(backward_mfma_kernel<2, 2>, BwdMap<2, 2>::total); break;
-        case 3: e = go(backward_mfma_kernel<2, 3>, BwdMap<2, 3>::total); break;
-        case 4: e = go(backward_mfma_kernel<2, 4>, BwdMap<2, 4>::total); break;
-        default: return hipErrorInvalidValue;
-      }
+    switch (10 * mt + s.n_layers) {
+      case 12: e = go(backward_mfma_kernel<1, 2>, BwdMap<1, 2>::total); break;
+      case 13: e = go(backward_mfma_kernel<1, 3>, BwdMap<1, 3>::total); break;
+      case 14: e = go(backward_mfma_kernel<1, 4>, BwdMap<1, 4>::total); break;
+      case 22: e = go(backward_mfma_kernel<2, 2>, BwdMap<2, 2>::total); break;
+      case 23: e = go(backward_mfma_kernel<2, 3>, BwdMap<2, 3>::total); break;
+      case 24: e = go(backward_mfma_kernel<2, 4>, BwdMap<2, 4>::total); break;
+      default: return hipErrorInvalidValue;
     }
   }
   if (e != hipSuccess) return e;
