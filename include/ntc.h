@@ -161,16 +161,18 @@ ntc_status ntc_mlp_pack(const ntc_mlp *mlp, int32_t compute, const float *act_am
 
 /* FP8 range calibration: act_amax[l] = max over the n samples of |input of
  * layer l| (the feature vector for l = 0, the ReLU output of layer l-1
- * otherwise), evaluated with the plain FP32 decode [device, n_layers
+ * otherwise), evaluated with plain FP32 FMAs [device, n_layers
  * floats, overwritten]. packed_f32 is the NTC_F32 image of `mlp` written by
  * ntc_mlp_pack; uv float [n][2] [device, 8-byte aligned], n >= 1. */
 ntc_status ntc_calibrate_fp8(const ntc_latents *lat, const ntc_mlp *mlp, const void *packed_f32,
                              const float *uv, int64_t n, float *act_amax, void *stream);
 
 /* Fused decode (Sec. 3.1 + Sec. 3.3 + Sec. 4): out[s] = f(x(uv[s])) for
- * s < n. compute selects the arithmetic: NTC_F32 (FP32: plain FMAs, one
- * pixel per lane, for BC1 latents; FP32 matrix cores, 32 samples per step,
- * for float latents and at most 4 layers), NTC_F16 (FP16 matrix cores, FP32
+ * s < n. compute selects the arithmetic: NTC_F32 (FP32: every product of two
+ * FP32 numbers is formed from three-part BF16 splits on the BF16 matrix cores
+ * with FP32 accumulation, to FP32 accuracy; numbers near the ends of FP32's
+ * range, and short batches of float latents, take the FP32 matrix cores),
+ * NTC_F16 (FP16 matrix cores, FP32
  * accumulation),
  * NTC_BF16 (BF16 matrix cores, FP32 accumulation) or NTC_FP8_E4M3 (E4M3
  * matrix cores with per-layer scales, FP32 accumulation). packed is the image written by ntc_mlp_pack for the same

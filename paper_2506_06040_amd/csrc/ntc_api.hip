@@ -220,7 +220,7 @@ ntc_status ntc_calibrate_fp8(const ntc_latents *lat, const ntc_mlp *mlp, const v
   a.n_layers = s.n_layers;
   a.lay = pack_layout(s, NTC_F32);
   hipError_t e = launch_fill_f32(act_amax, s.n_layers, 0.0f, (hipStream_t)stream);
-  if (e == hipSuccess) e = launch_decode_plain(a, s, act_amax, device_cus(), (hipStream_t)stream);
+  if (e == hipSuccess) e = launch_calibrate(a, s, act_amax, device_cus(), (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "calibration launch");
   return ok();
 }
@@ -273,10 +273,13 @@ ntc_status ntc_decode(const ntc_latents *lat, const ntc_mlp *mlp, int32_t comput
   a.lay = pack_layout(s, compute);
   const int cus = device_cus();
   hipError_t e;
-  if (compute == NTC_F32 && lat->format == NTC_LATENT_F32 && s.n_layers <= 4)
+  // Float latents, short batches: the FP32 matrix kernel has less to set up
+  // than the split one (us, FP32 / split: 14-64-64-8 11.2 / 13.2 at 4096
+  // samples and 17.1 / 14.3 at 65536; 14-32-32-8 7.7 / 8.9 and 9.4 / 9.7).
+  if (compute == NTC_F32 && lat->format == NTC_LATENT_F32 && s.n_layers <= 4 && n * s.hid <= (1 << 21))
     e = launch_forward_f32(a, s, (hipStream_t)stream);
   else if (compute == NTC_F32)
-    e = launch_decode_plain(a, s, nullptr, cus, (hipStream_t)stream);
+    e = launch_decode_f32(a, s, cus, (hipStream_t)stream);
   else
     e = launch_decode_mfma(a, s, compute, cus * waves_per_cu, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "decode launch");

@@ -83,10 +83,11 @@ struct DecodeArgs {
   int64_t img_px;       // pixels of those images
 };
 
-hipError_t launch_decode_plain(const DecodeArgs &a, const MlpShape &s, float *calib_amax, int n_cus,
-                               hipStream_t st);
+hipError_t launch_calibrate(const DecodeArgs &a, const MlpShape &s, float *act_amax, int n_cus, hipStream_t st);
 hipError_t launch_decode_mfma(const DecodeArgs &a, const MlpShape &s, int compute, int grid_waves, hipStream_t st);
-// FP32 decode of float latents on the matrix cores (up to 4 layers).
+// FP32 decode on the BF16 matrix cores with split operands (ntc_split.hip).
+hipError_t launch_decode_f32(DecodeArgs a, const MlpShape &s, int n_cus, hipStream_t st);
+// FP32 decode of float latents on the FP32 matrix cores (up to 4 layers).
 hipError_t launch_forward_f32(const DecodeArgs &a, const MlpShape &s, hipStream_t st);
 int decode_span_tiles(int hid, int n_layers, int compute);  // 64-pixel tiles per span of the matrix-core decode
 hipError_t launch_bc1_texels(const LevelArgs &L, float *out, uint16_t *numer, hipStream_t st);

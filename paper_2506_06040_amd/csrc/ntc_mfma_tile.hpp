@@ -974,7 +974,8 @@ __device__ __forceinline__ void swap_halves(typename P::Frag &lo, typename P::Fr
 // coordinates, computed by 16 lanes in parallel (level, axis, min / max). If
 // the footprints fit the LDS region (stage_cap texels), every texel in them
 // is decoded once into `stage` (exact integer BC1 decode, scaled to FP32;
-// F16TEX: then rounded to FP16, 8 bytes per texel, see Tex16) and
+// F16TEX: then rounded to FP16, 8 bytes per texel, see Tex16; NUMER: the
+// numerators themselves as FP16, which holds them exactly) and
 // the function returns true with kbw / kbase locating texel (i, j) of level
 // k at j kbw[k] + i + kbase[k]. `srec` is this wave's staging record area
 // (2 entries per level), `salt` a value that changes from span to span (see
@@ -982,7 +983,7 @@ __device__ __forceinline__ void swap_halves(typename P::Frag &lo, typename P::Fr
 // span lies in [0, 1] (NaN and infinities do not). interior: on every level
 // the sampling position of every pixel of the span lies in [0, n - 2] on
 // both axes, so the clamp of clamp_tap changes nothing.
-template <int ST, bool F16TEX>
+template <int ST, bool F16TEX, bool NUMER = false>
 __device__ __forceinline__ bool stage_span(const DecodeArgs &a, const float (&u)[ST], const float (&v)[ST],
                                            f32x4 *stage, const f32x4 *ltab, f32x4 *srec, int salt,
                                            int (&kbw)[kMaxLevels], int (&kbase)[kMaxLevels], bool &in_unit,
@@ -1077,7 +1078,16 @@ __device__ __forceinline__ bool stage_span(const DecodeArgs &a, const float (&u)
     const uint32_t pos = (uint32_t)(Y & 3) << 2;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float3 val = texel_f32(bc1_numer(b.x, b.y, pos + i));
+      const uint32_t num = bc1_numer(b.x, b.y, pos + i);
+      if constexpr (NUMER) {
+        const f32x2 rg = {numer_r(num), numer_g(num)}, b0 = {numer_b(num), 0.0f};
+        Tex16 t16;
+        t16.rg = __builtin_convertvector(rg, half2_t);
+        t16.b1 = __builtin_convertvector(b0, half2_t);
+        reinterpret_cast<uint2 *>(stage)[4 * t + i] = tex16_bits(t16);
+        continue;
+      }
+      const float3 val = texel_f32(num);
       if constexpr (F16TEX)
         reinterpret_cast<uint2 *>(stage)[4 * t + i] = tex16_bits(tex16_of(val));
       else

@@ -1,7 +1,6 @@
-// Plain FP32 decode (one pixel per lane, scalar FMAs: the analogue of the
-// paper's "software FMA" path of Table 2), the FP8 range calibration that
-// shares it, the BC1 texel export, small fill kernels and the weight
-// packers.
+// FP8 range calibration (one sample per lane, scalar FMAs: the analogue of
+// the paper's "software FMA" path of Table 2), the BC1 texel export, small
+// fill kernels and the weight packers.
 #include <hip/hip_runtime.h>
 
 #include "ntc_device.hpp"
@@ -365,7 +364,7 @@ hipError_t launch_pack(const MlpShape &s, const MlpPtrs &p, int compute, const f
 }
 
 // ---------------------------------------------------------------------------
-// Plain FP32 decode
+// FP8 range calibration
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void atomic_max_nonneg(float *addr, float v) {
   // non-negative IEEE floats order like their bit patterns
@@ -378,16 +377,15 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-template <int HID, bool CALIB>
+template <int HID>
 // The packed image comes as its own read-only, non-aliasing argument: its
 // loads are then uniform and unclobbered, and the compiler reads the weights
 // through the scalar cache (one load for the whole wavefront) instead of
 // once per lane.
-__global__ __launch_bounds__(256) void decode_plain_kernel(DecodeArgs a, const float *__restrict__ wp,
-                                                           float *__restrict__ amax) {
+__global__ __launch_bounds__(256) void calibrate_kernel(DecodeArgs a, const float *__restrict__ wp,
+                                                        float *__restrict__ amax) {
   const int n_levels = a.lat.n_levels;
   const int n_layers = a.n_layers;
-  const int n_out = a.n_out;
   float am[kMaxLayers];
 #pragma unroll
   for (int l = 0; l < kMaxLayers; ++l) am[l] = 0.f;
@@ -416,10 +414,8 @@ __global__ __launch_bounds__(256) void decode_plain_kernel(DecodeArgs a, const f
       if (k == 3 * n_levels) x[k] = uv.x;
       if (k == 3 * n_levels + 1) x[k] = uv.y;
     }
-    if (CALIB) {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) am[0] = fmaxf(am[0], fabsf(x[k]));
-    }
+    for (int k = 0; k < 16; ++k) am[0] = fmaxf(am[0], fabsf(x[k]));
     float h[HID];
     {
       const float *W = wpi + a.lay.w_off[0] / 4;
@@ -433,10 +429,8 @@ __global__ __launch_bounds__(256) void decode_plain_kernel(DecodeArgs a, const f
       }
     }
     for (int l = 1; l < n_layers - 1; ++l) {
-      if (CALIB) {
 #pragma unroll
-        for (int k = 0; k < HID; ++k) am[l] = fmaxf(am[l], h[k]);
-      }
+      for (int k = 0; k < HID; ++k) am[l] = fmaxf(am[l], h[k]);
       const float *W = wpi + a.lay.w_off[l] / 4;
       const float *b = wpi + a.lay.b_off[l] / 4;
       float h2[HID];
@@ -450,60 +444,35 @@ __global__ __launch_bounds__(256) void decode_plain_kernel(DecodeArgs a, const f
 #pragma unroll
       for (int o = 0; o < HID; ++o) h[o] = h2[o];
     }
-    if (CALIB) {
 #pragma unroll
-      for (int k = 0; k < HID; ++k) am[n_layers - 1] = fmaxf(am[n_layers - 1], h[k]);
-      continue;  // calibration only needs the layer inputs
-    }
-    const float *W = wpi + opaque_zero(iter + 1) + a.lay.w_off[n_layers - 1] / 4;
-    const float *b = wpi + opaque_zero(iter + 2) + a.lay.b_off[n_layers - 1] / 4;
-#pragma unroll
-    for (int o = 0; o < 16; ++o) {
-      if (o < n_out) {
-        float acc = b[o];
-#pragma unroll
-        for (int k = 0; k < HID; ++k) acc = fmaf(W[o * HID + k], h[k], acc);
-        const float f = 1.0f / (1.0f + expf(-acc));
-        if (a.out_f16)
-          reinterpret_cast<_Float16 *>(a.out)[p * n_out + o] = (_Float16)f;
-        else
-          reinterpret_cast<float *>(a.out)[p * n_out + o] = f;
-      }
-    }
+    for (int k = 0; k < HID; ++k) am[n_layers - 1] = fmaxf(am[n_layers - 1], h[k]);
   }
-  if (CALIB) {
 #pragma unroll
-    for (int l = 0; l < kMaxLayers; ++l) {
-      if (l < n_layers) {
-        const float m = wave_max(am[l]);
-        if ((threadIdx.x & 63) == 0) atomic_max_nonneg(amax + l, m);
-      }
+  for (int l = 0; l < kMaxLayers; ++l) {
+    if (l < n_layers) {
+      const float m = wave_max(am[l]);
+      if ((threadIdx.x & 63) == 0) atomic_max_nonneg(amax + l, m);
     }
   }
 }
 
 template <int HID>
-static hipError_t launch_plain_hid(const DecodeArgs &a, float *calib, int n_cus, hipStream_t st) {
+static hipError_t launch_calibrate_hid(const DecodeArgs &a, float *amax, int n_cus, hipStream_t st) {
   const int bs = 256;
   int64_t blocks = (a.n + bs - 1) / bs;
   const int64_t cap = (int64_t)n_cus * 16;
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
-  if (calib)
-    hipLaunchKernelGGL((decode_plain_kernel<HID, true>), dim3((unsigned)blocks), dim3(bs), 0, st, a,
-                       reinterpret_cast<const float *>(a.packed), calib);
-  else
-    hipLaunchKernelGGL((decode_plain_kernel<HID, false>), dim3((unsigned)blocks), dim3(bs), 0, st, a,
-                       reinterpret_cast<const float *>(a.packed), calib);
+  hipLaunchKernelGGL((calibrate_kernel<HID>), dim3((unsigned)blocks), dim3(bs), 0, st, a,
+                     reinterpret_cast<const float *>(a.packed), amax);
   return hipGetLastError();
 }
 
-hipError_t launch_decode_plain(const DecodeArgs &a, const MlpShape &s, float *calib_amax, int n_cus,
-                               hipStream_t st) {
+hipError_t launch_calibrate(const DecodeArgs &a, const MlpShape &s, float *act_amax, int n_cus, hipStream_t st) {
   switch (s.hid) {
-    case 16: return launch_plain_hid<16>(a, calib_amax, n_cus, st);
-    case 32: return launch_plain_hid<32>(a, calib_amax, n_cus, st);
-    case 64: return launch_plain_hid<64>(a, calib_amax, n_cus, st);
+    case 16: return launch_calibrate_hid<16>(a, act_amax, n_cus, st);
+    case 32: return launch_calibrate_hid<32>(a, act_amax, n_cus, st);
+    case 64: return launch_calibrate_hid<64>(a, act_amax, n_cus, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -520,3 +520,90 @@ def test_span_boundaries(compute, tol):
             assert np.all(got[n:] == -3.0), (dims, n)
             err = np.abs(got[:n].astype(np.float64) - O.decode(olat, omlp, uv))
             assert np.all(err <= tol), (dims, n, float(err.max()))
+
+
+@pytest.mark.parametrize("dims,sizes,address,n", [
+    ((14, 64, 64, 64, 8), [(64, 64), (32, 32), (16, 16), (8, 8)], "clamp", 1),
+    ((14, 64, 64, 64, 64, 9), [(64, 64), (32, 32), (16, 16), (8, 8)], "clamp", 65),
+    ((14, 32, 32, 8), [(64, 64), (32, 32), (16, 16), (8, 8)], "wrap", 127),
+    ((11, 16, 3), [(64, 32), (32, 16), (16, 8)], "clamp", 129),
+    ((5, 64, 16), [(32, 32)], "wrap", 4099),
+    ((8, 32, 32, 32, 12), [(1024, 1024), (512, 512)], "clamp", 256 * 12 * 128 - 1),  # 64-pixel spans, then 128
+    ((8, 32, 32, 32, 12), [(1024, 1024), (512, 512)], "clamp", 256 * 12 * 128 + 65),
+])
+@pytest.mark.parametrize("order", ["rows", "random"])
+def test_f32_split_shapes(dims, sizes, address, n, order):
+    """FP32 decode over the tails of 32-pixel tiles and 64- and 128-pixel
+    spans, staged and direct texels, every network width and depth class:
+    FP32 out within 1e-5 relative of the oracle, nothing written past the end,
+    FP16 out within FP16 rounding."""
+    ntc = _ntc()
+    rng = np.random.default_rng(n + len(dims))
+    lat_np = I.bc1_pyramid(rng, sizes)
+    Ws, bs = I.xavier_mlp(rng, dims, bias="normal")
+    shift = I.PAPER_SHIFT[:len(sizes)]
+    if order == "rows":
+        k = np.arange(n)
+        uv = np.stack([(k % 700 + 0.5) / 700, (k // 700 + 0.5) / 600], 1).astype(np.float32)
+    else:
+        uv = (rng.random((n, 2)) * 1.4 - 0.2).astype(np.float32)
+    lat = ntc.Latents(lat_np, shift=shift, address=address)
+    mlp = ntc.Mlp(Ws, bs)
+    ref = O.decode(O.Latents(lat_np, shift=shift, address=O.WRAP if address == "wrap" else O.CLAMP), O.Mlp(Ws, bs), uv)
+    buf = torch.full((n + 4, dims[-1]), 7.0, device="cuda")
+    ntc.decode(lat, mlp, torch.from_numpy(uv).cuda(), compute="f32", out=buf[:n])
+    out = buf.cpu().numpy()
+    assert np.all(out[n:] == 7.0)
+    assert np.all(np.abs(out[:n] - ref) <= TOL_F32_REL * np.abs(ref))
+    o16 = ntc.decode(lat, mlp, torch.from_numpy(uv).cuda(), compute="f32", out_dtype=torch.float16).cpu().numpy()
+    assert np.all(np.abs(o16.astype(np.float64) - ref) <= 2.0 ** -11 * np.abs(ref) + 1e-7)
+
+
+@pytest.mark.parametrize("fmt", ["bc1", "f32"])
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** 60, 2.0 ** 100, 2.0 ** 122, 2.0 ** -60, 2.0 ** -115])
+def test_f32_split_range(scale, fmt):
+    """FP32 decode of networks whose hidden activations are scaled by `scale`
+    (undone by the next layer: the function stays the same): the largest
+    leave the range in which numbers are split and take the FP32 matrix
+    products, the smallest have parts below the normal range. Tolerance as
+    for any FP32 decode."""
+    ntc = _ntc()
+    rng = np.random.default_rng(61)
+    sizes = [(64, 64), (32, 32), (16, 16), (8, 8)]
+    lat_np = I.bc1_pyramid(rng, sizes) if fmt == "bc1" else I.f32_pyramid(rng, sizes)
+    Ws, bs = I.xavier_mlp(rng, (14, 64, 64, 8), bias="normal")
+    Ws[0], bs[0] = (Ws[0] * np.float32(scale)), (bs[0] * np.float32(scale))
+    Ws[1] = Ws[1] / np.float32(scale)
+    uv = rng.random((40000, 2)).astype(np.float32)
+    lat, mlp = _gpu_case(lat_np, Ws, bs, I.PAPER_SHIFT)
+    out = ntc.decode(lat, mlp, torch.from_numpy(uv).cuda(), compute="f32").cpu().numpy()
+    olat, omlp = _oracle_case(lat_np, Ws, bs, I.PAPER_SHIFT)
+    ref = O.decode(olat, omlp, uv)
+    assert np.all(np.abs(out - ref) <= TOL_F32_REL * np.abs(ref))
+
+
+def test_f32_split_pixels_do_not_depend_on_neighbours():
+    """Pixels with coordinates beyond the split range (and infinite or NaN
+    latents) among others: the others equal a launch without them bit for bit,
+    and the finite ones match the oracle."""
+    ntc = _ntc()
+    rng = np.random.default_rng(62)
+    lat_np = I.f32_pyramid(rng, [(64, 64), (32, 32)])
+    lat_np[0][5, 7] = np.inf
+    lat_np[1][20, 3] = np.nan
+    Ws, bs = I.xavier_mlp(rng, (8, 64, 64, 8), bias="normal")
+    Ws[0][:, 6:] *= np.float32(1e-6)
+    uv = rng.random((70000, 2)).astype(np.float32)
+    far = uv.copy()
+    at = rng.choice(uv.shape[0], 500, replace=False)
+    far[at] *= np.float32(2.0e6)
+    keep = np.ones(uv.shape[0], bool)
+    keep[at] = False
+    lat, mlp = _gpu_case(lat_np, Ws, bs, I.PAPER_SHIFT[:2])
+    a = ntc.decode(lat, mlp, torch.from_numpy(uv).cuda(), compute="f32").cpu().numpy()
+    b = ntc.decode(lat, mlp, torch.from_numpy(far).cuda(), compute="f32").cpu().numpy()
+    assert np.array_equal(a[keep], b[keep], equal_nan=True)
+    ref = O.decode(O.Latents(lat_np, shift=I.PAPER_SHIFT[:2]), O.Mlp(Ws, bs), far)
+    fin = at[np.isfinite(O.features(O.Latents(lat_np, shift=I.PAPER_SHIFT[:2]), far[at])).all(1)]
+    assert fin.size > 400
+    assert np.all(np.abs(b[fin] - ref[fin]) <= TOL_F32_REL * np.abs(ref[fin]) + 1e-6)
