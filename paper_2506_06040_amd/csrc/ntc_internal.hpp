@@ -92,6 +92,13 @@ hipError_t launch_forward_f32(const DecodeArgs &a, const MlpShape &s, hipStream_
 int decode_span_tiles(int hid, int n_layers, int compute);  // 64-pixel tiles per span of the matrix-core decode
 hipError_t launch_bc1_texels(const LevelArgs &L, float *out, uint16_t *numer, hipStream_t st);
 hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t st);
+// Arrays to zero in one launch (n = 0: none; 4-byte aligned).
+constexpr int kMaxZero = kMaxLevels + 1;
+struct ZeroArgs {
+  float *p[kMaxZero];
+  int64_t n[kMaxZero];
+};
+hipError_t launch_zero(const ZeroArgs &z, hipStream_t st);
 
 // Backward. Workspace (256-byte aligned sections): per-block FP32 partial
 // sums of the weight gradients, the feature gradient dL/dx of every sample,

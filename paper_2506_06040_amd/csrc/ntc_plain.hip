@@ -3,6 +3,8 @@
 // fill kernels and the weight packers.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "ntc_device.hpp"
 #include "ntc_internal.hpp"
 
@@ -511,6 +513,32 @@ hipError_t launch_bc1_texels(const LevelArgs &L, float *out, uint16_t *numer, hi
 __global__ void fill_f32_kernel(float *p, int64_t n, float v) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
+}
+
+// Zeroes several arrays in one launch: thread i of the grid takes every
+// grid-th element of each.
+__global__ __launch_bounds__(256) void zero_kernel(ZeroArgs z) {
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < kMaxZero; ++k) {
+    float *p = z.p[k];
+    // 16-byte stores from the first aligned element on
+    const int64_t head = min((int64_t)(((16 - ((uintptr_t)p & 15)) & 15) >> 2), z.n[k]);
+    const int64_t n4 = (z.n[k] - head) >> 2;
+    float4 *q = reinterpret_cast<float4 *>(p + head);
+    for (int64_t i = t; i < n4; i += stride) q[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (t < head) p[t] = 0.0f;
+    if (t < z.n[k] - head - 4 * n4) p[head + 4 * n4 + t] = 0.0f;
+  }
+}
+
+hipError_t launch_zero(const ZeroArgs &z, hipStream_t st) {
+  int64_t n = 1;
+  for (int k = 0; k < kMaxZero; ++k) n = std::max(n, z.n[k]);
+  const int64_t blocks = std::min<int64_t>((n / 4 + 255) / 256 + 1, 2048);
+  hipLaunchKernelGGL(zero_kernel, dim3((unsigned)blocks), dim3(256), 0, st, z);
+  return hipGetLastError();
 }
 
 hipError_t launch_fill_f32(float *p, int64_t n, float v, hipStream_t st) {
