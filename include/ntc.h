@@ -106,9 +106,11 @@ typedef struct {
  *                   networks of four or more layers and for the 64-wide
  *                   BF16 / E4M3 decodes, 8 otherwise); other values give
  *                   NTC_E_UNSUPPORTED
- *   stage_capacity: texels a wave may stage in LDS per span (64..4096,
- *                   default 1024); spans whose footprint is larger fall back
- *                   to direct block fetches. */
+ *   stage_capacity: texels of 16 bytes a wave may stage in LDS per span
+ *                   (64..4096, default 1024; twice as many of the FP16
+ *                   decode's 8-byte texels); spans whose footprint is larger
+ *                   fall back to direct block fetches.
+ * With wrap addressing spans are 128 pixels whatever tiles_per_iter says. */
 typedef struct {
     int32_t waves_per_cu;
     int32_t tiles_per_iter;

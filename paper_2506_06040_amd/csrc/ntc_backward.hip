@@ -216,14 +216,6 @@ __global__ __launch_bounds__(64 * kReduceWaves) void reduce_f64_kernel(ReduceArg
 typedef float bf32x16 __attribute__((ext_vector_type(16)));
 typedef float bf32x4 __attribute__((ext_vector_type(4)));
 
-// i modulo n for |i| <= 2^25, with rn about 1 / n: the quotient is off by at
-// most one (an integer division takes several times as long).
-__device__ __forceinline__ int wrap_near(int i, int n, float rn) {
-  int r = i - n * (int)floorf((float)i * rn);
-  r += r < 0 ? n : 0;
-  return r >= n ? r - n : r;
-}
-
 // Level parameters in LDS, so that a lane half reads its two levels' own
 // without holding them in registers or choosing among scalars:
 // [h][j] = grid pointer, w, h | fw, fh, sx, sy | 1 / fw, 1 / fh.

@@ -97,6 +97,15 @@ __device__ __forceinline__ int address_coord(int i, int n, int mode) {
   return min(max(i, 0), n - 1);
 }
 
+// i modulo n for |i| <= 2^24 + 1 and n >= 4, with rn within 2^-22 of 1 / n
+// (relative): the quotient is off by at most one. An integer division takes
+// several times as long.
+__device__ __forceinline__ int wrap_near(int i, int n, float rn) {
+  int r = i - n * (int)floorf((float)i * rn);
+  r += r < 0 ? n : 0;
+  return r >= n ? r - n : r;
+}
+
 // Bilinear footprint on one level: x = u w - 1/2 + s (texel centres at
 // (i + 1/2) / w), taps floor(x) and floor(x) + 1, fraction x - floor(x).
 // The position is first limited to +-2^24 texels so that every index stays

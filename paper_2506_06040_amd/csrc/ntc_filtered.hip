@@ -567,7 +567,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
               return staged_sample(stage, one ? fw1 : fw0, one ? fh1 : fh0, cx, cy, one ? kbw1 : kbw0,
                                    one ? kb1 : kb0, x, y, one ? in1 : in0);
             }
-            return sample_direct16(mip_level(f, k, m), tap_coord(x), tap_coord(y), 0);
+            return sample_direct16<kEitherMode>(mip_level(f, k, m), tap_coord(x), tap_coord(y), 0);
           };
           // every lane reads mip m_lo alone (blend weight 0) and it is
           // staged: the samples take the region's values as wave-uniform

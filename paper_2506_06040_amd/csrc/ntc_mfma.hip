@@ -16,9 +16,15 @@
 
 namespace ntc {
 
-template <class P, int HID, int NL, int VEC4>
+constexpr int kWrapTiles = 2;  // 64-pixel tiles per span with wrap addressing (4: 88 in place of 82 us, see decode_span_wrap)
+
+// One kernel per address mode: the wrapped one is rolled and small, the
+// clamped one keeps the registers and the schedule that it has alone (both
+// with staging in one kernel: 1 to 3% slower clamped decodes). The mode stays a
+// run-time value in the clamped spans of FP32 texels (as a constant: 1% slower).
+template <class P, int HID, int NL, int VEC4, int ADDR>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PER_SIMD, NTC_WAVES_PER_SIMD))) void decode_mfma_kernel(DecodeArgs a) {
-  constexpr int ST = span_tiles_for(HID, NL, P::kF16Tex);
+  constexpr int ST = ADDR == kWrapOnly ? kWrapTiles : span_tiles_for(HID, NL, P::kF16Tex);
   constexpr int SPX = 64 * ST;
   extern __shared__ f32x4 smem[];
   f32x4 *stage = smem;
@@ -50,8 +56,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
   }
   for (int64_t it = vb; it < n_spans; it += nb) {
     const int64_t nx = it + nb;
-    decode_span<P, HID, NL, ST, VEC4>(a, it * SPX, a.n, stage, bias, ltab, W, uvs, nx < n_spans ? nx * SPX : -1,
-                                      a.n, obuf);
+    const int64_t next = nx < n_spans ? nx * SPX : -1;
+    if constexpr (ADDR == kWrapOnly)
+      decode_span_wrap<P, HID, NL, ST, VEC4>(a, it * SPX, a.n, stage, bias, ltab, W, uvs, next, a.n, obuf);
+    else
+      decode_span<P, HID, NL, ST, VEC4, false, P::kF16Tex ? kClampOnly : kEitherMode>(a, it * SPX, a.n, stage, bias, ltab, W, uvs, next, a.n, obuf);
   }
 }
 
@@ -59,14 +68,20 @@ template <class P, int HID, int VEC4>
 static hipError_t launch_mfma_v(const DecodeArgs &a, int n_layers, int grid, hipStream_t st) {
   const size_t lds =
       (size_t)(a.stage_cap + BiasLds<HID, 5>::kCount + LevelTab::kCount + (VEC4 ? 0 : 32 * 16 / 4)) * sizeof(f32x4);
+  auto go = [&](auto clamped, auto wrapped) {
+    if (a.lat.address == 0)
+      hipLaunchKernelGGL(clamped, dim3(grid), dim3(64), lds, st, a);
+    else
+      hipLaunchKernelGGL(wrapped, dim3(grid), dim3(64), lds, st, a);
+    return hipGetLastError();
+  };
   switch (n_layers) {
-    case 2: hipLaunchKernelGGL((decode_mfma_kernel<P, HID, 2, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
-    case 3: hipLaunchKernelGGL((decode_mfma_kernel<P, HID, 3, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
-    case 4: hipLaunchKernelGGL((decode_mfma_kernel<P, HID, 4, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
-    case 5: hipLaunchKernelGGL((decode_mfma_kernel<P, HID, 5, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
+    case 2: return go(decode_mfma_kernel<P, HID, 2, VEC4, kClampOnly>, decode_mfma_kernel<P, HID, 2, VEC4, kWrapOnly>);
+    case 3: return go(decode_mfma_kernel<P, HID, 3, VEC4, kClampOnly>, decode_mfma_kernel<P, HID, 3, VEC4, kWrapOnly>);
+    case 4: return go(decode_mfma_kernel<P, HID, 4, VEC4, kClampOnly>, decode_mfma_kernel<P, HID, 4, VEC4, kWrapOnly>);
+    case 5: return go(decode_mfma_kernel<P, HID, 5, VEC4, kClampOnly>, decode_mfma_kernel<P, HID, 5, VEC4, kWrapOnly>);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 template <class P, int HID>
@@ -94,7 +109,7 @@ int decode_span_tiles(int hid, int n_layers, int compute) {
 
 hipError_t launch_decode_mfma(const DecodeArgs &a, const MlpShape &s, int compute, int grid_waves, hipStream_t st) {
   int64_t grid = grid_waves;
-  const int span = decode_span_tiles(s.hid, s.n_layers, compute);
+  const int span = a.lat.address == 0 ? decode_span_tiles(s.hid, s.n_layers, compute) : kWrapTiles;
   const int64_t n_iter = (a.n_tiles + span - 1) / span;
   if (grid > n_iter) grid = n_iter;
   if (grid >= 8) grid &= ~(int64_t)7;

@@ -7,12 +7,12 @@
 //   2. Footprint: every tap index is a monotonic function of the coordinate,
 //      so the span's extreme coordinates (wave reductions) give each level's
 //      tap range; 16 lanes evaluate them at once (level x axis x min/max).
-//   3. Staging (clamp addressing, footprint within the LDS region): whole
+//   3. Staging (footprint within the LDS region): whole
 //      blocks covering the footprint, one item per texel row of a block
 //      (4 texels), all levels numbered in one sequence so that a single
 //      round of 64 lanes usually covers the span. Each item is decoded with
-//      exact integer arithmetic and written as FP32 texels to LDS. Otherwise,
-//      and for wrap addressing, taps fetch their blocks directly.
+//      exact integer arithmetic and written as FP32 texels to LDS. Otherwise
+//      taps fetch their blocks directly. (Wrap addressing: decode_span_wrap.)
 //   4. Sub-spans of 64 pixels: each lane samples all levels of its own pixel
 //      (clamp-to-edge applied to the sampling position: tap clamped to
 //      [0, n - 2], fraction to [0, 1]), converts its 16 feature slots to the
@@ -469,6 +469,12 @@ __device__ __forceinline__ void clamp_tap(float u, float f, float c, float capf,
   fr = __builtin_amdgcn_fmed3f(x - t, 0.0f, 1.0f);
 }
 
+// Address mode of the code that a kernel compiles: clamp or wrap addressing
+// alone, or either, as the arguments say (wrapped spans are then not staged).
+constexpr int kClampOnly = 0, kWrapOnly = 1, kEitherMode = 2;
+// Positions of wrapped spans that are staged (see stage_span).
+constexpr float kWrapFar = 4194304.0f;
+
 // Texel of a BC1 level as three FP32 channel values.
 __device__ __forceinline__ float3 texel_f32(uint32_t p) {
   return make_float3(numer_r(p) * kInvDenRB, numer_g(p) * kInvDenG, numer_b(p) * kInvDenRB);
@@ -828,6 +834,7 @@ struct TabLevel {
 
 // Taps (columns i0, i1, rows j0, j1) and fractions of one level with direct
 // block fetches; `mode` 0 clamp, 1 wrap.
+template <int ADDR>
 __device__ __forceinline__ void direct_taps(const TabLevel &L, float u, float v, int mode, int &i0, int &i1, int &j0,
                                             int &j1, float &fx, float &fy) {
   if (mode == 0) {
@@ -843,29 +850,41 @@ __device__ __forceinline__ void direct_taps(const TabLevel &L, float u, float v,
   y = fminf(fmaxf(y, -16777216.0f), 16777216.0f);
   const float xf = floorf(x), yf = floorf(y);
   const int ix = (int)xf, iy = (int)yf;
-  i0 = address_coord(ix, L.w, 1);
-  i1 = address_coord(ix + 1, L.w, 1);
-  j0 = address_coord(iy, L.h, 1);
-  j1 = address_coord(iy + 1, L.h, 1);
+  if constexpr (ADDR == kClampOnly) {
+    // never reached in such a kernel: the branch keeps the levels apart, which
+    // the compiler schedules better than one block of code for all of them
+    // (random coordinates: 10 to 15%; with the short form below 2%)
+    i0 = address_coord(ix, L.w, 1);
+    i1 = address_coord(ix + 1, L.w, 1);
+    j0 = address_coord(iy, L.h, 1);
+    j1 = address_coord(iy + 1, L.h, 1);
+  } else {
+    i0 = wrap_near(ix, L.w, __builtin_amdgcn_rcpf((float)L.w));
+    j0 = wrap_near(iy, L.h, __builtin_amdgcn_rcpf((float)L.h));
+    i1 = i0 + 1 == L.w ? 0 : i0 + 1;
+    j1 = j0 + 1 == L.h ? 0 : j0 + 1;
+  }
   fx = x - xf;
   fy = y - yf;
 }
 
 // Sample of one level with direct block fetches (FP32 blend).
+template <int ADDR>
 __device__ __forceinline__ float3 sample_direct_t(const TabLevel &L, float u, float v, int mode) {
   int i0, i1, j0, j1;
   float fx, fy;
-  direct_taps(L, u, v, mode, i0, i1, j0, j1, fx, fy);
+  direct_taps<ADDR>(L, u, v, mode, i0, i1, j0, j1, fx, fy);
   return blend4(texel_direct(L.bc1, L.bw, i0, j0), texel_direct(L.bc1, L.bw, i1, j0),
                 texel_direct(L.bc1, L.bw, i0, j1), texel_direct(L.bc1, L.bw, i1, j1), fx, fy);
 }
 
 // The same sample with FP16 texels and the packed FP16 blend (bit for bit
 // what the staged path computes from its LDS copy of the texels).
+template <int ADDR>
 __device__ __forceinline__ Tex16 sample_direct16(const TabLevel &L, float u, float v, int mode) {
   int i0, i1, j0, j1;
   float fx, fy;
-  direct_taps(L, u, v, mode, i0, i1, j0, j1, fx, fy);
+  direct_taps<ADDR>(L, u, v, mode, i0, i1, j0, j1, fx, fy);
   return lerp_tex16(tex16_of(texel_direct(L.bc1, L.bw, i0, j0)), tex16_of(texel_direct(L.bc1, L.bw, i1, j0)),
                     tex16_of(texel_direct(L.bc1, L.bw, i0, j1)), tex16_of(texel_direct(L.bc1, L.bw, i1, j1)), fx, fy);
 }
@@ -968,8 +987,8 @@ __device__ __forceinline__ void swap_halves(typename P::Frag &lo, typename P::Fr
   }
 }
 
-// Footprint and staging of one span whose lane coordinates are u, v (clamp
-// addressing). The taps of every level are monotonic in (u, v), so the
+// Footprint and staging of one span whose lane coordinates are u, v. The
+// taps of every level are monotonic in (u, v), so the
 // span's footprint on level k is spanned by the taps of the extreme
 // coordinates, computed by 16 lanes in parallel (level, axis, min / max). If
 // the footprints fit the LDS region (stage_cap texels), every texel in them
@@ -982,8 +1001,11 @@ __device__ __forceinline__ void swap_halves(typename P::Frag &lo, typename P::Fr
 // opaque_zero). in_unit (set when the span is staged): every u and v of the
 // span lies in [0, 1] (NaN and infinities do not). interior: on every level
 // the sampling position of every pixel of the span lies in [0, n - 2] on
-// both axes, so the clamp of clamp_tap changes nothing.
-template <int ST, bool F16TEX, bool NUMER = false>
+// both axes, so the clamp of clamp_tap changes nothing. ADDR = kWrapOnly: the
+// region is that of the taps before wrapping, the fetches bring block columns
+// and rows into the level; positions must lie within +-kWrapFar (NaN does
+// not), where a tap is a 24-bit factor.
+template <int ST, bool F16TEX, bool NUMER = false, int ADDR = kEitherMode>
 __device__ __forceinline__ bool stage_span(const DecodeArgs &a, const float (&u)[ST], const float (&v)[ST],
                                            f32x4 *stage, const f32x4 *ltab, f32x4 *srec, int salt,
                                            int (&kbw)[kMaxLevels], int (&kbase)[kMaxLevels], bool &in_unit,
@@ -991,7 +1013,8 @@ __device__ __forceinline__ bool stage_span(const DecodeArgs &a, const float (&u)
   const int lane = threadIdx.x & 63;
   in_unit = false;
   interior = false;
-  if (a.lat.address != 0) return false;
+  constexpr bool wrap = ADDR == kWrapOnly;
+  if (ADDR == kEitherMode && a.lat.address != 0) return false;
   float umin = tap_coord(u[0]), umax = umin, vmin = tap_coord(v[0]), vmax = vmin;
 #pragma unroll
   for (int q = 1; q < ST; ++q) {
@@ -1013,10 +1036,15 @@ __device__ __forceinline__ bool stage_span(const DecodeArgs &a, const float (&u)
   const int le = (lane >> 1) & 7;  // level le / 2, axis le % 2
   const f32x4 tb = (ltab + opaque_zero(salt))[3 * (le >> 1) + (le & 1)];
   const float ext = (lane & 2) ? ((lane & 1) ? vmax : vmin) : ((lane & 1) ? umax : umin);
-  const int ti = (int)tap_floor(ext, tb[0], tb[1], tb[2]);
   // the positions are monotonic in the coordinate: the extremes decide
   const float raw = fmaf(ext, tb[0], tb[1]);
-  interior = __builtin_amdgcn_ballot_w64(lane < 16 && !(raw >= 0.0f && raw <= tb[2])) == 0;
+  const int ti = wrap ? (int)floorf(fminf(fmaxf(raw, -kWrapFar), kWrapFar)) : (int)tap_floor(ext, tb[0], tb[1], tb[2]);
+  if constexpr (wrap) {
+    // (tap_coord's limits: NaN and infinities sit on them)
+    if (__builtin_amdgcn_ballot_w64(lane < 16 && !(fabsf(raw) <= kWrapFar && fabsf(ext) < 1048576.0f)) != 0) return false;
+  } else {
+    interior = __builtin_amdgcn_ballot_w64(lane < 16 && !(raw >= 0.0f && raw <= tb[2])) == 0;
+  }
   // every lane of quad k receives the four values of level k
   const int qbx = __builtin_amdgcn_mov_dpp(ti, 0x00, 0xF, 0xF, false);
   const int qex = __builtin_amdgcn_mov_dpp(ti, 0x55, 0xF, 0xF, false);
@@ -1033,7 +1061,8 @@ __device__ __forceinline__ bool stage_span(const DecodeArgs &a, const float (&u)
   const int qnrow = qey - qby + 2;
   // (levels past n_levels have a zero sampling scale: their footprint is
   // texels 0..1 x 0..1, two items)
-  const int qitems = __mul24(qncol, qnrow);
+  // (wrap: limited, so that the product stays an integer far beyond any capacity)
+  const int qitems = wrap ? __mul24(min(qncol, 4096), min(qnrow, 16384)) : __mul24(qncol, qnrow);
   int kib[kMaxLevels], total = 0;
 #pragma unroll
   for (int k = 0; k < kMaxLevels; ++k) {
@@ -1045,7 +1074,9 @@ __device__ __forceinline__ bool stage_span(const DecodeArgs &a, const float (&u)
     kbase[k] = 4 * total - by * kbw[k] - 4 * col0;
     total += items;
   }
-  if (4 * total > a.stage_cap) return false;
+  // the region holds stage_cap FP32 texels, or twice as many FP16 ones (rows of
+  // 1920 pixels over a 256^2 level, 512-pixel spans: 59 -> 36 us)
+  if (4 * total > (F16TEX ? 2 : 1) * a.stage_cap) return false;
   // per-level staging records, written by the lead lane of each quad:
   // {first item, blocks per staged row, 1 / that, first block column}
   // and {first texel row, blocks per level row, block pointer}
@@ -1054,9 +1085,16 @@ __device__ __forceinline__ bool stage_span(const DecodeArgs &a, const float (&u)
     const int k = lane >> 2;
     const int ib = k == 0 ? kib[0] : (k == 1 ? kib[1] : (k == 2 ? kib[2] : kib[3]));
     const f32x4 eb = (ltab + opaque_zero(salt))[3 * k + 2];
+    int c0 = qcol0, y0 = qby, size = __float_as_int(eb[2]);
+    if constexpr (wrap) {  // the first block column and row inside the level; its height beside the blocks per row
+      const int h = __float_as_int((ltab + opaque_zero(salt))[3 * k + 1][3]);
+      c0 = wrap_near(c0, size, __builtin_amdgcn_rcpf((float)size));
+      y0 = wrap_near(y0, h, __builtin_amdgcn_rcpf((float)h));
+      size |= h << 16;
+    }
     srec[2 * k] = (f32x4){__int_as_float(ib), __int_as_float(qncol), __builtin_amdgcn_rcpf((float)qncol),
-                          __int_as_float(qcol0)};
-    srec[2 * k + 1] = (f32x4){__int_as_float(qby), eb[2], eb[0], eb[1]};
+                          __int_as_float(c0)};
+    srec[2 * k + 1] = (f32x4){__int_as_float(y0), __int_as_float(size), eb[0], eb[1]};
   }
   // item t: its block row (blocks, index word) and staged texels; the row
   // inside the level is (t - first + 1/2) / ncol rounded down, exact since
@@ -1071,6 +1109,13 @@ __device__ __forceinline__ bool stage_span(const DecodeArgs &a, const float (&u)
     const int col = tl - __mul24(row, ncol);
     Y = __float_as_int(r1[0]) + row;
     const uint2 *blk = (const uint2 *)(((unsigned long long)__float_as_uint(r1[3]) << 32) | __float_as_uint(r1[2]));
+    if constexpr (wrap) {
+      const int bw = __float_as_int(r1[1]) & 0xffff, h = __float_as_int(r1[1]) >> 16;
+      int c = __float_as_int(r0[3]) + col;
+      while (c >= bw) c -= bw;  // once, unless the footprint passes the whole level
+      while (Y >= h) Y -= h;
+      return gload2u(blk + (__mul24(Y >> 2, bw) + c));
+    }
     // footprint rows and blocks lie inside the level
     return gload2u(blk + (__mul24(Y >> 2, __float_as_int(r1[1])) + __float_as_int(r0[3]) + col));
   };
@@ -1112,13 +1157,19 @@ __device__ __forceinline__ bool stage_span(const DecodeArgs &a, const float (&u)
 // (u, v) in the half-0 slots, levels 2, 3 in the half-1 slots), converted to
 // the operand type and exchanged between the lane halves (swap_halves): bx[0]
 // then feeds the N-tile of lanes 0..31's pixels, bx[1] that of lanes 32..63.
-// Left/top tap and fraction of a staged pixel. INTERIOR (the span's
+// Left/top tap and fraction of a staged pixel. kTapInterior (the span's
 // positions lie in [0, n - 2]): floor and fraction of the position as they
-// stand, which is what clamp_tap gives there; otherwise clamp_tap of the
-// sanitised coordinate.
-template <bool INTERIOR>
+// stand, which is what clamp_tap gives there; kTapClamp: clamp_tap of the
+// sanitised coordinate; kTapWrap: floor and fraction before wrapping.
+constexpr int kTapClamp = 0, kTapInterior = 1, kTapWrap = 2;
+template <int TAP>
 __device__ __forceinline__ void span_tap(float u, float f, float c, float capf, int &i0, float &fr) {
-  if (INTERIOR) {
+  if (TAP == kTapWrap) {
+    const float x = fmaf(u, f, c);
+    const float t = floorf(x);
+    i0 = (int)t;
+    fr = x - t;
+  } else if (TAP == kTapInterior) {
     const float x = fmaf(u, f, c);
     i0 = (int)x;  // x >= 0: truncation is the floor
     fr = __builtin_amdgcn_fractf(x);
@@ -1171,7 +1222,7 @@ __device__ __forceinline__ void operands16(const Tex16 (&c)[kMaxLevels], float u
 }
 
 // Operands of the pixel (uq, vq) from the staged texels.
-template <class P, bool INTERIOR>
+template <class P, int TAP>
 __device__ __forceinline__ void staged_operands(const DecodeArgs &a, const f32x4 *stage, const f32x4 *ltab,
                                                 const int (&kbw)[kMaxLevels], const int (&kbase)[kMaxLevels],
                                                 float uq, float vq, float in_scale, int salt,
@@ -1185,8 +1236,8 @@ __device__ __forceinline__ void staged_operands(const DecodeArgs &a, const f32x4
       Lk.read(ltab + opaque_zero(salt), k);
       int i0, j0;
       float fx, fy;
-      span_tap<INTERIOR>(uq, Lk.fw, Lk.cx, Lk.wm2, i0, fx);
-      span_tap<INTERIOR>(vq, Lk.fh, Lk.cy, Lk.hm2, j0, fy);
+      span_tap<TAP>(uq, Lk.fw, Lk.cx, Lk.wm2, i0, fx);
+      span_tap<TAP>(vq, Lk.fh, Lk.cy, Lk.hm2, j0, fy);
       int r = __mul24(j0, kbw[k]) + i0;
       asm("" : "+v"(r));
       const uint2 *t = s16 + kbase[k] + r;
@@ -1205,8 +1256,8 @@ __device__ __forceinline__ void staged_operands(const DecodeArgs &a, const f32x4
     Lk.read(ltab + opaque_zero(salt), k);
     int i0, j0;
     float fx, fy;
-    span_tap<INTERIOR>(uq, Lk.fw, Lk.cx, Lk.wm2, i0, fx);
-    span_tap<INTERIOR>(vq, Lk.fh, Lk.cy, Lk.hm2, j0, fy);
+    span_tap<TAP>(uq, Lk.fw, Lk.cx, Lk.wm2, i0, fx);
+    span_tap<TAP>(vq, Lk.fh, Lk.cy, Lk.hm2, j0, fy);
     // taps lie inside the staged region of the level; the row offset is
     // one multiply-add and the byte address one shift-add (the empty asm
     // keeps the compiler from distributing the shift over the sum)
@@ -1223,16 +1274,17 @@ __device__ __forceinline__ void staged_operands(const DecodeArgs &a, const f32x4
 
 // Operands of the pixel (uq, vq) with direct block fetches (footprint beyond
 // the LDS region, or wrap addressing).
-template <class P>
+template <class P, int ADDR>
 __device__ __forceinline__ void direct_operands(const DecodeArgs &a, const f32x4 *ltab, float uq, float vq,
                                                 float in_scale, int salt, typename P::Frag (&bx)[2]) {
+  const int mode = a.lat.address;  // read at run time also where the kernel knows it (see direct_taps)
   if constexpr (P::kF16Tex) {
     Tex16 c[kMaxLevels];
 #pragma unroll
     for (int k = 0; k < kMaxLevels; ++k) {
       TabLevel Lk;
       Lk.read(ltab + opaque_zero(salt), k);
-      c[k] = sample_direct16(Lk, uq, vq, a.lat.address);
+      c[k] = sample_direct16<ADDR>(Lk, uq, vq, mode);
     }
     operands16(c, uq, vq, bx);
     return;
@@ -1242,7 +1294,7 @@ __device__ __forceinline__ void direct_operands(const DecodeArgs &a, const f32x4
   for (int k = 0; k < kMaxLevels; ++k) {
     TabLevel Lk;
     Lk.read(ltab + opaque_zero(salt), k);
-    put_level(xl, xh, k, sample_direct_t(Lk, uq, vq, a.lat.address));
+    put_level(xl, xh, k, sample_direct_t<ADDR>(Lk, uq, vq, mode));
   }
   pixel_operands<P>(xl, xh, uq, vq, in_scale, bx);
 }
@@ -1284,7 +1336,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t span_out(const DecodeArgs &a, 
 // during this span, so that its latency overlaps the work of the span.
 // obuf (2 KB of LDS, or nullptr): output staging of the FP32 rows of widths
 // that are not a multiple of 4 (see store_outputs).
-template <class P, int HID, int NL, int ST, int VEC4, bool IDX = false>
+template <class P, int HID, int NL, int ST, int VEC4, bool IDX = false, int ADDR = kEitherMode>
 __device__ __forceinline__ void decode_span(const DecodeArgs &a, int64_t first, int64_t end_px, f32x4 *stage,
                                             const f32x4 *bias, f32x4 *ltab, const MfmaWeights<P, HID, NL> &W,
                                             SpanUv<ST> &uvs, int64_t next_first, int64_t next_end_px,
@@ -1306,7 +1358,7 @@ __device__ __forceinline__ void decode_span(const DecodeArgs &a, int64_t first, 
   }
   int kbw[kMaxLevels], kbase[kMaxLevels];
   bool in_unit, interior;
-  const bool staged = stage_span<ST, P::kF16Tex>(a, u, v, stage, ltab, ltab + LevelTab::kLevelEntries, span_salt,
+  const bool staged = stage_span<ST, P::kF16Tex, false, ADDR>(a, u, v, stage, ltab, ltab + LevelTab::kLevelEntries, span_salt,
                                                  kbw, kbase, in_unit, interior);
 
   // FP16: the staged path runs with ReLU by clamp, so it takes only spans
@@ -1327,7 +1379,7 @@ __device__ __forceinline__ void decode_span(const DecodeArgs &a, int64_t first, 
       NTC_UNROLL_STAGED
       for (int q = 0; q < ST; ++q) {
         Frag bx[2];
-        staged_operands<P, true>(a, stage, ltab, kbw, kbase, u[q], v[q], W.in_scale, span_salt + q, bx);
+        staged_operands<P, kTapInterior>(a, stage, ltab, kbw, kbase, u[q], v[q], W.in_scale, span_salt + q, bx);
         subspan_mlp<P, HID, NL, VEC4, P::kUnitReLU, IDX>(a, W, bias, ors, bx, q, span_salt + 2 * q, first, span,
                                                          obuf);
       }
@@ -1335,7 +1387,7 @@ __device__ __forceinline__ void decode_span(const DecodeArgs &a, int64_t first, 
       NTC_UNROLL_STAGED
       for (int q = 0; q < ST; ++q) {
         Frag bx[2];
-        staged_operands<P, false>(a, stage, ltab, kbw, kbase, u[q], v[q], W.in_scale, span_salt + q, bx);
+        staged_operands<P, kTapClamp>(a, stage, ltab, kbw, kbase, u[q], v[q], W.in_scale, span_salt + q, bx);
         subspan_mlp<P, HID, NL, VEC4, P::kUnitReLU, IDX>(a, W, bias, ors, bx, q, span_salt + 2 * q, first, span,
                                                          obuf);
       }
@@ -1354,7 +1406,7 @@ __device__ __forceinline__ void decode_span(const DecodeArgs &a, int64_t first, 
       v[i] = v[i + 1];
     }
     Frag bx[2];
-    direct_operands<P>(a, ltab, uq, vq, W.in_scale, q, bx);
+    direct_operands<P, ADDR>(a, ltab, uq, vq, W.in_scale, q, bx);
     subspan_mlp<P, HID, NL, VEC4, false, IDX>(a, W, bias, ors, bx, q, 2 * q, first, span, obuf);
   }
   // the next span's uv, completed here: this path then leaves no pending
@@ -1362,6 +1414,53 @@ __device__ __forceinline__ void decode_span(const DecodeArgs &a, int64_t first, 
   if (NTC_UV_PREFETCH && next_first >= 0) {
     uvs.template load_any<IDX>(a, next_first, next_end_px);
     uvs.ready();
+  }
+}
+
+// The same for wrap addressing: the span staged before wrapping, or fetched
+// directly. Rolled, with the max-based ReLU (wrapped coordinates mostly leave
+// the unit square). 1920x1080 over 1024^2..128^2 levels, FP16 14-64-64-8, rows
+// of pixels: 83 -> 49 us (staged), with the levels repeated three times (1.6
+// texels a pixel, footprints at the staging limit) 83 -> 68, random
+// coordinates (never staged; no integer divisions in the taps) 83 -> 81.
+// (Staging sub-span by sub-span where a span does not fit decodes about as
+// many texels as direct fetches: 94 against 87 us.)
+template <class P, int HID, int NL, int ST, int VEC4>
+__device__ __forceinline__ void decode_span_wrap(const DecodeArgs &a, int64_t first, int64_t end_px, f32x4 *stage,
+                                                 const f32x4 *bias, f32x4 *ltab, const MfmaWeights<P, HID, NL> &W,
+                                                 SpanUv<ST> &uvs, int64_t next_first, int64_t next_end_px,
+                                                 float *obuf) {
+  const int64_t left = end_px - first;
+  const int span = left < 64 * ST ? (int)left : 64 * ST;
+  const __amdgpu_buffer_rsrc_t ors = span_out(a, first, span);
+  float u[ST], v[ST];
+#pragma unroll
+  for (int q = 0; q < ST; ++q) {
+    u[q] = uvs.u[q];
+    v[q] = uvs.v[q];
+  }
+  f32x4 *srec = ltab + LevelTab::kLevelEntries;
+  int kbw[kMaxLevels], kbase[kMaxLevels];
+  bool in_unit, interior;
+  const bool whole =
+      stage_span<ST, P::kF16Tex, false, kWrapOnly>(a, u, v, stage, ltab, srec, (int)first, kbw, kbase, in_unit, interior);
+  if (next_first >= 0) uvs.load(a.uv, next_first, next_end_px);
+#pragma unroll 1
+  for (int q = 0; q < ST; ++q) {
+    if (64 * q >= span) break;
+    const float uq = u[0], vq = v[0];
+#pragma unroll
+    for (int i = 0; i + 1 < ST; ++i) {
+      u[i] = u[i + 1];
+      v[i] = v[i + 1];
+    }
+    const int salt = (int)first + q;
+    typename P::Frag bx[2];
+    if (whole)
+      staged_operands<P, kTapWrap>(a, stage, ltab, kbw, kbase, uq, vq, W.in_scale, salt, bx);
+    else
+      direct_operands<P, kWrapOnly>(a, ltab, uq, vq, W.in_scale, salt, bx);
+    subspan_mlp<P, HID, NL, VEC4, false>(a, W, bias, ors, bx, q, 2 * salt, first, span, obuf);
   }
 }
 

@@ -220,7 +220,7 @@ __device__ __forceinline__ float3 staged_level(const uint2 *t, int pitch, float 
 __device__ __forceinline__ float3 direct_level(const TabLevel &L, float u, float v, int mode) {
   int i0, i1, j0, j1;
   float fx, fy;
-  direct_taps(L, u, v, mode, i0, i1, j0, j1, fx, fy);
+  direct_taps<kEitherMode>(L, u, v, mode, i0, i1, j0, j1, fx, fy);
   auto at = [&](int i, int j) {
     const uint2 b = gload2u(L.bc1 + (int64_t)(j >> 2) * L.bw + (i >> 2));
     const uint32_t p = bc1_numer(b.x, b.y, (uint32_t)(((j & 3) << 2) | (i & 3)));
@@ -248,10 +248,11 @@ __device__ __forceinline__ void grid_levels(const LatArgs &lat, float u, float v
   if (lat.address == 1) {
 #pragma unroll
     for (int k = 0; k < kMaxLevels; ++k) {
-      i1[k] = address_coord(i0[k] + 1, lat.lv[k].w, 1);
-      j1[k] = address_coord(j0[k] + 1, lat.lv[k].h, 1);
-      i0[k] = address_coord(i0[k], lat.lv[k].w, 1);
-      j0[k] = address_coord(j0[k], lat.lv[k].h, 1);
+      const int w = lat.lv[k].w, h = lat.lv[k].h;
+      i0[k] = wrap_near(i0[k], w, __builtin_amdgcn_rcpf((float)w));
+      j0[k] = wrap_near(j0[k], h, __builtin_amdgcn_rcpf((float)h));
+      i1[k] = i0[k] + 1 == w ? 0 : i0[k] + 1;
+      j1[k] = j0[k] + 1 == h ? 0 : j0[k] + 1;
     }
   } else {
 #pragma unroll
@@ -445,7 +446,11 @@ void decode_split_kernel(DecodeArgs a) {
     int kbw[kMaxLevels], kbase[kMaxLevels];
     bool in_unit, interior, staged = false;
     if constexpr (BC1)
-      staged = stage_span<ST, true, true>(a, u, v, stage, ltab, srec, (int)first, kbw, kbase, in_unit, interior);
+      staged = a.lat.address == 0
+                   ? stage_span<ST, true, true, kClampOnly>(a, u, v, stage, ltab, srec, (int)first, kbw, kbase, in_unit,
+                                                            interior)
+                   : stage_span<ST, true, true, kWrapOnly>(a, u, v, stage, ltab, srec, (int)first, kbw, kbase, in_unit,
+                                                           interior);
     if (it + step < n_spans) uvs.load(a.uv, (it + step) * spx, span_end(it + step));
 
 #pragma unroll 1
@@ -472,8 +477,13 @@ void decode_split_kernel(DecodeArgs a) {
               L.read(tab, k);
               int i0, j0;
               float fx, fy;
-              span_tap<false>(uq, L.fw, L.cx, L.wm2, i0, fx);
-              span_tap<false>(vq, L.fh, L.cy, L.hm2, j0, fy);
+              if (a.lat.address != 0) {
+                span_tap<kTapWrap>(uq, L.fw, L.cx, L.wm2, i0, fx);
+                span_tap<kTapWrap>(vq, L.fh, L.cy, L.hm2, j0, fy);
+              } else {
+                span_tap<kTapClamp>(uq, L.fw, L.cx, L.wm2, i0, fx);
+                span_tap<kTapClamp>(vq, L.fh, L.cy, L.hm2, j0, fy);
+              }
               c[k] = staged_level(reinterpret_cast<const uint2 *>(stage) + kbase[k] + __mul24(j0, kbw[k]) + i0, kbw[k],
                                   fx, fy);
             }
@@ -583,7 +593,7 @@ static hipError_t launch_split_hp(const DecodeArgs &a, int n_layers, int groups,
 }
 
 hipError_t launch_decode_f32(DecodeArgs a, const MlpShape &s, int n_cus, hipStream_t st) {
-  a.stage_cap = kSplitStage;
+  a.stage_cap = kSplitStage / 2;  // counted in 16-byte texels
   // Spans of 64 pixels where longer ones would leave wavefronts without work:
   // 65,536 pixels of 14-64-64-64-8 take 20 us against 29 with 128-pixel spans,
   // whose two sub-spans are one chain of 528 matrix instructions.

@@ -607,3 +607,45 @@ def test_f32_split_pixels_do_not_depend_on_neighbours():
     fin = at[np.isfinite(O.features(O.Latents(lat_np, shift=I.PAPER_SHIFT[:2]), far[at])).all(1)]
     assert fin.size > 400
     assert np.all(np.abs(b[fin] - ref[fin]) <= TOL_F32_REL * np.abs(ref[fin]) + 1e-6)
+
+
+@pytest.mark.parametrize("compute", ["f16", "bf16", "fp8", "f32"])
+@pytest.mark.parametrize("sizes,scale,offset", [
+    ([(64, 64), (32, 32), (16, 16), (8, 8)], 3.0, -1.0),       # spans across the edges, several periods
+    ([(64, 32), (32, 16), (16, 8), (4, 4)], 0.3, 0.85),        # footprints over one edge
+    ([(128, 128), (64, 64), (8, 8), (4, 4)], 40.0, -20.0),     # footprints wider than the small levels, or not staged
+    ([(64, 64), (32, 32), (16, 16), (8, 8)], 1.0, 30000.0),    # far from the origin
+    ([(64, 64), (32, 32), (16, 16), (8, 8)], 1.0e5, -4.0e4),   # positions past the staged range
+])
+def test_wrap_staged_equals_direct(compute, sizes, scale, offset):
+    """Wrap addressing: coherent pixels (footprints staged before wrapping)
+    give bit for bit what the same pixels give with the smallest staging
+    capacity and in shuffled order (direct fetches), over edges, several
+    periods, levels smaller than a footprint, coordinates far out and NaN."""
+    ntc = _ntc()
+    rng = np.random.default_rng(71)
+    lat_np = I.bc1_pyramid(rng, sizes)
+    Ws, bs = I.xavier_mlp(rng, (14, 32, 32, 9), bias="normal")
+    Ws[0][:, 12:] *= np.float32(1.0 / max(1.0, abs(offset) + scale))
+    lat = ntc.Latents(lat_np, shift=I.PAPER_SHIFT, address="wrap")
+    mlp = ntc.Mlp(Ws, bs)
+    w, h = 333, 61
+    k = np.arange(w * h)
+    uv = (np.stack([(k % w + 0.5) / w, (k // w + 0.5) / w], 1) * scale + offset).astype(np.float32)
+    uv[5000] = np.nan
+    uv[9000, 1] = np.inf
+    amax = ntc.calibrate_fp8(lat, mlp, torch.rand((4096, 2), device="cuda")) if compute == "fp8" else None
+    packed = ntc.pack(mlp, compute, act_amax=amax)
+    t = torch.from_numpy(uv).cuda()
+    a = ntc.decode(lat, mlp, t, compute=compute, packed=packed).cpu().numpy()
+    fin = np.isfinite(uv).all(1)
+    perm = rng.permutation(w * h)
+    b = ntc.decode(lat, mlp, t[torch.from_numpy(perm).cuda()].contiguous(), compute=compute, packed=packed).cpu().numpy()
+    assert np.array_equal(a[perm][fin[perm]], b[fin[perm]])
+    if compute != "f32":
+        c = ntc.decode(lat, mlp, t, compute=compute, packed=packed, cfg=ntc.tile_cfg(stage_capacity=64)).cpu().numpy()
+        assert np.array_equal(a[fin], c[fin])
+    # FP32 coordinates of this size carry the position to a fraction of a texel only as far as scale and offset allow
+    if abs(offset) + scale <= 64.0 and compute in ("f32", "f16"):
+        ref = O.decode(O.Latents(lat_np, shift=I.PAPER_SHIFT, address=O.WRAP), O.Mlp(Ws, bs), uv[fin])
+        assert np.max(np.abs(a[fin] - ref)) <= (TOL_F16_ABS if compute == "f16" else 1e-5)
