@@ -8,12 +8,17 @@
 // pixels to lists with global atomics, and notes that these do not scale
 // when many tiles are mixed. Here the lists are built without global
 // atomics and in a fixed order, so that the result is deterministic:
-//   1. count: one wavefront per chunk of 128 consecutive tiles (two tiles per
-//      step, lane = pixel) classifies each tile and counts its valid pixels
-//      per key (material, kind), kind 0 = simple tile, 1 = other;
+//   1. count: one workgroup per chunk of 128 consecutive tiles (two tiles per
+//      wavefront step, lane = pixel) classifies each tile and counts its valid
+//      pixels per key (material, kind), kind 0 = simple tile, 1 = other;
 //   2. scan: per key, exclusive prefix over chunks; then over materials;
-//   3. write: the same walk ranks each pixel inside its key group (ballot and
-//      lane-count) and writes its index.
+//   3. write: the same walk, once to count per wavefront and once to rank each
+//      pixel inside its key group (ballot and lane-count) and write its index.
+// A chunk's 64 steps are a chain of load, ballot and LDS latencies, and a
+// frame has fewer chunks than the card has SIMDs (2560 x 1440: 900), so a
+// chunk is shared by eight wavefronts of eight consecutive steps each, whose
+// material ids are loaded together (count 12, write 16 us at 2560 x
+// 1440 with 64 materials; one wavefront per chunk 35 and 37 us).
 // Output: the valid pixels grouped by material; inside a material, first
 // the pixels of its simple tiles, then its other pixels, each part in tile
 // order and row-major inside a tile.
@@ -73,21 +78,56 @@ __device__ __forceinline__ StepPixel step_pixel(const ClassifyArgs &a, int chunk
 // so that one wait covers all of them instead of one load latency per step.
 constexpr int kPrefetch = 8;
 
+// Wavefronts of a chunk. The write pass keeps a position per key and
+// wavefront in LDS (64 bytes a material with eight); above kWideMats
+// materials that would be more than 64 KiB, and one wavefront walks the chunk.
+constexpr int kChunkWaves = kTilesPerChunk / 2 / kPrefetch;
+constexpr int kWideMats = 1024;
+
 // Kind of the pixel's tile (0 simple, 1 other) and the tile's class
 // (0 no neural pixel, 1 simple, 2 mixed or sparse), from the 32 lanes of
 // its half of the wavefront.
 __device__ __forceinline__ void tile_kind(bool valid, uint32_t m, int lane, int &kind, int &cls) {
   const uint64_t vb = __ballot(valid);
-  const int n = __popcll((vb >> (lane & 32)) & 0xFFFFFFFFull);
-  uint32_t mn = valid ? m : 0xFFFFFFFFu, mx = valid ? m : 0u;
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) {
-    mn = min(mn, (uint32_t)__shfl_xor((int)mn, o, 32));
-    mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, 32));
-  }
-  const bool simple = n > 16 && mn == mx;
+  const uint32_t lo = (uint32_t)vb, hi = (uint32_t)(vb >> 32);
+  // the first valid id of each half against all of them
+  const int m_lo = __builtin_amdgcn_readlane((int)m, lo ? __builtin_ctz(lo) : 0);
+  const int m_hi = __builtin_amdgcn_readlane((int)m, 32 + (hi ? __builtin_ctz(hi) : 0));
+  const uint64_t differ = __ballot(valid && (int)m != (lane < 32 ? m_lo : m_hi));
+  const int n = lane < 32 ? __popc(lo) : __popc(hi);
+  const bool simple = n > 16 && (uint32_t)(differ >> (lane & 32)) == 0;
   kind = simple ? 0 : 1;
   cls = n == 0 ? 0 : (simple ? 1 : 2);
+}
+
+// Keys (material, kind) of kPrefetch steps from s0, -1 where there is no
+// valid pixel, and the pixels' indices.
+__device__ __forceinline__ void step_keys(const ClassifyArgs &a, int chunk, int s0, int lane, bool classes,
+                                          int (&key)[kPrefetch], int32_t (&idx)[kPrefetch]) {
+  StepPixel ps[kPrefetch];
+#pragma unroll
+  for (int i = 0; i < kPrefetch; ++i) ps[i] = step_pixel(a, chunk, s0 + i, lane);
+#pragma unroll
+  for (int i = 0; i < kPrefetch; ++i) {
+    const bool valid = ps[i].m < (uint32_t)a.n_mats;
+    int kind, cls;
+    tile_kind(valid, ps[i].m, lane, kind, cls);
+    if (classes && (lane & 31) == 0 && ps[i].tile < a.n_tiles) a.tile_class[ps[i].tile] = (uint8_t)cls;
+    key[i] = valid ? 2 * (int)ps[i].m + kind : -1;
+    idx[i] = ps[i].idx;
+  }
+}
+
+// f(k, same): every key k among the wavefront's lanes, with the lanes that have it.
+template <class F>
+__device__ __forceinline__ void each_key(int key, F f) {
+  uint64_t pending = __ballot(key >= 0);
+  while (pending) {
+    const int k = __builtin_amdgcn_readlane(key, __builtin_ctzll(pending));
+    const uint64_t same = __ballot(key == k);
+    f(k, same);
+    pending &= ~same;
+  }
 }
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
@@ -95,37 +135,28 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
 }
 
 // Pass 1: per chunk and key, the number of valid pixels. LDS: 2 n_mats ints.
-__global__ __launch_bounds__(64) void classify_count_kernel(ClassifyArgs a) {
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void classify_count_kernel(ClassifyArgs a) {
   extern __shared__ int32_t cnt[];
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int chunk = blockIdx.x;
   const int n_keys = 2 * a.n_mats;
-  for (int k = lane; k < n_keys; k += 64) cnt[k] = 0;
+  for (int k = threadIdx.x; k < n_keys; k += 64 * WAVES) cnt[k] = 0;
   __syncthreads();
-  for (int s0 = 0; s0 < kTilesPerChunk / 2; s0 += kPrefetch) {
-    StepPixel ps[kPrefetch];
+  constexpr int kSteps = kTilesPerChunk / 2 / WAVES;
+  for (int s0 = wave * kSteps; s0 < (wave + 1) * kSteps; s0 += kPrefetch) {
+    int key[kPrefetch];
+    int32_t idx[kPrefetch];
+    step_keys(a, chunk, s0, lane, a.tile_class != nullptr, key, idx);
 #pragma unroll
-    for (int i = 0; i < kPrefetch; ++i) ps[i] = step_pixel(a, chunk, s0 + i, lane);
-#pragma unroll
-    for (int i = 0; i < kPrefetch; ++i) {
-      const StepPixel p = ps[i];
-      const bool valid = p.m < (uint32_t)a.n_mats;
-      int kind, cls;
-      tile_kind(valid, p.m, lane, kind, cls);
-      if (a.tile_class && (lane & 31) == 0 && p.tile < a.n_tiles) a.tile_class[p.tile] = (uint8_t)cls;
-      const int key = valid ? 2 * (int)p.m + kind : -1;
-      uint64_t pending = __ballot(valid);
-      while (pending) {
-        const int leader = __builtin_ctzll(pending);
-        const int k = __builtin_amdgcn_readlane(key, leader);
-        const uint64_t same = __ballot(key == k);
-        if (lane == 0) cnt[k] += __popcll(same);
-        pending &= ~same;
-      }
-    }
+    for (int i = 0; i < kPrefetch; ++i)
+      each_key(key[i], [&](int k, uint64_t same) {
+        if (lane == 0) atomicAdd(&cnt[k], __popcll(same));
+      });
   }
   __syncthreads();
-  for (int k = lane; k < n_keys; k += 64) a.counts[(int64_t)k * a.n_chunks + chunk] = cnt[k];
+  for (int k = threadIdx.x; k < n_keys; k += 64 * WAVES) a.counts[(int64_t)k * a.n_chunks + chunk] = cnt[k];
 }
 
 // Pass 2a: one workgroup per key, exclusive prefix over chunks (in place),
@@ -180,42 +211,54 @@ __global__ __launch_bounds__(kScanThreads) void classify_scan_materials_kernel(C
   if (threadIdx.x == kScanThreads - 1) a.mat_offsets[a.n_mats] = part[kScanThreads - 1];
 }
 
-// Pass 3: write every valid pixel's index at its place. LDS: 2 n_mats ints
-// (the running position of each key inside this chunk's share).
-__global__ __launch_bounds__(64) void classify_write_kernel(ClassifyArgs a) {
-  extern __shared__ int32_t run[];
-  const int lane = threadIdx.x;
+// Pass 3: write every valid pixel's index at its place. LDS: per wavefront
+// 2 n_mats ints, the number of its pixels of each key, then the running
+// position of the key inside the wavefront's share.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void classify_write_kernel(ClassifyArgs a) {
+  extern __shared__ int32_t run_all[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int chunk = blockIdx.x;
   const int n_keys = 2 * a.n_mats;
-  for (int k = lane; k < n_keys; k += 64) {
-    const int m = k >> 1;
-    run[k] = a.mat_offsets[m] + ((k & 1) ? a.totals[k - 1] : 0) + a.counts[(int64_t)k * a.n_chunks + chunk];
+  int32_t *run = run_all + wave * n_keys;
+  constexpr int kSteps = kTilesPerChunk / 2 / WAVES;
+  static_assert(WAVES == 1 || kSteps == kPrefetch, "the keys of a wavefront's steps stay in registers");
+  int key[kPrefetch];
+  int32_t idx[kPrefetch];
+  if (WAVES > 1) {
+    for (int k = threadIdx.x; k < WAVES * n_keys; k += 64 * WAVES) run_all[k] = 0;
+    step_keys(a, chunk, wave * kSteps, lane, false, key, idx);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPrefetch; ++i)
+      each_key(key[i], [&](int k, uint64_t same) {
+        if (lane == 0) run[k] += __popcll(same);
+      });
+    __syncthreads();
+  }
+  for (int k = threadIdx.x; k < n_keys; k += 64 * WAVES) {
+    int32_t pos = a.mat_offsets[k >> 1] + ((k & 1) ? a.totals[k - 1] : 0) + a.counts[(int64_t)k * a.n_chunks + chunk];
+    if (WAVES == 1) run[k] = pos;
+#pragma unroll
+    for (int w = 0; w < WAVES && WAVES > 1; ++w) {
+      const int32_t n = run_all[w * n_keys + k];
+      run_all[w * n_keys + k] = pos;
+      pos += n;
+    }
   }
   __syncthreads();
-  for (int s0 = 0; s0 < kTilesPerChunk / 2; s0 += kPrefetch) {
-    StepPixel ps[kPrefetch];
+  for (int s0 = wave * kSteps; s0 < (wave + 1) * kSteps; s0 += kPrefetch) {
+    if (WAVES == 1) step_keys(a, chunk, s0, lane, false, key, idx);
 #pragma unroll
-    for (int i = 0; i < kPrefetch; ++i) ps[i] = step_pixel(a, chunk, s0 + i, lane);
-#pragma unroll
-    for (int i = 0; i < kPrefetch; ++i) {
-      const StepPixel p = ps[i];
-      const bool valid = p.m < (uint32_t)a.n_mats;
-      int kind, cls;
-      tile_kind(valid, p.m, lane, kind, cls);
-      const int key = valid ? 2 * (int)p.m + kind : -1;
-      uint64_t pending = __ballot(valid);
-      while (pending) {
-        const int leader = __builtin_ctzll(pending);
-        const int k = __builtin_amdgcn_readlane(key, leader);
-        const uint64_t same = __ballot(key == k);
+    for (int i = 0; i < kPrefetch; ++i)
+      each_key(key[i], [&](int k, uint64_t same) {
         const int base = run[k];
-        if (key == k) a.list[base + (int)lanes_below(same)] = p.idx;
+        if (key[i] == k) a.list[base + (int)lanes_below(same)] = idx[i];
         // every lane has read run[k] before lane 0 moves it (one wavefront,
         // LDS operations complete in order)
         if (lane == 0) run[k] = base + __popcll(same);
-        pending &= ~same;
-      }
-    }
+      });
   }
 }
 
@@ -261,14 +304,22 @@ hipError_t launch_classify(const uint16_t *mat, int w, int h, int n_mats, int32_
   a.list = list;
   a.tile_class = tile_class;
   const size_t lds = 2 * (size_t)n_mats * sizeof(int32_t);
-  hipLaunchKernelGGL(classify_count_kernel, dim3(a.n_chunks), dim3(64), lds, st, a);
+  const bool wide = n_mats <= kWideMats;
+  if (wide)
+    hipLaunchKernelGGL(classify_count_kernel<kChunkWaves>, dim3(a.n_chunks), dim3(64 * kChunkWaves), lds, st, a);
+  else
+    hipLaunchKernelGGL(classify_count_kernel<1>, dim3(a.n_chunks), dim3(64), lds, st, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(classify_scan_chunks_kernel, dim3(2 * n_mats), dim3(kScanThreads), 0, st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(classify_scan_materials_kernel, dim3(1), dim3(kScanThreads), 0, st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(classify_write_kernel, dim3(a.n_chunks), dim3(64), lds, st, a);
+  if (wide)
+    hipLaunchKernelGGL(classify_write_kernel<kChunkWaves>, dim3(a.n_chunks), dim3(64 * kChunkWaves),
+                       kChunkWaves * lds, st, a);
+  else
+    hipLaunchKernelGGL(classify_write_kernel<1>, dim3(a.n_chunks), dim3(64), lds, st, a);
   return hipGetLastError();
 }
 

@@ -46,6 +46,23 @@ def test_classify_bitexact(f):
     assert torch.equal(lst, lst2)
 
 
+# Both widths of the walk (up to 1024 materials eight wavefronts share a chunk
+# of 128 tiles), a last chunk of one tile, of one wavefront's and of all but
+# one wavefront's tiles, frames of noise alone.
+@pytest.mark.parametrize("w,h,n,noise", [(8, 4 * 129, 2, 0.5), (8, 4 * 144, 70, 1.0), (1024, 4 * 7 - 1, 1024, 0.1),
+                                         (1024, 4 * 7 - 1, 1025, 0.1), (333, 77, 4096, 1.0)])
+def test_classify_chunk_shares(w, h, n, noise):
+    ntc = _ntc()
+    mat = I.material_frame(np.random.default_rng(w + h + n), w, h, n, noise=noise)
+    olst, ooff, osimple, otcls = C.classify(mat, n)
+    for classes in (True, False):
+        lst, off, simple, tcls = ntc.classify(torch.from_numpy(mat).cuda(), n, tile_class=classes)
+        assert np.array_equal(off.cpu().numpy(), ooff)
+        assert np.array_equal(simple.cpu().numpy(), osimple)
+        assert np.array_equal(lst.cpu().numpy(), olst)
+        assert tcls is None if not classes else np.array_equal(tcls.cpu().numpy(), otcls)
+
+
 def test_gather_and_scatter():
     ntc = _ntc()
     rng = np.random.default_rng(8)
