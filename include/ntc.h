@@ -396,6 +396,31 @@ ntc_status ntc_batched_plan(const ntc_material *mats, int32_t n_mats, const ntc_
  * the host image (read for the launch size only), plan_dev its device copy. */
 ntc_status ntc_decode_batched(const void *plan_host, const void *plan_dev, size_t bytes, void *stream);
 
+/* The same for a classified frame, with the plan built on the device, so
+ * that nothing waits for the lists of ntc_classify. A frame table holds what
+ * does not depend on the frame: latents, MLP shapes and packed images of the
+ * materials (n, uv, out, pixel_index and image_pixels of `mats` are not read;
+ * one output width and dtype; n_mats in 1..NTC_MAX_CLASSIFY_MATERIALS), and of
+ * `cfg` waves_per_cu, stage_capacity and n_cus. Build it in host memory, copy
+ * it to the device once (256-byte aligned), use it for any number of frames,
+ * in any streams at once. [host] */
+ntc_status ntc_frame_table_size(int32_t n_mats, size_t *bytes);
+ntc_status ntc_frame_table(const ntc_material *mats, int32_t n_mats, const ntc_batch_cfg *cfg, void *table_host,
+                           size_t bytes);
+
+/* Workspace bytes of ntc_decode_frame. [host] */
+ntc_status ntc_decode_frame_workspace(const void *table_host, size_t table_bytes, size_t *bytes);
+
+/* Decode a frame: material m reads uv[p] and writes out[p] for the pixels p of
+ * pixel_list[mat_offsets[m] .. mat_offsets[m + 1]), as written by ntc_classify
+ * [device]. uv [image_pixels][2], out [image_pixels][C] with the limits of
+ * ntc_material. table_host is the host image (read for sizes only), table_dev
+ * its device copy. workspace [device, 256-byte aligned] holds the plan until
+ * the launch has run: one per call in flight. */
+ntc_status ntc_decode_frame(const void *table_host, const void *table_dev, size_t table_bytes,
+                            const int32_t *pixel_list, const int32_t *mat_offsets, const float *uv, void *out,
+                            int64_t image_pixels, void *workspace, size_t ws_bytes, void *stream);
+
 /* ------------------------------------------------------------------------
  * Test export: BC1 texel decode of one level (Sec. 3.1 blend).
  * numer [device, may be NULL] uint16 [H][W][3]: exact numerators of the

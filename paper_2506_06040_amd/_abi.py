@@ -105,6 +105,10 @@ SIGNATURES = {
                                      ctypes.POINTER(_SZ)]),
     "ntc_batched_plan": (_I32, [ctypes.POINTER(ntc_material), _I32, ctypes.POINTER(ntc_batch_cfg), _P, _SZ]),
     "ntc_decode_batched": (_I32, [_P, _P, _SZ, _P]),
+    "ntc_frame_table_size": (_I32, [_I32, ctypes.POINTER(_SZ)]),
+    "ntc_frame_table": (_I32, [ctypes.POINTER(ntc_material), _I32, ctypes.POINTER(ntc_batch_cfg), _P, _SZ]),
+    "ntc_decode_frame_workspace": (_I32, [_P, _SZ, ctypes.POINTER(_SZ)]),
+    "ntc_decode_frame": (_I32, [_P, _P, _SZ, _P, _P, _P, _P, _I64, _P, _SZ, _P]),
     "ntc_bc1_decode_texels": (_I32, [ctypes.POINTER(ntc_latents), _I32, _P, _P, _P]),
 }
 

@@ -422,15 +422,19 @@ def _device_cus(device="cuda") -> int:
 # Frame classification by material and the frame decode it feeds
 # (Sec. 4 "Tile-based classification", Algorithm 1)
 # ---------------------------------------------------------------------------
+def _require_ids(mat_ids: torch.Tensor):
+    _require_cuda(mat_ids, "mat_ids")
+    if mat_ids.dtype not in (torch.uint16, torch.int16) or mat_ids.dim() != 2 or not mat_ids.is_contiguous():
+        raise ValueError("mat_ids must be a contiguous [H][W] uint16 (or int16 bit pattern) tensor")
+
+
 def classify(mat_ids: torch.Tensor, n_mats: int, tile_class: bool = True):
     """Classify the 8x4 tiles of a frame (uint16 material ids [H][W]; ids >=
     n_mats are not neural). Returns (pixel_list int32 [valid], mat_offsets
     int32 [n_mats + 1], mat_simple int32 [n_mats], tile_class uint8 [tiles]
     or None); pixel_list is sliced to the valid count, which takes one
     device-to-host copy of mat_offsets[n_mats]."""
-    _require_cuda(mat_ids, "mat_ids")
-    if mat_ids.dtype not in (torch.uint16, torch.int16) or mat_ids.dim() != 2 or not mat_ids.is_contiguous():
-        raise ValueError("mat_ids must be a contiguous [H][W] uint16 (or int16 bit pattern) tensor")
+    _require_ids(mat_ids)
     h, w = mat_ids.shape
     dev = mat_ids.device
     ws = ctypes.c_size_t(0)
@@ -471,8 +475,11 @@ def scatter_rows(rows: torch.Tensor, pixel_list: torch.Tensor, image: torch.Tens
 
 class FrameDecoder:
     """Decode a frame whose pixels use several neural materials: classify
-    the tiles, gather the uv of every material's pixels, decode them with
-    one batched launch (FP16 matrix cores) and scatter the outputs back.
+    the tiles and decode every material's pixels through the lists with one
+    batched launch (FP16 matrix cores), or gather their uv, decode and scatter
+    the outputs back. The batch plan is built on the device, so that decode
+    waits for nothing; with a cfg of the caller's own (work item size), or
+    gathered, it is built on the host.
     materials: sequence of (Latents, Mlp) with a common output width."""
 
     def __init__(self, materials, cfg=None, out_dtype=torch.float32, device="cuda"):
@@ -483,6 +490,7 @@ class FrameDecoder:
         self.n_out = widths.pop()
         self.packed = [pack(m, "f16") for _, m in self.materials]
         self.cfg, self.out_dtype, self.device = cfg, out_dtype, device
+        self._table = None  # (signature, host image, device image) of _frame_table
 
     def plan(self, mat_ids: torch.Tensor, uv_image: torch.Tensor, out: Optional[torch.Tensor] = None,
              indexed: bool = True):
@@ -532,12 +540,81 @@ class FrameDecoder:
             out = torch.zeros((h, w, self.n_out), dtype=self.out_dtype, device=self.device)
         if not out.is_contiguous() or out.dtype != self.out_dtype or tuple(out.shape) != (h, w, self.n_out):
             raise ValueError("out must be a contiguous [H][W][C] image of the decoder's dtype")
+        if indexed and self.cfg is None and self._decode_on_device(mat_ids, uv_image, out):
+            return out
         p = self.plan(mat_ids, uv_image, out=out, indexed=indexed)
         if p["plan"] is not None:
             p["plan"].launch()
             if not indexed:
                 scatter_rows(p["rows"], p["pixel_list"], out)
         return out
+
+    def _frame_table(self):
+        """Host and device image of the materials' frame table (what of the
+        batch plan does not depend on the frame), laid out again whenever a
+        pointer, size or shape in it changes. None if a material is outside
+        what a batch takes."""
+        sig = b"".join([bytes(lat.c) + bytes(mlp.c) + packed.data_ptr().to_bytes(8, "little")
+                        for (lat, mlp), packed in zip(self.materials, self.packed)])
+        sig = (sig, self.out_dtype, str(self.device))
+        table = self._table
+        if table is not None and table[0] == sig:
+            return table
+        n = len(self.materials)
+        arr = (A.ntc_material * n)()
+        for c, (lat, mlp), packed in zip(arr, self.materials, self.packed):
+            c.lat, c.mlp, c.packed, c.out_dtype = lat.c, mlp.c, packed.data_ptr(), OUT_DTYPES[self.out_dtype]
+        nbytes = ctypes.c_size_t(0)
+        cfg = batch_cfg(waves_per_cu=8, n_cus=_device_cus(self.device))
+        try:
+            check(A.lib().ntc_frame_table_size(n, ctypes.byref(nbytes)))
+            host = np.zeros(nbytes.value, dtype=np.uint8)
+            check(A.lib().ntc_frame_table(arr, n, ctypes.byref(cfg), host.ctypes.data, host.nbytes))
+        except NtcError:
+            return None
+        # a copy from pageable memory is complete when it returns; frames in
+        # flight on any stream keep the table that this one replaces
+        # (record_stream at each use)
+        dev = torch.from_numpy(host).to(self.device)
+        self._table = table = (sig, host, dev)
+        return table
+
+    def _decode_on_device(self, mat_ids: torch.Tensor, uv_image: torch.Tensor, out: torch.Tensor) -> bool:
+        """Classification, plan and decode enqueued without waiting for the
+        pixel lists. False (and nothing decoded) where the batch of the listed
+        pixels has to be checked first: more pixels than an indexed batch
+        takes, or tensors that only a frame without neural pixels may have."""
+        _require_ids(mat_ids)
+        h, w = mat_ids.shape
+        uv = uv_image.reshape(-1, 2)
+        px = uv.numel() // 2
+        row = self.n_out * out.element_size()
+        if not (uv.is_cuda and 1 <= px and max(8, row) * px < 1 << 30 and h * w <= 1 << 28 and
+                uv.data_ptr() % 8 == 0 and out.data_ptr() % 16 == 0):
+            return False
+        L, n = A.lib(), len(self.materials)
+        ws, ps = ctypes.c_size_t(0), ctypes.c_size_t(0)
+        check(L.ntc_classify_workspace(w, h, n, ctypes.byref(ws)))
+        # one buffer: offsets, simple counts, list, classification workspace
+        parts = [4 * (n + 1), 4 * n, 4 * w * h, ws.value]
+        offs = [0]
+        for b in parts:
+            offs.append(offs[-1] + (b + 255) // 256 * 256)
+        stream = torch.cuda.current_stream()
+        sh = _stream_handle(stream)
+        buf = torch.empty(offs[-1], dtype=torch.uint8, device=mat_ids.device)
+        off, simple, lst, work = (buf.data_ptr() + o for o in offs[:-1])
+        check(L.ntc_classify(_ptr(mat_ids), w, h, n, lst, off, simple, None, work, ws.value, sh))
+        table = self._frame_table()
+        if table is None:
+            return False
+        _, host, dev = table
+        check(L.ntc_decode_frame_workspace(host.ctypes.data, host.nbytes, ctypes.byref(ps)))
+        plan = torch.empty(ps.value, dtype=torch.uint8, device=mat_ids.device)
+        dev.record_stream(stream)
+        check(L.ntc_decode_frame(host.ctypes.data, _ptr(dev), host.nbytes, lst, off, _ptr(uv), _ptr(out), px,
+                                 _ptr(plan), ps.value, sh))
+        return True
 
 
 # ---------------------------------------------------------------------------

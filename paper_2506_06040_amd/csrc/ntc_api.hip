@@ -716,4 +716,86 @@ ntc_status ntc_decode_batched(const void *plan_host, const void *plan_dev, size_
   return ok();
 }
 
+ntc_status ntc_frame_table_size(int32_t n_mats, size_t *bytes) {
+  if (!bytes) return fail(NTC_E_NULL, "bytes is NULL");
+  if (n_mats < 1 || n_mats > NTC_MAX_CLASSIFY_MATERIALS)
+    return fail(NTC_E_SHAPE, "n_mats %d outside 1..%d", n_mats, NTC_MAX_CLASSIFY_MATERIALS);
+  *bytes = frame_table_bytes(n_mats);
+  return ok();
+}
+
+ntc_status ntc_frame_table(const ntc_material *mats, int32_t n_mats, const ntc_batch_cfg *cfg, void *table_host,
+                           size_t bytes) {
+  if (!mats) return fail(NTC_E_NULL, "materials is NULL");
+  size_t need = 0;
+  ntc_status st = ntc_frame_table_size(n_mats, &need);
+  if (st) return st;
+  // the frame's fields do not matter here: one tile at the packed image
+  std::vector<ntc_material> any(mats, mats + n_mats);
+  for (ntc_material &M : any) {
+    M.uv = (const float *)M.packed;
+    M.out = const_cast<void *>(M.packed);
+    M.n = 64;
+    M.pixel_index = nullptr;
+    M.image_pixels = 0;
+  }
+  BatchSetup b;
+  if ((st = setup_batch(any.data(), n_mats, cfg, &b))) return st;
+  for (int m = 1; m < n_mats; ++m)
+    if (b.mats[m].a.n_out != b.mats[0].a.n_out || b.mats[m].a.out_f16 != b.mats[0].a.out_f16)
+      return fail(NTC_E_SHAPE, "material %d: outputs unlike those of material 0", m);
+  if (!table_host) return fail(NTC_E_NULL, "table_host is NULL");
+  if (bytes < need) return fail(NTC_E_WORKSPACE, "table needs %zu bytes, got %zu", need, bytes);
+  const int cus = cfg && cfg->n_cus ? cfg->n_cus : 256, wpc = cfg && cfg->waves_per_cu ? cfg->waves_per_cu : 8;
+  build_frame_table(b.mats.data(), n_mats, cus * wpc, b.stage_cap, (uint8_t *)table_host, need);
+  return ok();
+}
+
+static ntc_status read_frame_table(const void *table_host, size_t bytes, FrameTable *t) {
+  if (!table_host) return fail(NTC_E_NULL, "table_host is NULL");
+  if (bytes < sizeof(FrameTable)) return fail(NTC_E_WORKSPACE, "table too small");
+  memcpy(t, table_host, sizeof *t);
+  if (t->plan.magic != kFrameMagic || t->plan.version != kPlanVersion) return fail(NTC_E_SHAPE, "not a frame table");
+  if (t->total_bytes > bytes) return fail(NTC_E_WORKSPACE, "frame table truncated");
+  if (t->plan.n_waves < 1 || t->plan.stage_cap < 64 || t->plan.stage_cap > 4096 || t->plan.n_mats < 1 ||
+      t->plan.n_mats > NTC_MAX_CLASSIFY_MATERIALS || t->total_bytes != frame_table_bytes(t->plan.n_mats))
+    return fail(NTC_E_SHAPE, "corrupt frame table");
+  return NTC_OK;
+}
+
+ntc_status ntc_decode_frame_workspace(const void *table_host, size_t table_bytes, size_t *bytes) {
+  if (!bytes) return fail(NTC_E_NULL, "bytes is NULL");
+  FrameTable t;
+  ntc_status st = read_frame_table(table_host, table_bytes, &t);
+  if (st) return st;
+  *bytes = t.plan.total_bytes;
+  return ok();
+}
+
+ntc_status ntc_decode_frame(const void *table_host, const void *table_dev, size_t table_bytes,
+                            const int32_t *pixel_list, const int32_t *mat_offsets, const float *uv, void *out,
+                            int64_t image_pixels, void *workspace, size_t ws_bytes, void *stream) {
+  FrameTable t;
+  ntc_status st = read_frame_table(table_host, table_bytes, &t);
+  if (st) return st;
+  if (!table_dev || !pixel_list || !mat_offsets || !uv || !out || !workspace)
+    return fail(NTC_E_NULL, "table_dev, pixel_list, mat_offsets, uv, out or workspace is NULL");
+  if (!aligned(table_dev, 256) || !aligned(workspace, 256))
+    return fail(NTC_E_ALIGN, "table_dev and workspace must be 256-byte aligned");
+  if (!aligned(pixel_list, 4) || !aligned(mat_offsets, 4) || !aligned(uv, 8) || !aligned(out, 16))
+    return fail(NTC_E_ALIGN, "pixel_list, mat_offsets, uv or out misaligned");
+  const int64_t esz = t.out_f16 ? 2 : 4;
+  if (image_pixels < 1 || image_pixels >= ((int64_t)1 << 30) || image_pixels * t.n_out * esz >= ((int64_t)1 << 30) ||
+      image_pixels * 8 >= ((int64_t)1 << 30))
+    return fail(NTC_E_SHAPE, "image_pixels %lld outside 1..2^30 bytes of uv and output", (long long)image_pixels);
+  if (ws_bytes < t.plan.total_bytes)
+    return fail(NTC_E_WORKSPACE, "workspace needs %zu bytes, got %zu", (size_t)t.plan.total_bytes, ws_bytes);
+  hipError_t e = launch_frame_plan(t, (const uint8_t *)table_dev, pixel_list, mat_offsets, uv, out, image_pixels,
+                                   (uint8_t *)workspace, (hipStream_t)stream);
+  if (e != hipSuccess) return hip_fail(e, "frame plan launch");
+  e = launch_decode_batched((const uint8_t *)workspace, t.plan, (hipStream_t)stream);
+  if (e != hipSuccess) return hip_fail(e, "batched launch");
+  return ok();
+}
+
 }  // extern "C"

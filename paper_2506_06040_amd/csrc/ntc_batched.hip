@@ -122,14 +122,6 @@ int shape_id_of(int hid, int n_layers) {
   return 3 * hi + (n_layers - 2);
 }
 
-// Estimated cost of one 64-pixel tile: MFMA issue slots of the MLP plus a
-// fixed share for sampling and staging.
-static double tile_cost(int hid, int n_layers) {
-  const int mt = hid / 16, kc = hid >= 32 ? hid / 32 : 1;
-  const double mfma = 4.0 * (mt + (double)(n_layers - 2) * mt * kc + kc);
-  return mfma + 12.0;
-}
-
 size_t plan_bytes(int n_mats, int64_t n_items, int n_waves) {
   size_t off = (sizeof(BatchPlanHeader) + 255) / 256 * 256;
   off += (size_t)n_mats * sizeof(BatchMaterial);
@@ -161,7 +153,7 @@ void build_plan(const BatchMaterial *mats, int n_mats, int item_tiles, int n_wav
   std::vector<double> cost;
   for (int m = 0; m < n_mats; ++m) {
     const int64_t tiles = mats[m].a.n_tiles;
-    const double c = tile_cost(mats[m].hid, mats[m].n_layers);
+    const double c = tile_cost(mats[m].hid, mats[m].n_layers, 12.0);
     for (int64_t t = 0; t < tiles; t += item_tiles) {
       BatchItem it;
       it.mat = m;

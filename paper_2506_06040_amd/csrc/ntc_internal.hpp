@@ -170,6 +170,30 @@ struct BatchPlanHeader {
 constexpr uint32_t kPlanMagic = 0x4E544350u;  // "NTCP"
 constexpr uint32_t kPlanVersion = 1;
 
+// A frame's materials (ntc_frame.hip): the part of the plan that does not
+// depend on the frame, from which a kernel builds the plan of a classified
+// frame. Layout of the table: FrameTable, BatchMaterial [n_mats] (uv, out, n,
+// n_tiles, pix and img_px of the frame still to be filled in), uint32
+// order [n_mats] (index, shape and tile cost of the materials, by MLP shape).
+struct FrameTable {
+  BatchPlanHeader plan;  // header of the frame's plan
+  int32_t n_out, out_f16;
+  uint64_t mats_off, order_off, total_bytes;
+};
+constexpr uint32_t kFrameMagic = 0x4E544346u;  // "NTCF"
+size_t frame_table_bytes(int n_mats);
+void build_frame_table(const BatchMaterial *mats, int n_mats, int n_waves, int stage_cap, uint8_t *out, size_t bytes);
+// Sets t.plan.n_waves to the waves that the plan is for.
+hipError_t launch_frame_plan(FrameTable &t, const uint8_t *table_dev, const int32_t *list,
+                             const int32_t *mat_offsets, const float *uv, void *image, int64_t img_px,
+                             uint8_t *plan_dev, hipStream_t st);
+
+// Estimated cost of a 64-pixel tile: matrix issue slots of the MLP plus a
+// fixed share for sampling and staging.
+inline double tile_cost(int hid, int n_layers, double sampling) {
+  const int mt = hid / 16, kc = hid >= 32 ? hid / 32 : 1;
+  return 4.0 * (mt + (double)(n_layers - 2) * mt * kc + kc) + sampling;
+}
 hipError_t launch_decode_batched(const uint8_t *plan_dev, const BatchPlanHeader &h, hipStream_t st);
 int shape_id_of(int hid, int n_layers);
 size_t plan_bytes(int n_mats, int64_t n_items, int n_waves);

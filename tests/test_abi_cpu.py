@@ -243,3 +243,43 @@ def test_classify_noalloc_limits(A):
     assert L.ntc_classify_noalloc(0x1001, 64, 64, 3, 0x1000, 0x1000, 0x1000, 0, None) == A.E_ALIGN
     assert L.ntc_classify_noalloc(0x1000, 0, 64, 3, 0x1000, 0x1000, 0x1000, 0, None) == A.E_SHAPE
     assert L.ntc_classify_noalloc(0x1000, 64, 64, 0, 0x1000, 0x1000, 0x1000, 0, None) == A.E_SHAPE
+
+
+def test_frame_entries_reject(A):
+    """Checks of the frame table and ntc_decode_frame, on the host alone."""
+    L = A.lib()
+    n = ctypes.c_size_t(0)
+    assert L.ntc_frame_table_size(64, None) == A.E_NULL
+    assert L.ntc_frame_table_size(0, ctypes.byref(n)) == A.E_SHAPE
+    assert L.ntc_frame_table_size(4097, ctypes.byref(n)) == A.E_SHAPE
+    assert L.ntc_frame_table_size(2, ctypes.byref(n)) == A.OK
+    mats = (A.ntc_material * 2)()
+    for m in mats:
+        m.lat.n_levels, m.lat.format = 1, A.LATENT_BC1
+        m.lat.width[0] = m.lat.height[0] = 16
+        m.lat.data[0] = 0x1000
+        m.mlp.n_layers = 2
+        m.mlp.dims[0], m.mlp.dims[1], m.mlp.dims[2] = 5, 16, 4
+        m.packed = 0x1000
+    buf = (ctypes.c_uint8 * n.value)()
+    assert L.ntc_frame_table(None, 2, None, buf, n.value) == A.E_NULL
+    assert L.ntc_frame_table(mats, 2, None, None, n.value) == A.E_NULL
+    assert L.ntc_frame_table(mats, 2, None, buf, n.value - 1) == A.E_WORKSPACE
+    mats[1].mlp.dims[2] = 8  # outputs unlike those of the other material
+    assert L.ntc_frame_table(mats, 2, None, buf, n.value) == A.E_SHAPE
+    mats[1].mlp.dims[2] = 4
+    assert L.ntc_frame_table(mats, 2, None, buf, n.value) == A.OK
+    ws = ctypes.c_size_t(0)
+    assert L.ntc_decode_frame_workspace(buf, n.value - 1, ctypes.byref(ws)) == A.E_WORKSPACE
+    assert L.ntc_decode_frame_workspace(buf, n.value, ctypes.byref(ws)) == A.OK and ws.value > 0
+    p = 0x1000
+
+    def call(dev=p, lst=p, uv=p, out=p, px=64, work=p, size=ws.value):
+        return L.ntc_decode_frame(buf, dev, n.value, lst, p, uv, out, px, work, size, None)
+
+    assert call(dev=None) == A.E_NULL and call(lst=None) == A.E_NULL and call(work=None) == A.E_NULL
+    assert call(dev=p + 64) == A.E_ALIGN and call(uv=p + 4) == A.E_ALIGN and call(out=p + 8) == A.E_ALIGN
+    assert call(px=0) == A.E_SHAPE and call(px=1 << 27) == A.E_SHAPE and call(px=1 << 62) == A.E_SHAPE
+    assert call(size=ws.value - 1) == A.E_WORKSPACE
+    buf[0] ^= 1
+    assert call() == A.E_SHAPE  # not a frame table

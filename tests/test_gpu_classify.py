@@ -140,3 +140,66 @@ def test_batched_indexed_ignores_invalid_indices():
     assert np.array_equal(got[good], ref.cpu().numpy())
     untouched = np.setdiff1d(np.arange(h * w), good)
     assert np.all(got[untouched] == 7.0)
+
+
+# The plan built on the device against the one built on the host (a cfg of
+# one's own) and against gather, decode and scatter: every MLP shape, frames
+# with fewer tiles than waves, of one pixel, without neural pixels, with more
+# materials than pixels, FP16 outputs and pixels that keep their value.
+@pytest.mark.parametrize("w,h,n,noise,bg,dt", [
+    (256, 192, 9, 0.02, 0.15, torch.float32), (1024, 512, 40, 0.01, 0.1, torch.float16),
+    (1, 1, 1, 0.0, 0.0, torch.float32), (9, 5, 3, 1.0, 1.0, torch.float32), (37, 22, 300, 1.0, 0.2, torch.float32),
+    (640, 360, 2, 0.0, 0.0, torch.float32)])
+def test_frame_plan_on_device_equals_host_plan(w, h, n, noise, bg, dt):
+    ntc = _ntc()
+    rng = np.random.default_rng(w + n)
+    mat = I.material_frame(rng, w, h, n, noise=noise, background=bg)
+    mats = []
+    for m in range(n):
+        lat_np = I.bc1_pyramid(rng, [(32, 32), (16, 16), (8, 8), (4, 4)])
+        dims = (14,) + ((16, 32, 64)[m % 3],) * (1 + m // 3 % 3) + (8,)
+        mats.append((ntc.Latents(lat_np, shift=I.PAPER_SHIFT), ntc.Mlp(*I.xavier_mlp(rng, dims, bias="normal"))))
+    mat_t = torch.from_numpy(mat).cuda()
+    uv = torch.from_numpy(rng.random((h, w, 2)).astype(np.float32)).cuda()
+    dev = ntc.FrameDecoder(mats, out_dtype=dt)
+    host = ntc.FrameDecoder(mats, cfg=ntc.batch_cfg(item_pixels=128, n_cus=8), out_dtype=dt)
+
+    def image(fd, **kw):
+        return fd.decode(mat_t, uv, out=torch.full((h, w, 8), 7.0, dtype=dt, device="cuda"), **kw)
+
+    ref = image(host)
+    assert torch.equal(ref, image(dev, indexed=False))
+    assert torch.equal(ref, image(dev))
+    assert torch.equal(ref, image(dev))  # the table of the first frame
+    assert bool((ref.cpu().numpy()[mat >= n] == 7.0).all())
+    # other weights in the decoder's list of images
+    dev.packed[0] = ntc.pack(ntc.Mlp(*I.xavier_mlp(rng, [int(d) for d in mats[0][1].dims], bias="normal")), "f16")
+    host.packed[0] = dev.packed[0]
+    assert torch.equal(image(host), image(dev))
+    # other materials, on another stream
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        dev.materials.reverse(), dev.packed.reverse(), host.materials.reverse(), host.packed.reverse()
+        assert torch.equal(image(host), image(dev))
+    torch.cuda.current_stream().wait_stream(s)
+
+
+def test_frame_decode_rejects_as_before():
+    ntc = _ntc()
+    rng = np.random.default_rng(3)
+    lat = ntc.Latents(I.bc1_pyramid(rng, [(16, 16), (8, 8)]), shift=I.PAPER_SHIFT[:2])
+    deep = ntc.Mlp(*I.xavier_mlp(rng, (8, 16, 16, 16, 16, 4), bias="normal"))
+    fd = ntc.FrameDecoder([(lat, deep)])  # five layers: not in a batch
+    uv = torch.zeros((8, 8, 2), device="cuda")
+    with pytest.raises(ntc.NtcError):
+        fd.decode(torch.zeros((8, 8), dtype=torch.int16, device="cuda"), uv)
+    assert not fd.decode(torch.full((8, 8), 5, dtype=torch.int16, device="cuda"), uv).any()
+    fd = ntc.FrameDecoder([(lat, ntc.Mlp(*I.xavier_mlp(rng, (8, 16, 4), bias="normal")))])
+    with pytest.raises(ValueError):
+        fd.decode(torch.zeros((8, 8), dtype=torch.int32, device="cuda"), uv)
+    with pytest.raises(ValueError):
+        fd.decode(torch.zeros((8, 8), dtype=torch.int16, device="cuda"), uv.cpu())
+    with pytest.raises(ntc.NtcError):  # misaligned uv
+        fd.decode(torch.zeros((8, 8), dtype=torch.int16, device="cuda"),
+                  torch.zeros(129, device="cuda")[1:].reshape(8, 8, 2))
