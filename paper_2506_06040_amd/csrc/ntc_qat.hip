@@ -42,81 +42,108 @@ struct QatArgs {
 __device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + __expf(-x)); }
 
 // Code of logit x on M + 1 levels: the number of midpoint logits mid[0..M-1]
-// at or below x. A candidate from the FP32 sigmoid (within one level of the
-// answer: its error is far below 1 / (2M)) is corrected by the exact
-// comparisons. NaN gives 0.
+// at or below x. From two below a candidate of the FP32 sigmoid (within one
+// level of the answer: its error is far below 1 / (2M)) four exact
+// comparisons, whose midpoints load together. NaN gives 0.
 __device__ __forceinline__ int quant_code(float x, const float *mid, int M) {
   const float s = sigmoidf(x) * (float)M;
-  int c = s >= 0.0f ? (int)rintf(fminf(s, (float)M)) : 0;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-    if (c > 0 && !(x >= mid[c - 1])) --c;
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-    if (c < M && x >= mid[c]) ++c;
-  return c;
+  const int c = s >= 0.0f ? (int)rintf(fminf(s, (float)M)) : 0;
+  const int lo = min(max(c - 2, 0), M - 3);
+  int code = lo + (x >= mid[lo]) + (x >= mid[lo + 1]) + (x >= mid[lo + 2]);
+  if (lo + 3 < M) code += x >= mid[lo + 3];
+  return x == x ? code : 0;
 }
 
-// Endpoint codes of a block as red | blue << 8 | green << 16 (the field
-// order of the decoder's numerators).
-__device__ __forceinline__ uint32_t endpoint_codes(const float *p, const QatTables &t) {
-  const uint32_t r = (uint32_t)quant_code(p[0], t.mid5, 31);
-  const uint32_t g = (uint32_t)quant_code(p[1], t.mid6, 63);
-  const uint32_t b = (uint32_t)quant_code(p[2], t.mid5, 31);
-  return r | (b << 8) | (g << 16);
+// The same for the 2-bit weights, whose three midpoints are all compared.
+__device__ __forceinline__ int weight_code(float x, const QatTables &t) {
+  return (x >= t.mid2[0]) + (x >= t.mid2[1]) + (x >= t.mid2[2]);
 }
 
-// One thread per texel.
-__global__ __launch_bounds__(256) void qat_texels_kernel(QatArgs a) {
+// The texels and gradients kernels take a block in 16 lanes (a DPP row), one
+// texel each; lanes 0 to 5 also hold the endpoint logits. One thread per block
+// left the largest level of a 256 x 256 texture to 64 wavefronts, each a
+// chain of 22 codes of dependent loads (four levels of 256 to 32 texels,
+// gradients: 94 -> @B@ us, texels 26 -> @T@ us).
+struct BlockLane {
+  int64_t block;
+  int t;         // texel (t & 3, t >> 2)
+  int64_t texel; // its index in the level
+};
+
+__device__ __forceinline__ bool block_lane(const QatArgs &a, BlockLane &b) {
   const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= (int64_t)a.w * a.h) return;
-  const int i = (int)(id % a.w), j = (int)(id / a.w);
-  const float *p = a.params + ((int64_t)(j >> 2) * a.bw + (i >> 2)) * kQatParams;
-  const uint32_t e0 = endpoint_codes(p, a.t), e1 = endpoint_codes(p + 3, a.t);
-  const uint32_t w = (uint32_t)quant_code(p[6 + 4 * (j & 3) + (i & 3)], a.t.mid2, 3);
-  // numerators over 6 (2^b - 1), as the BC1 decoder forms them; one
-  // rounding of the exact quotient (a double quotient of these small
-  // integers is never a float32 rounding tie)
-  const uint32_t n = 2u * (3u - w) * e0 + 2u * w * e1;
-  float *o = a.texels + id * 3;
-  o[0] = (float)((double)(n & 255u) / 186.0);
-  o[1] = (float)((double)(n >> 16) / 378.0);
-  o[2] = (float)((double)((n >> 8) & 255u) / 186.0);
+  b.block = id >> 4;
+  b.t = (int)(id & 15);
+  if (b.block >= (int64_t)a.bw * a.bh) return false;
+  const int bx = (int)(b.block % a.bw), by = (int)(b.block / a.bw);
+  b.texel = (int64_t)(4 * by + (b.t >> 2)) * a.w + 4 * bx + (b.t & 3);
+  return true;
 }
 
-// One thread per block: gradients with the quantisation passed through,
+// Code of lane t's endpoint logit x (t < 6; other lanes: of the last one).
+__device__ __forceinline__ int endpoint_code(float x, int t, const QatTables &q) {
+  const bool green = t == 1 || t == 4;
+  return quant_code(x, green ? q.mid6 : q.mid5, green ? 63 : 31);
+}
+
+// Sum over the 16 lanes of a row, in every lane.
+__device__ __forceinline__ float row_sum(float v) {
+#define NTC_ROW_ADD(N) \
+  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xF, 0xF, false))  // row_ror:N
+  NTC_ROW_ADD(8);
+  NTC_ROW_ADD(4);
+  NTC_ROW_ADD(2);
+  NTC_ROW_ADD(1);
+#undef NTC_ROW_ADD
+  return v;
+}
+
+__global__ __launch_bounds__(256) void qat_texels_kernel(QatArgs a) {
+  BlockLane b;
+  if (!block_lane(a, b)) return;
+  const float *p = a.params + b.block * kQatParams;
+  const float xe = p[min(b.t, 5)], xw = p[6 + b.t];
+  const int ec = endpoint_code(xe, b.t, a.t);
+  const int w = weight_code(xw, a.t);
+  // numerators over 6 (2^b - 1), as the BC1 decoder forms them, and their
+  // quotient rounded once
+  float *o = a.texels + b.texel * 3;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const int e0 = __shfl(ec, c, 16), e1 = __shfl(ec, 3 + c, 16);
+    const int n = 2 * (3 - w) * e0 + 2 * w * e1;
+    o[c] = __fdiv_rn((float)n, c == 1 ? 378.0f : 186.0f);
+  }
+}
+
+// Gradients with the quantisation passed through,
 //   dL/dE0_c = sum_t (1 - w_t/3) g_tc, dL/dE1_c = sum_t (w_t/3) g_tc,
 //   dL/dw_t = sum_c (E1_c - E0_c) g_tc  (values E, w/3 in [0, 1]),
 // each times the sigmoid's derivative at its logit.
 __global__ __launch_bounds__(256) void qat_backward_kernel(QatArgs a) {
-  const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (id >= (int64_t)a.bw * a.bh) return;
-  const int bx = (int)(id % a.bw), by = (int)(id / a.bw);
-  const float *p = a.params + id * kQatParams;
-  float *gp = a.texels + id * kQatParams;
-  const uint32_t e0 = endpoint_codes(p, a.t), e1 = endpoint_codes(p + 3, a.t);
-  const float ev0[3] = {numer_r(e0) * (1.0f / 31.0f), numer_g(e0) * (1.0f / 63.0f), numer_b(e0) * (1.0f / 31.0f)};
-  const float ev1[3] = {numer_r(e1) * (1.0f / 31.0f), numer_g(e1) * (1.0f / 63.0f), numer_b(e1) * (1.0f / 31.0f)};
-  float g0[3] = {0.f, 0.f, 0.f}, g1[3] = {0.f, 0.f, 0.f};
-  for (int t = 0; t < 16; ++t) {
-    const int i = 4 * bx + (t & 3), j = 4 * by + (t >> 2);
-    const float *g = a.grad + ((int64_t)j * a.w + i) * 3;
-    const float wv = (float)quant_code(p[6 + t], a.t.mid2, 3) * (1.0f / 3.0f);
-    float ga = 0.f;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      g0[c] = fmaf(1.0f - wv, g[c], g0[c]);
-      g1[c] = fmaf(wv, g[c], g1[c]);
-      ga = fmaf(ev1[c] - ev0[c], g[c], ga);
-    }
-    const float s = sigmoidf(p[6 + t]);
-    gp[6 + t] = s * (1.0f - s) * ga;
-  }
+  BlockLane b;
+  if (!block_lane(a, b)) return;
+  const float *p = a.params + b.block * kQatParams;
+  float *gp = a.texels + b.block * kQatParams;
+  const float *g = a.grad + b.texel * 3;
+  const float xe = p[min(b.t, 5)], xw = p[6 + b.t];
+  const float gt[3] = {g[0], g[1], g[2]};
+  const bool green = b.t == 1 || b.t == 4;
+  const float ev = (float)endpoint_code(xe, b.t, a.t) * (green ? 1.0f / 63.0f : 1.0f / 31.0f);
+  const float wv = (float)weight_code(xw, a.t) * (1.0f / 3.0f);
+  float ga = 0.f, ge = 0.f;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    const float s0 = sigmoidf(p[c]), s1 = sigmoidf(p[3 + c]);
-    gp[c] = s0 * (1.0f - s0) * g0[c];
-    gp[3 + c] = s1 * (1.0f - s1) * g1[c];
+    const float d = __shfl(ev, 3 + c, 16) - __shfl(ev, c, 16);
+    ga = fmaf(d, gt[c], ga);
+    const float g0 = row_sum((1.0f - wv) * gt[c]), g1 = row_sum(wv * gt[c]);
+    ge = b.t == c ? g0 : (b.t == 3 + c ? g1 : ge);
+  }
+  const float sw = sigmoidf(xw);
+  gp[6 + b.t] = sw * (1.0f - sw) * ga;
+  if (b.t < 6) {
+    const float se = sigmoidf(xe);
+    gp[b.t] = se * (1.0f - se) * ge;
   }
 }
 
@@ -141,7 +168,7 @@ __global__ __launch_bounds__(256) void qat_export_kernel(QatArgs a) {
   uint32_t idx = 0;
   if (c[0] != c[1]) {
     for (int t = 0; t < 16; ++t) {
-      uint32_t w = (uint32_t)quant_code(p[6 + t], a.t.mid2, 3);
+      uint32_t w = (uint32_t)weight_code(p[6 + t], a.t);
       if (swap) w = 3u - w;
       idx |= ((0x78u >> (2u * w)) & 3u) << (2u * t);  // {0, 2, 3, 1}[w]
     }
@@ -183,7 +210,7 @@ QatTables qat_tables() {
 hipError_t launch_qat_texels(const float *params, int w, int h, float *texels, hipStream_t st) {
   QatArgs a = qat_args(params, w, h);
   a.texels = texels;
-  const int64_t n = (int64_t)w * h;
+  const int64_t n = (int64_t)w * h;  // 16 lanes a block
   hipLaunchKernelGGL(qat_texels_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
@@ -193,7 +220,7 @@ hipError_t launch_qat_backward(const float *params, int w, int h, const float *g
   QatArgs a = qat_args(params, w, h);
   a.grad = grad_texels;
   a.texels = grad_params;
-  const int64_t n = (int64_t)a.bw * a.bh;
+  const int64_t n = (int64_t)w * h;
   hipLaunchKernelGGL(qat_backward_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
   return hipGetLastError();
 }

@@ -67,6 +67,32 @@ def test_qat_backward_parity():
         assert err <= 1e-5 * scale, name
 
 
+# One block, blocks that do not fill a wavefront or a workgroup, a level one
+# block wide or high. FP32 sums of 16 terms against FP64: at most 16 roundings
+# of 2^-24 of the terms' magnitudes, below 1e-5 of the largest gradient. A NaN
+# logit has code 0, an infinite one the end of its range.
+@pytest.mark.parametrize("w,h", [(4, 4), (36, 20), (4, 132), (132, 4), (72, 68)])
+def test_qat_row_shapes(w, h):
+    ntc = _ntc()
+    rng = np.random.default_rng(w * 1000 + h + 7)
+    p = _params(rng, h // 4, w // 4)
+    g = rng.standard_normal((h, w, 3)).astype(np.float32)
+    got = ntc.qat_backward(torch.from_numpy(p).cuda(), w, h, torch.from_numpy(g).cuda()).cpu().numpy()
+    ref = Q.backward(p, g)
+    for sl in (slice(0, 6), slice(6, 22)):
+        assert np.max(np.abs(got[..., sl] - ref[..., sl])) <= 1e-5 * np.max(np.abs(ref[..., sl]))
+    tex = ntc.qat_texels(torch.from_numpy(p).cuda(), w, h).cpu().numpy()
+    assert np.array_equal(tex, Q.texels(p)[2].astype(np.float32))
+    odd = p.copy()
+    odd[..., ::3] = np.where(rng.random(odd[..., ::3].shape) < 0.5, np.inf, np.nan).astype(np.float32)
+    odd[..., 1::5] = -np.inf
+    low = np.where(np.isnan(odd), np.float32(-100.0), np.clip(odd, -100.0, 100.0)).astype(np.float32)
+    assert torch.equal(ntc.qat_texels(torch.from_numpy(odd).cuda(), w, h),
+                       ntc.qat_texels(torch.from_numpy(low).cuda(), w, h))
+    assert torch.equal(ntc.qat_export_bc1(torch.from_numpy(odd).cuda(), w, h),
+                       ntc.qat_export_bc1(torch.from_numpy(low).cuda(), w, h))
+
+
 def test_qat_training_chain():
     """params -> quantised texels -> FP32 decode -> loss -> gradients into the
     logits (autograd through QatTexelsFn and NtcDecodeFn) against the oracle:
