@@ -29,13 +29,6 @@ namespace {
 
 constexpr int kFiltStageTexels = 2048;  // LDS texels (8 bytes each) per wavefront
 constexpr int kRegions = 2 * kMaxLevels;
-#ifndef NTC_FILT_TRI_SUBS  // 64-pixel sub-spans per staged span of the trilinear decode
-#define NTC_FILT_TRI_SUBS 16
-#endif
-#ifndef NTC_FILT_ANI_SUBS  // and of the anisotropic decode
-#define NTC_FILT_ANI_SUBS 4
-#endif
-
 // Mip m of level k as a sampling table entry (clamp to edge).
 __device__ __forceinline__ TabLevel mip_level(const FilterArgs &f, int k, int m) {
   const MipArgs &M = f.mip[k][m];
@@ -185,19 +178,62 @@ __device__ __forceinline__ float3 filter_level(const LodSel &s, float u, float v
   return make_float3(acc.x * inv, acc.y * inv, acc.z * inv);
 }
 
+// Filtered features of one level whose samples all come from staged texels
+// (anisotropic): lo(x, y) and, with HI, hi(x, y) are the samples of mips m0 and
+// m0 + 1. The taps go two at a time, so that one's LDS reads are in flight
+// during the other's arithmetic; the sums are those of filter_level, tap by
+// tap (a blend by t = 0 is the first sample itself: texels are finite).
+template <bool HI, class LO, class HIS>
+__device__ __forceinline__ float3 filter_level_staged(const LodSel &s, float u, float v, LO &&lo, HIS &&hi) {
+  float3 acc = make_float3(0.f, 0.f, 0.f);
+  auto tap = [&](int i, Tex16 &a, Tex16 &b) {
+    const float t = aniso_offset(i, s.inv);
+    const float x = fmaf(t, s.du, u), y = fmaf(t, s.dv, v);
+    a = lo(x, y);
+    if (HI) b = hi(x, y);
+  };
+  auto add = [&](const Tex16 &a, const Tex16 &b) {
+    float3 c = tex_f3(a);
+    if (HI) {
+      const float3 c1 = tex_f3(b);
+      c.x = fmaf(s.t, c1.x - c.x, c.x);
+      c.y = fmaf(s.t, c1.y - c.y, c.y);
+      c.z = fmaf(s.t, c1.z - c.z, c.z);
+    }
+    acc.x += c.x;
+    acc.y += c.y;
+    acc.z += c.z;
+  };
+  int i = 1;
+  Tex16 a0, b0, a1, b1;
+  for (; i < s.n; i += 2) {
+    tap(i, a0, b0);
+    tap(i + 1, a1, b1);
+    add(a0, b0);
+    add(a1, b1);
+  }
+  if (i <= s.n) {
+    tap(i, a0, b0);
+    add(a0, b0);
+  }
+  const float inv = 1.0f / (float)s.n;
+  return make_float3(acc.x * inv, acc.y * inv, acc.z * inv);
+}
+
 // Trilinear features of one level in packed FP16: the sample of mip m0,
 // blended towards the sample of mip m0 + 1 by t (a subtraction and a fused
 // multiply-add per channel pair; the constant 1 of the (b, 1) pair stays 1).
+__device__ __forceinline__ Tex16 blend16(Tex16 c, Tex16 c1, float t) {
+  const _Float16 th = (_Float16)t;
+  const half2_t t2 = {th, th};
+  c.rg = __builtin_elementwise_fma(t2, c1.rg - c.rg, c.rg);
+  c.b1 = __builtin_elementwise_fma(t2, c1.b1 - c.b1, c.b1);
+  return c;
+}
 template <class SMP>
 __device__ __forceinline__ Tex16 trilinear16(const LodSel &s, float u, float v, SMP &&smp) {
   Tex16 c = smp(s.m0, u, v);
-  if (s.t > 0.0f) {
-    const Tex16 c1 = smp(s.m0 + 1, u, v);
-    const _Float16 th = (_Float16)s.t;
-    const half2_t t2 = {th, th};
-    c.rg = __builtin_elementwise_fma(t2, c1.rg - c.rg, c.rg);
-    c.b1 = __builtin_elementwise_fma(t2, c1.b1 - c.b1, c.b1);
-  }
+  if (s.t > 0.0f) c = blend16(c, smp(s.m0 + 1, u, v), s.t);
   return c;
 }
 
@@ -373,9 +409,8 @@ __device__ __forceinline__ Tex16 staged_sample(const uint2 *stage, float fw, flo
 // A span is SUBS sub-spans of 64 consecutive pixels: the footprints of all
 // its pixels are staged once, then each sub-span is sampled and run through
 // the MLP. Long spans spread the footprint reductions, the staging records
-// and the partly filled staging passes over more pixels; trilinear spans
-// take 1024 pixels, anisotropic ones (footprints stretched along the major
-// axis) 256.
+// and the partly filled staging passes over more pixels; short ones keep the
+// waves busy (span_subs).
 template <class P, int HID, int NL, int VEC4, int FILTER, int SUBS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PER_SIMD, NTC_WAVES_PER_SIMD))) void decode_filtered_kernel(FilterArgs f) {
   extern __shared__ f32x4 smem[];
@@ -413,14 +448,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
     uv_next = a.uv[p];
     d_next = f.duv[p];
   }
-  for (int64_t s = blockIdx.x; s < n_span; s += gridDim.x) {
+  // Spans are dealt to the waves back and forth (pass by pass of the grid, the
+  // odd passes in reverse): the tap counts of a picture change steadily over
+  // its rows, and waves that all walk in one direction differ by the change
+  // over a whole pass each time (1920 x 1080, 16
+  // taps, 256-pixel spans: 326 -> 303 us).
+  const int64_t grid = gridDim.x;
+  auto span_of = [&](int64_t pass) {
+    return pass * grid + ((pass & 1) ? grid - 1 - (int64_t)blockIdx.x : (int64_t)blockIdx.x);
+  };
+  int64_t s = blockIdx.x;
+  for (int64_t pass = 0; s < n_span; s = span_of(++pass)) {
     float2 uv[SUBS];
     float4 d[SUBS];
     if constexpr (SUBS == 1) {
       uv[0] = uv_next;
       d[0] = d_next;
-      if (s + gridDim.x < n_span) {
-        const int64_t p = pixel_of(s + gridDim.x, 0);
+      if (span_of(pass + 1) < n_span) {
+        const int64_t p = pixel_of(span_of(pass + 1), 0);
         uv_next = a.uv[p];
         d_next = f.duv[p];
       }
@@ -569,22 +614,31 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
             }
             return sample_direct16<kEitherMode>(mip_level(f, k, m), tap_coord(x), tap_coord(y), 0);
           };
-          // every lane reads mip m_lo alone (blend weight 0) and it is
-          // staged: the samples take the region's values as wave-uniform
-          // parameters (the same values as smp gives them)
-          const bool lo_only = s0 && __builtin_amdgcn_ballot_w64(sel[k].m0 != mlo || sel[k].t > 0.0f) == 0;
-          auto smp_lo = [&](int, float x, float y) -> Tex16 {
-            return staged_sample(stage, fw0, fh0, cx, cy, kbw0, kb0, x, y, in0);
+          // every lane reads mip m_lo (alone, or blended with m_lo + 1), those
+          // are staged and every position is an interior one: the samples
+          // take the regions' values as wave-uniform parameters (the same
+          // values as smp gives them)
+          const bool at_lo = s0 && in0 && __builtin_amdgcn_ballot_w64(sel[k].m0 != mlo) == 0;
+          const bool lo_only = at_lo && __builtin_amdgcn_ballot_w64(sel[k].t > 0.0f) == 0;
+          const bool pair = at_lo && s1 && in1;
+          auto smp_lo = [&](float x, float y) -> Tex16 {
+            return staged_sample(stage, fw0, fh0, cx, cy, kbw0, kb0, x, y, true);
+          };
+          auto smp_hi = [&](float x, float y) -> Tex16 {
+            return staged_sample(stage, fw1, fh1, cx, cy, kbw1, kb1, x, y, true);
           };
           if constexpr (FILTER == 1) {
             if (lo_only)
-              c16[k] = smp_lo(mlo, u, v);
+              c16[k] = smp_lo(u, v);
+            else if (pair)
+              c16[k] = blend16(smp_lo(u, v), smp_hi(u, v), sel[k].t);
             else
               c16[k] = trilinear16(sel[k], u, v, smp);
           } else {
             if (lo_only)
-              c = filter_level<FILTER>(sel[k], u, v,
-                                       [&](int m, float x, float y) { return tex_f3(smp_lo(m, x, y)); });
+              c = filter_level_staged<false>(sel[k], u, v, smp_lo, smp_hi);
+            else if (pair)
+              c = filter_level_staged<true>(sel[k], u, v, smp_lo, smp_hi);
             else
               c = filter_level<FILTER>(sel[k], u, v, [&](int m, float x, float y) { return tex_f3(smp(m, x, y)); });
           }
@@ -612,9 +666,32 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
   }
 }
 
-template <int HID, int VEC4, int FILTER>
+// 64-pixel sub-spans per span. A longer span shares one staging over more
+// pixels, but its waves end further apart, the more so the more taps a pixel
+// may take: the largest span is taken that leaves every wave enough of them.
+// Measured (us; passes: spans of 64 pixels / waves; spans of 16, 4, 1 or 4, 2,
+// 1 sub-spans):
+//   trilinear 4096 x 4096 (128 passes) 447, 494, 674; 3000 x 2200 (50) 161,
+//   154, 228; 2000 x 1500 (23) 128, 109, 133; 1000 x 800 (6) 113, 49, 46;
+//   300 x 200 (0.5) 91, 24, 13;
+//   2 or 4 taps 2500 x 2000 (38) 241, 262, 278; 2000 x 1500 (23) 139, 153, 164;
+//   1000 x 1000 (8) 82, 69, 70; 1000 x 700 (5) 43, 40, 44;
+//   8 or 16 taps 2500 x 2000 (38) 258, 267, 285; 2000 x 1500 (23, footprints
+//   up to 16 : 1) 346, 261, 245; 1920 x 1080 (16) 303, 197, 162; 1500 x 1500
+//   (17, few taps) 116, 107, 117; 300 x 200 (0.5) 135, 72, 40.
+// (With spans of 16 and 4 sub-spans for all of them: 466, 194, 169, 111, 89;
+// 263, 151, 82, 45; 275, 383, 338, 121, 136.)
+int span_subs(const FilterArgs &f, int waves) {
+  const int64_t n64 = (f.d.n + 63) / 64;
+  if (f.filter == 1) return n64 >= (int64_t)16 * 6 * waves ? 16 : (n64 >= (int64_t)4 * 2 * waves ? 4 : 1);
+  if (f.max_aniso <= 4) return n64 >= (int64_t)10 * waves ? 4 : (n64 >= (int64_t)5 * waves ? 2 : 1);
+  return n64 >= (int64_t)4 * 8 * waves ? 4 : (n64 >= (int64_t)2 * 8 * waves ? 2 : 1);
+}
+
+template <int HID, int VEC4, int FILTER, int S>
 hipError_t launch_nl(const FilterArgs &f, int n_layers, int grid, hipStream_t st) {
-  constexpr int S = FILTER == 1 ? NTC_FILT_TRI_SUBS : NTC_FILT_ANI_SUBS;
+  const int64_t n_span = (f.d.n + 64 * S - 1) / (64 * S);
+  if (grid > n_span) grid = (int)n_span;
   const size_t lds = (size_t)(BiasLds<HID, 5>::kCount + 2 * kRegions) * sizeof(f32x4) + kFiltStageTexels * sizeof(uint2);
   switch (n_layers) {
     case 2: hipLaunchKernelGGL((decode_filtered_kernel<PrecF16, HID, 2, VEC4, FILTER, S>), dim3(grid), dim3(64), lds, st, f); break;
@@ -627,7 +704,15 @@ hipError_t launch_nl(const FilterArgs &f, int n_layers, int grid, hipStream_t st
 
 template <int HID, int VEC4>
 hipError_t launch_filter(const FilterArgs &f, int n_layers, int grid, hipStream_t st) {
-  return f.filter == 1 ? launch_nl<HID, VEC4, 1>(f, n_layers, grid, st) : launch_nl<HID, VEC4, 2>(f, n_layers, grid, st);
+  const int subs = span_subs(f, grid);
+  if (f.filter == 1) {
+    if (subs == 16) return launch_nl<HID, VEC4, 1, 16>(f, n_layers, grid, st);
+    if (subs == 4) return launch_nl<HID, VEC4, 1, 4>(f, n_layers, grid, st);
+    return launch_nl<HID, VEC4, 1, 1>(f, n_layers, grid, st);
+  }
+  if (subs == 4) return launch_nl<HID, VEC4, 2, 4>(f, n_layers, grid, st);
+  if (subs == 2) return launch_nl<HID, VEC4, 2, 2>(f, n_layers, grid, st);
+  return launch_nl<HID, VEC4, 2, 1>(f, n_layers, grid, st);
 }
 
 template <int HID>
@@ -642,15 +727,11 @@ hipError_t launch_vec(const FilterArgs &f, int n_layers, int grid, hipStream_t s
 }  // namespace
 
 hipError_t launch_decode_filtered(const FilterArgs &f, const MlpShape &s, int grid_waves, hipStream_t st) {
-  int64_t grid = grid_waves;
-  const int64_t span_px = 64 * (f.filter == 1 ? NTC_FILT_TRI_SUBS : NTC_FILT_ANI_SUBS);
-  const int64_t n_span = (f.d.n + span_px - 1) / span_px;
-  if (grid > n_span) grid = n_span;
-  if (grid < 1) grid = 1;
+  const int grid = grid_waves < 1 ? 1 : grid_waves;
   switch (s.hid) {
-    case 16: return launch_vec<16>(f, s.n_layers, (int)grid, st);
-    case 32: return launch_vec<32>(f, s.n_layers, (int)grid, st);
-    case 64: return launch_vec<64>(f, s.n_layers, (int)grid, st);
+    case 16: return launch_vec<16>(f, s.n_layers, grid, st);
+    case 32: return launch_vec<32>(f, s.n_layers, grid, st);
+    case 64: return launch_vec<64>(f, s.n_layers, grid, st);
     default: return hipErrorInvalidValue;
   }
 }

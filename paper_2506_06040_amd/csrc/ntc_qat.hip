@@ -61,9 +61,9 @@ __device__ __forceinline__ int weight_code(float x, const QatTables &t) {
 
 // The texels and gradients kernels take a block in 16 lanes (a DPP row), one
 // texel each; lanes 0 to 5 also hold the endpoint logits. One thread per block
-// left the largest level of a 256 x 256 texture to 64 wavefronts, each a
-// chain of 22 codes of dependent loads (four levels of 256 to 32 texels,
-// gradients: 94 -> @B@ us, texels 26 -> @T@ us).
+// left a level of 512 x 512 texels to 256 wavefronts, each a chain of 22 codes
+// of dependent loads: 24 us at 512 x 512 and at 1024 x 1024 alike (four levels
+// up to 1024 x 1024: gradients 98 -> 22 us, texels 36 -> 21 us).
 struct BlockLane {
   int64_t block;
   int t;         // texel (t & 3, t >> 2)

@@ -239,3 +239,38 @@ def test_output_widths(n_out):
         err = np.abs(out - ref)[keep].max()
         assert (~keep).sum() <= 1e-3 * uv.shape[0]
         assert err <= TOL_F16_ABS, (filt, n_out, err)
+
+
+# Every span length of the launch (by the pixel count and the tap limit): a
+# pixel's result depends on neither the span nor the pass it falls into, so a
+# long batch equals short ones bit for bit, at the first and last spans too.
+@pytest.mark.parametrize("filter,aniso,passes", [("trilinear", 1, 97.3), ("trilinear", 1, 9.1), ("anisotropic", 4, 11.2),
+                                                 ("anisotropic", 4, 6.3), ("anisotropic", 16, 33.1),
+                                                 ("anisotropic", 16, 17.2)])
+def test_filtered_span_lengths(filter, aniso, passes):
+    ntc = _ntc()
+    rng = np.random.default_rng(int(passes * 10))
+    waves = 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    n = int(passes * 64 * waves) + 37
+    chains = []
+    for side in (128, 64):
+        chains.append([I.bc1_pyramid(rng, [(side >> m, side >> m)])[0] for m in range(4)])
+    lat = ntc.LatentMips(chains, shift=I.PAPER_SHIFT[:2])
+    mlp = ntc.Mlp(*I.xavier_mlp(rng, (8, 16, 4), bias="normal"))
+    packed = ntc.pack(mlp, "f16")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    i = torch.arange(n, device="cuda")
+    uv = torch.stack([(i % 4099) / 4099.0, i / n], 1).float().contiguous()
+    # from magnified to beyond the last mip, footprints of up to 30 : 1
+    s = torch.exp2(-9.0 * (i / n))[:, None]
+    duv = (torch.randn((n, 4), generator=g, device="cuda") * s * torch.tensor([1.0, 0.05, 0.1, 0.4], device="cuda"))
+    duv = (duv * 0.2).float().contiguous()
+
+    def run(a, b):
+        return ntc.decode_filtered(lat, mlp, uv[a:b].contiguous(), duv[a:b].contiguous(), filter=filter,
+                                   max_aniso=aniso, packed=packed)
+
+    whole = run(0, n)
+    for a in (0, 1000, n // 3, n // 2 + 5, n - 30000):
+        assert torch.equal(whole[a:a + 30000], run(a, a + 30000)), a
