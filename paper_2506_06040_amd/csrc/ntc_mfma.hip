@@ -110,9 +110,20 @@ int decode_span_tiles(int hid, int n_layers, int compute) {
 hipError_t launch_decode_mfma(const DecodeArgs &a, const MlpShape &s, int compute, int grid_waves, hipStream_t st) {
   int64_t grid = grid_waves;
   const int span = a.lat.address == 0 ? decode_span_tiles(s.hid, s.n_layers, compute) : kWrapTiles;
+  // Spans of one tile while the batch is short (us, one tile / span of 4 or 8,
+  // FP16; widths of whole spans, else wrapped rows):
+  //   14-64-64-64-8, spans of 4: 65536 pixels 8 / 13 to 15, 2^18 (two tiles a
+  //   wave) 12 / 13, 5 2^16 14 / 13 and 15 to 22, 2^19 18 / 14 and 20 to 23;
+  //   14-32-32-8, spans of 8: 65536 7 / 19, 2^18 10 / 21, 3 2^17 15 / 21,
+  //   2^19 18 / 16 and 21, 2^20 24 / 16.
+  const int short_tiles = span == 8 ? 3 : 2;  // a wave
+  if (a.lat.address == 0 && a.n_tiles <= short_tiles * grid)
+    return launch_decode_short(a, s, compute, (int)(a.n_tiles < grid ? a.n_tiles : grid), st);
   const int64_t n_iter = (a.n_tiles + span - 1) / span;
-  if (grid > n_iter) grid = n_iter;
-  if (grid >= 8) grid &= ~(int64_t)7;
+  // a multiple of 8 for the XCD numbering: rounded up where the spans are
+  // fewer than the waves (down, the spans left over would take a second pass)
+  if (grid > n_iter) grid = n_iter < 8 ? n_iter : (n_iter + 7) & ~(int64_t)7;
+  else if (grid >= 8) grid &= ~(int64_t)7;
   if (grid < 1) grid = 1;
   if (compute == 1) return launch_mfma_prec<PrecF16>(a, s, (int)grid, st);
   if (compute == 2) return launch_mfma_prec<PrecBF16>(a, s, (int)grid, st);

@@ -1,0 +1,84 @@
+// Short batches of the matrix-core decode: the same walk as ntc_mfma.hip with
+// spans of one 64-pixel tile.
+//
+// A batch of fewer spans of 256 or 512 pixels than the card has wavefronts to
+// run leaves SIMDs idle, and its time is that of one wavefront working through
+// one span, tile after tile (300 to 65536 pixels, FP16 14-64-64-64-8: 14.5 -> 8
+// us in a stream of launches; 14-32-32-8 19 -> 7.5).
+#include <hip/hip_runtime.h>
+
+#include "ntc_device.hpp"
+#include "ntc_internal.hpp"
+#include "ntc_mfma_tile.hpp"
+
+namespace ntc {
+
+template <class P, int HID, int NL, int VEC4>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PER_SIMD, NTC_WAVES_PER_SIMD))) void decode_short_kernel(DecodeArgs a) {
+  extern __shared__ f32x4 smem[];
+  f32x4 *stage = smem;
+  f32x4 *bias = smem + a.stage_cap;
+  f32x4 *ltab = bias + BiasLds<HID, NL>::kCount;
+  // output staging for widths that are not a multiple of 4 (32 x 16 floats)
+  float *obuf = VEC4 ? nullptr : reinterpret_cast<float *>(ltab + LevelTab::kCount);
+  const int lane = threadIdx.x;
+
+  MfmaWeights<P, HID, NL> W;
+  W.load(a.packed, a.lay, lane);
+  BiasLds<HID, NL>::fill(bias, a.packed, a.lay, lane);
+  LevelTab::fill(ltab, a.lat, lane);
+  W.ready();
+  __syncthreads();
+
+  SpanUv<1> uvs;
+  uvs.load(a.uv, (int64_t)blockIdx.x * 64, a.n);
+  uvs.ready();
+  for (int64_t it = blockIdx.x; it < a.n_tiles; it += gridDim.x) {
+    const int64_t nx = it + gridDim.x;
+    decode_span<P, HID, NL, 1, VEC4, false, kClampOnly>(a, it * 64, a.n, stage, bias, ltab, W, uvs,
+                                                        nx < a.n_tiles ? nx * 64 : -1, a.n, obuf);
+  }
+}
+
+template <class P, int HID, int VEC4>
+static hipError_t launch_short_v(const DecodeArgs &a, int n_layers, int grid, hipStream_t st) {
+  const size_t lds =
+      (size_t)(a.stage_cap + BiasLds<HID, 5>::kCount + LevelTab::kCount + (VEC4 ? 0 : 32 * 16 / 4)) * sizeof(f32x4);
+  switch (n_layers) {
+    case 2: hipLaunchKernelGGL((decode_short_kernel<P, HID, 2, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
+    case 3: hipLaunchKernelGGL((decode_short_kernel<P, HID, 3, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
+    case 4: hipLaunchKernelGGL((decode_short_kernel<P, HID, 4, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
+    case 5: hipLaunchKernelGGL((decode_short_kernel<P, HID, 5, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+template <class P, int HID>
+static hipError_t launch_short_hid(const DecodeArgs &a, int n_layers, int grid, hipStream_t st) {
+  switch (out_class(a.n_out)) {
+    case kOut4: return launch_short_v<P, HID, kOut4>(a, n_layers, grid, st);
+    case kOut4x2: return launch_short_v<P, HID, kOut4x2>(a, n_layers, grid, st);
+    default: return launch_short_v<P, HID, kOutAny>(a, n_layers, grid, st);
+  }
+}
+
+template <class P>
+static hipError_t launch_short_prec(const DecodeArgs &a, const MlpShape &s, int grid, hipStream_t st) {
+  switch (s.hid) {
+    case 16: return launch_short_hid<P, 16>(a, s.n_layers, grid, st);
+    case 32: return launch_short_hid<P, 32>(a, s.n_layers, grid, st);
+    case 64: return launch_short_hid<P, 64>(a, s.n_layers, grid, st);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// Clamp addressing; 1 <= grid <= a.n_tiles.
+hipError_t launch_decode_short(const DecodeArgs &a, const MlpShape &s, int compute, int grid, hipStream_t st) {
+  if (compute == 1) return launch_short_prec<PrecF16>(a, s, grid, st);
+  if (compute == 2) return launch_short_prec<PrecBF16>(a, s, grid, st);
+  if (compute == 3) return launch_short_prec<PrecF8>(a, s, grid, st);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace ntc
