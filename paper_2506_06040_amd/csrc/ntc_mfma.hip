@@ -110,15 +110,21 @@ int decode_span_tiles(int hid, int n_layers, int compute) {
 hipError_t launch_decode_mfma(const DecodeArgs &a, const MlpShape &s, int compute, int grid_waves, hipStream_t st) {
   int64_t grid = grid_waves;
   const int span = a.lat.address == 0 ? decode_span_tiles(s.hid, s.n_layers, compute) : kWrapTiles;
-  // Spans of one tile while the batch is short (us, one tile / span of 4 or 8,
-  // FP16; widths of whole spans, else wrapped rows):
-  //   14-64-64-64-8, spans of 4: 65536 pixels 8 / 13 to 15, 2^18 (two tiles a
-  //   wave) 12 / 13, 5 2^16 14 / 13 and 15 to 22, 2^19 18 / 14 and 20 to 23;
-  //   14-32-32-8, spans of 8: 65536 7 / 19, 2^18 10 / 21, 3 2^17 15 / 21,
-  //   2^19 18 / 16 and 21, 2^20 24 / 16.
-  const int short_tiles = span == 8 ? 3 : 2;  // a wave
-  if (a.lat.address == 0 && a.n_tiles <= short_tiles * grid)
-    return launch_decode_short(a, s, compute, (int)(a.n_tiles < grid ? a.n_tiles : grid), st);
+  // Spans of one tile where long ones would leave more than half of the first
+  // or of the second pass of the waves empty. Measured (us, one tile / spans
+  // of 4 or 8; FP16, pixels in rows of whole spans, and in odd rows, whose
+  // wrapped spans seldom fit the staging region); tiles a wave:
+  //   14-64-64-64-8, spans of 4: 1/2 8 / 13 to 15, 2 12 / 13, 2 1/2 14 / 13
+  //   and 15 to 22, 4 18 / 14 and 20 to 23, 5 24 / 28 and 29 / 34, 6 26 / 26
+  //   and 27 / 40, 7 29 / 27 and 29 / 38, 10 38 / 37;
+  //   14-32-32-8, spans of 8: 1/2 7 / 19, 2 10 / 21, 3 15 / 21, 5 16 / 16 and
+  //   22 / 31, 6 19 / 16 and 21 / 31, 8 24 / 16, 9 26 / 27 and 29 / 56,
+  //   10 29 / 42, 11.4 35 / 42 (odd).
+  if (a.lat.address == 0) {
+    const int64_t pass = span * grid, rest = a.n_tiles % pass;
+    if (a.n_tiles < 2 * pass && rest > 0 && 2 * rest <= pass)
+      return launch_decode_short(a, s, compute, (int)(a.n_tiles < grid ? a.n_tiles : grid), st);
+  }
   const int64_t n_iter = (a.n_tiles + span - 1) / span;
   // a multiple of 8 for the XCD numbering: rounded up where the spans are
   // fewer than the waves (down, the spans left over would take a second pass)

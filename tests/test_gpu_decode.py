@@ -651,9 +651,9 @@ def test_wrap_staged_equals_direct(compute, sizes, scale, offset):
         assert np.max(np.abs(a[fin] - ref)) <= (TOL_F16_ABS if compute == "f16" else 1e-5)
 
 
-# Batches on both sides of the change from spans of one tile to long ones
-# (two tiles a wave with spans of four tiles, three with spans of eight), and
-# of the waves: a pixel does not depend on its span, so pieces equal the whole.
+# Batches with spans of one tile (less than half of a first or second pass of
+# the waves with long ones) and with long spans: a pixel does not depend on
+# its span, so pieces equal the whole.
 @pytest.mark.parametrize("compute", ["f16", "bf16", "fp8"])
 @pytest.mark.parametrize("dims", [(14, 64, 64, 64, 8), (14, 32, 32, 5), (14, 16, 9)])
 def test_short_batches_equal_long(compute, dims):
@@ -661,7 +661,7 @@ def test_short_batches_equal_long(compute, dims):
     rng = np.random.default_rng(len(dims) + dims[-1])
     lat = ntc.Latents(I.bc1_pyramid(rng, [(64, 64), (32, 32), (16, 16), (8, 8)]), shift=I.PAPER_SHIFT)
     mlp = ntc.Mlp(*I.xavier_mlp(rng, dims, bias="normal"))
-    n = 64 * 8 * torch.cuda.get_device_properties(0).multi_processor_count * 4 + 17  # long spans
+    n = 64 * 8 * torch.cuda.get_device_properties(0).multi_processor_count * 16 + 17  # long spans
     i = torch.arange(n, device="cuda")
     uv = torch.stack([(i % 1013) / 1013.0, (i // 1013) / 1100.0], 1).float()
     uv[-3000:] = torch.rand((3000, 2), generator=torch.Generator().manual_seed(1)).cuda() * 1.2 - 0.1
@@ -673,7 +673,9 @@ def test_short_batches_equal_long(compute, dims):
         return ntc.decode(lat, mlp, uv[a:b].contiguous(), compute=compute, packed=packed, out_dtype=dt)
 
     whole, half = run(0, n), run(0, n, torch.float16)
-    for a, b in ((0, 1), (5, 68), (64, 128), (1000, 1065), (0, n // 4), (n // 2, n // 2 + n // 4 - 40), (n - 4000, n)):
+    w = n // 16  # a tile a wave
+    for a, b in ((0, 1), (5, 68), (64, 128), (1000, 1065), (0, w), (3 * w, 8 * w - 40), (w, 6 * w + 9), (0, 9 * w),
+                 (n - 4000, n)):
         print(f"[short] {compute} {dims} {a}:{b}", flush=True)
         assert torch.equal(whole[a:b], run(a, b)), (a, b)
         assert torch.equal(half[a:b], run(a, b, torch.float16)), (a, b)
