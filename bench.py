@@ -7,7 +7,7 @@ seed 2), MLP 14-64-64-64-8 (Xavier-normal, zero biases), uv at pixel
 centres plus uniform jitter of +-1/2 pixel, pixels in 8x8-tile order,
 FP32 output. One step = one ntc_decode launch over all 16.7 M pixels with
 inputs resident in HBM. value = pixels x steps / time of the timed steps,
-in Gtexel/s, for the FP16 matrix-core path; the plain FP32 and the E4M3
+in Gtexel/s, for the FP16 matrix-core path; the FP32 and the E4M3
 paths, the backward and the batched decode are reported beside it.
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W]
@@ -26,7 +26,7 @@ sys.path.insert(0, ROOT)
 METRIC = "Gtexels/s fused BC1+MLP decode at 4096², FP16/FP8 MFMA vs FP32 plain at stated err"
 PEAK_FP16_TFLOPS = 2500.0      # MI355X dense FP16 matrix peak
 PEAK_FP8_TFLOPS = 5000.0
-PEAK_FP32_VALU_TFLOPS = 157.3  # FP32 vector peak
+PEAK_FP32_VALU_TFLOPS = 157.3  # FP32 vector peak (the FP32 decode, on the BF16 matrix cores, can exceed it)
 PEAK_HBM_GBS = 8000.0
 KERNEL_SOURCES = ["paper_2506_06040_amd/csrc/ntc_mfma.hip", "paper_2506_06040_amd/csrc/ntc_mfma_tile.hpp",
                   "paper_2506_06040_amd/csrc/ntc_device.hpp"]
@@ -396,7 +396,7 @@ def main():
                               "classify_GBs": (2 * 2 * fw * fh + 4 * n_valid) / ms_cls / 1e6,
                               "end_to_end_ms": ms_e2e,
                               "note": "indexed: the batched decode reads uv and writes the image through the "
-                                      "pixel lists; end_to_end includes the host batch plan of each frame"}
+                                      "pixel lists; end_to_end: classification, plan built on the device, decode"}
         del mats, fd, fp, fg, mat_ids, uv_img, out_img, cw, cl
 
     cpu = None
