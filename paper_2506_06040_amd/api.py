@@ -235,7 +235,7 @@ def decode_backward(lat: Latents, mlp: Mlp, uv: torch.Tensor, grad_out: torch.Te
 
 
 class NtcDecodeFn(torch.autograd.Function):
-    """out = p(uv) for float latents with the plain FP32 decode; backward by
+    """out = p(uv) for float latents with the FP32 decode; backward by
     the hand-written gradient kernel. Only the inputs are saved: activations
     are recomputed per tile in the backward kernel.
 

@@ -63,7 +63,15 @@ static int backward_blocks(const MlpShape &s, int64_t n) {
 // larger power of two, keeping at most kMaxBins bins) level-0 texels.
 constexpr int kBinShift = 5;
 constexpr int kMaxBins = 4096;
-constexpr int kBinSamplesPerBlock = 4096;  // samples per workgroup of the count / scatter passes
+// Samples and threads per workgroup of the count / scatter passes. Larger
+// shares need fewer global atomics (one per workgroup and bin) but leave CUs
+// idle; more threads hide the latency of the loads, which are requested
+// together (us, count + scatter at 2^20 / 2^18 samples: 4096 by 256 threads 12.5
+// + 17.4 / 9.6 + 10.4, by 512 9.3 + 14.9 / 5.5 + 7.9, by 1024 8.5 + 14.1 /
+// 4.9 + 7.3; 8192 by 1024 7.1 + 13.6 / 6.5 + 10.9; 2048 by 512 12.9 + 20.9 /
+// 5.3 + 6.9).
+constexpr int kBinSamplesPerBlock = 4096;
+constexpr int kBinThreads = 1024;
 constexpr int kBinRun = 1120;              // samples of a bin taken by one workgroup of the accumulation
 constexpr int kAccThreads = 512;           // threads of that workgroup
 constexpr int kBinWindowFloats = 12288;    // largest LDS of a bin's texel window (48 KB)
@@ -778,17 +786,23 @@ __device__ __forceinline__ int bin_of(const BackwardArgs &a, float2 uv) {
 
 // Per-bin sample counts: a histogram in LDS per workgroup, added to the
 // global counts (which start at zero).
-__global__ __launch_bounds__(256) void bin_count_kernel(BackwardArgs a) {
+__global__ __launch_bounds__(kBinThreads) void bin_count_kernel(BackwardArgs a) {
   extern __shared__ int32_t hist[];
-  for (int k = threadIdx.x; k < a.n_bins; k += 256) hist[k] = 0;
+  for (int k = threadIdx.x; k < a.n_bins; k += kBinThreads) hist[k] = 0;
   __syncthreads();
   const int64_t s0 = (int64_t)blockIdx.x * kBinSamplesPerBlock;
-  for (int i = threadIdx.x; i < kBinSamplesPerBlock; i += 256) {
-    const int64_t s = s0 + i;
-    if (s < a.n) atomicAdd(&hist[bin_of(a, a.uv[s])], 1);
+  constexpr int kPer = kBinSamplesPerBlock / kBinThreads;
+  float2 uv[kPer];
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    const int64_t s = s0 + threadIdx.x + kBinThreads * i;
+    uv[i] = a.uv[s < a.n ? s : a.n - 1];
   }
+#pragma unroll
+  for (int i = 0; i < kPer; ++i)
+    if (s0 + threadIdx.x + kBinThreads * i < a.n) atomicAdd(&hist[bin_of(a, uv[i])], 1);
   __syncthreads();
-  for (int k = threadIdx.x; k < a.n_bins; k += 256)
+  for (int k = threadIdx.x; k < a.n_bins; k += kBinThreads)
     if (hist[k]) atomicAdd(&a.bin_count[k], hist[k]);
 }
 
@@ -838,27 +852,27 @@ __global__ __launch_bounds__(1024) void bin_scan_kernel(BackwardArgs a) {
 // LDS, reserves a range per bin with one global atomic, then writes. The
 // order inside a bin depends on timing (as does the order of the atomics
 // that follow it).
-__global__ __launch_bounds__(256) void bin_scatter_kernel(BackwardArgs a) {
+__global__ __launch_bounds__(kBinThreads) void bin_scatter_kernel(BackwardArgs a) {
   extern __shared__ int32_t lds[];
   int32_t *local = lds, *base = lds + a.n_bins;
-  for (int k = threadIdx.x; k < a.n_bins; k += 256) local[k] = 0;
+  for (int k = threadIdx.x; k < a.n_bins; k += kBinThreads) local[k] = 0;
   __syncthreads();
-  constexpr int kPer = kBinSamplesPerBlock / 256;
+  constexpr int kPer = kBinSamplesPerBlock / kBinThreads;
   const int64_t s0 = (int64_t)blockIdx.x * kBinSamplesPerBlock;
   int key[kPer], rank[kPer];
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
-    const int64_t s = s0 + threadIdx.x + 256 * i;
+    const int64_t s = s0 + threadIdx.x + kBinThreads * i;
     key[i] = s < a.n ? bin_of(a, a.uv[s]) : -1;
     rank[i] = key[i] >= 0 ? atomicAdd(&local[key[i]], 1) : 0;
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < a.n_bins; k += 256)
+  for (int k = threadIdx.x; k < a.n_bins; k += kBinThreads)
     if (local[k]) base[k] = atomicAdd(&a.bin_cursor[k], local[k]);
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < kPer; ++i)
-    if (key[i] >= 0) a.perm[base[key[i]] + rank[i]] = (int32_t)(s0 + threadIdx.x + 256 * i);
+    if (key[i] >= 0) a.perm[base[key[i]] + rank[i]] = (int32_t)(s0 + threadIdx.x + kBinThreads * i);
 }
 
 // Cells (left / top taps) of one level that one bin's samples fall into:
@@ -1303,11 +1317,11 @@ hipError_t launch_backward(const BackwardArgs &a, const MlpShape &s, float *cons
     return hipGetLastError();
   }
   const unsigned grid = (unsigned)((a.n + kBinSamplesPerBlock - 1) / kBinSamplesPerBlock);
-  hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(256), a.n_bins * sizeof(int32_t), st, a);
+  hipLaunchKernelGGL(bin_count_kernel, dim3(grid), dim3(kBinThreads), a.n_bins * sizeof(int32_t), st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(bin_scan_kernel, dim3(1), dim3(1024), 0, st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(256), 2 * a.n_bins * sizeof(int32_t), st, a);
+  hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(kBinThreads), 2 * a.n_bins * sizeof(int32_t), st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(bin_accum_kernel, dim3((unsigned)((a.n_runs + 7) / 8 * 8 * a.lat.n_levels)), dim3(kAccThreads),
                      (size_t)(a.bin_lds + 5 * kBinRun + a.bin_cells + 1) * sizeof(float), st, a);
