@@ -224,23 +224,10 @@ __global__ __launch_bounds__(64 * kReduceWaves) void reduce_f64_kernel(ReduceArg
 typedef float bf32x16 __attribute__((ext_vector_type(16)));
 typedef float bf32x4 __attribute__((ext_vector_type(4)));
 
-// Level parameters in LDS, so that a lane half reads its two levels' own
-// without holding them in registers or choosing among scalars:
-// [h][j] = grid pointer, w, h | fw, fh, sx, sy | 1 / fw, 1 / fh.
-struct LevelSel {
-  const float *grid;
-  int w, h;
-  float fw, fh, sx, sy;
-  float rw, rh;
-};
 constexpr int kLevelFloats = sizeof(LevelSel) / sizeof(float) + 2;  // a multiple of 4
 
 __device__ __forceinline__ void load_levels(float *tab, const LatArgs &lat, int tid) {
-  if (tid < kMaxLevels) {
-    const LevelArgs &A = lat.lv[tid];
-    *reinterpret_cast<LevelSel *>(tab + kLevelFloats * tid) = {A.grid, A.w,  A.h,         A.fw,       A.fh,
-                                                               A.sx,   A.sy, 1.0f / A.fw, 1.0f / A.fh};
-  }
+  if (tid < kMaxLevels) *reinterpret_cast<LevelSel *>(tab + kLevelFloats * tid) = level_sel(lat.lv[tid]);
 }
 
 template <int MT, int NL>

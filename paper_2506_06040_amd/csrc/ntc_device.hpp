@@ -97,13 +97,29 @@ __device__ __forceinline__ int address_coord(int i, int n, int mode) {
   return min(max(i, 0), n - 1);
 }
 
-// i modulo n for |i| <= 2^24 + 1 and n >= 4, with rn within 2^-22 of 1 / n
-// (relative): the quotient is off by at most one. An integer division takes
-// several times as long.
-__device__ __forceinline__ int wrap_near(int i, int n, float rn) {
+// i modulo n without an integer division, which takes several times as long.
+// rn is 1 / n to one unit in the last place; |i| <= 2^24 + 2 n, and <= 2^22
+// where n < 4 (block counts of small levels). The computed quotient is then
+// within 2^-22 |i| / n < 1 of i / n (the reciprocal, i as a float and the
+// product each round once; for n = 4 the reciprocal is exact), so its floor is
+// off by at most one.
+__host__ __device__ __forceinline__ int wrap_near(int i, int n, float rn) {
   int r = i - n * (int)floorf((float)i * rn);
   r += r < 0 ? n : 0;
   return r >= n ? r - n : r;
+}
+
+// Level parameters as the training kernels keep them in LDS, so that a lane
+// half reads its two levels' own without holding them in registers or choosing
+// among scalars.
+struct LevelSel {
+  const float *grid;
+  int w, h;
+  float fw, fh, sx, sy;
+  float rw, rh;  // 1 / w, 1 / h: of the sides, which unused levels have too (their scales fw, fh are zero)
+};
+__host__ __device__ __forceinline__ LevelSel level_sel(const LevelArgs &A) {
+  return {A.grid, A.w, A.h, A.fw, A.fh, A.sx, A.sy, 1.0f / (float)A.w, 1.0f / (float)A.h};
 }
 
 // Bilinear footprint on one level: x = u w - 1/2 + s (texel centres at

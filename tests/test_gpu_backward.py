@@ -319,3 +319,41 @@ def test_backward_latent_bins(sizes, address, span, hot):
     _, _, ol = O.backward(olat, O.Mlp(Ws, bs), uv, g)
     for k in range(len(sizes)):
         _close(f"bins dlat{k}", gl[k], ol[k])
+
+
+@pytest.mark.parametrize("address", ["clamp", "wrap"])
+@pytest.mark.parametrize("levels", [1, 2, 3])
+@pytest.mark.parametrize("n", [4096, 70000])  # the forward on the FP32 and on the BF16 matrix cores
+def test_non_finite_uv_float_latents(levels, address, n):
+    """NaN and infinite coordinates among finite ones, fewer levels than the
+    kernels sample: the finite samples' outputs equal a launch without the
+    others bit for bit, and with no upstream gradient on the others (zero
+    weights on u and v, so that their outputs are finite) the gradients do
+    not change beyond the order of their sums."""
+    ntc = _ntc()
+    rng = np.random.default_rng(100 * levels + n)
+    sizes = [(36, 20), (64, 64), (32, 16)][:levels]
+    lat_np = I.f32_pyramid(rng, sizes)
+    Ws, bs = I.xavier_mlp(rng, (3 * levels + 2, 64, 64, 8), bias="normal")
+    Ws[0][:, -2:] = 0.0
+    clean = (rng.random((n, 2)) * 1.5 - 0.25).astype(np.float32)
+    bad = np.array([[np.nan, 0.5], [0.5, np.nan], [np.inf, 0.2], [-np.inf, 0.7], [0.3, np.inf], [0.6, -np.inf],
+                    [np.nan, np.nan], [np.inf, -np.inf]], np.float32)
+    at = rng.choice(n, 40, replace=False)
+    mixed = np.insert(clean, at, bad[rng.integers(0, len(bad), 40)], axis=0)
+    fin = np.isfinite(mixed).all(1)
+    shift = I.PAPER_SHIFT[:levels]
+    lat, mlp = ntc.Latents(lat_np, shift=shift, address=address), ntc.Mlp(Ws, bs)
+    print(f"[non-finite uv] {levels} levels {address} n={n}", flush=True)
+    a = ntc.decode(lat, mlp, torch.from_numpy(mixed).cuda(), compute="f32").cpu().numpy()
+    b = ntc.decode(lat, mlp, torch.from_numpy(clean).cuda(), compute="f32").cpu().numpy()
+    assert np.array_equal(a[fin], b) and np.isfinite(a).all()
+    g = np.zeros((mixed.shape[0], 8))
+    g[fin] = rng.standard_normal((n, 8))
+    gW, gb, gl = _gpu_direct(lat_np, Ws, bs, mixed, g, shift, address=address)
+    rW, rb, rl = _gpu_direct(lat_np, Ws, bs, clean, g[fin], shift, address=address)
+    for l in range(3):  # the first layer's columns of u and v: 0 times infinity
+        _close(f"dW{l}", gW[l][:, :-2] if l == 0 else gW[l], rW[l][:, :-2] if l == 0 else rW[l])
+        _close(f"db{l}", gb[l], rb[l])
+    for k in range(levels):
+        _close(f"dlat{k}", gl[k], rl[k])
