@@ -586,10 +586,10 @@ class FrameDecoder:
         takes, or tensors that only a frame without neural pixels may have."""
         _require_ids(mat_ids)
         h, w = mat_ids.shape
-        uv = uv_image.reshape(-1, 2)
+        uv = uv_image.reshape(-1, 2)  # may be a view of other strides
         px = uv.numel() // 2
         row = self.n_out * out.element_size()
-        if not (uv.is_cuda and 1 <= px and max(8, row) * px < 1 << 30 and h * w <= 1 << 28 and
+        if not (uv.is_cuda and uv.is_contiguous() and 1 <= px and max(8, row) * px < 1 << 30 and h * w <= 1 << 28 and
                 uv.data_ptr() % 8 == 0 and out.data_ptr() % 16 == 0):
             return False
         L, n = A.lib(), len(self.materials)

@@ -203,3 +203,22 @@ def test_frame_decode_rejects_as_before():
     with pytest.raises(ntc.NtcError):  # misaligned uv
         fd.decode(torch.zeros((8, 8), dtype=torch.int16, device="cuda"),
                   torch.zeros(129, device="cuda")[1:].reshape(8, 8, 2))
+
+
+@pytest.mark.parametrize("view", ["columns", "expanded"])
+def test_frame_decode_rejects_strided_uv(view):
+    """Coordinates that are not adjacent pairs: ValueError where there is
+    something to decode, nothing to do (and no error) where there is not."""
+    ntc = _ntc()
+    rng = np.random.default_rng(4)
+    lat = ntc.Latents(I.bc1_pyramid(rng, [(16, 16), (8, 8)]), shift=I.PAPER_SHIFT[:2])
+    fd = ntc.FrameDecoder([(lat, ntc.Mlp(*I.xavier_mlp(rng, (8, 16, 4), bias="normal")))])
+    uv = torch.rand((8, 8, 4), device="cuda")[..., :2] if view == "columns" else torch.rand((1, 1, 2), device="cuda").expand(8, 8, 2)
+    assert not uv.reshape(-1, 2).is_contiguous()
+    with pytest.raises(ValueError):
+        fd.decode(torch.zeros((8, 8), dtype=torch.int16, device="cuda"), uv)
+    assert not fd.decode(torch.full((8, 8), 5, dtype=torch.int16, device="cuda"), uv).any()
+    # a transposed image is copied into pairs
+    t = torch.rand((8, 8, 2), device="cuda").transpose(0, 1)
+    ids = torch.zeros((8, 8), dtype=torch.int16, device="cuda")
+    assert torch.equal(fd.decode(ids, t), fd.decode(ids, t.contiguous()))
