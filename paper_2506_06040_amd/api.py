@@ -589,8 +589,9 @@ class FrameDecoder:
         uv = uv_image.reshape(-1, 2)  # may be a view of other strides
         px = uv.numel() // 2
         row = self.n_out * out.element_size()
-        if not (uv.is_cuda and uv.is_contiguous() and 1 <= px and max(8, row) * px < 1 << 30 and h * w <= 1 << 28 and
-                uv.data_ptr() % 8 == 0 and out.data_ptr() % 16 == 0):
+        if not (uv.is_cuda and uv.is_contiguous() and out.dtype in OUT_DTYPES and 1 <= px and
+                max(8, row) * px < 1 << 30 and h * w <= 1 << 28 and uv.data_ptr() % 8 == 0 and
+                out.data_ptr() % 16 == 0):
             return False
         L, n = A.lib(), len(self.materials)
         ws, ps = ctypes.c_size_t(0), ctypes.c_size_t(0)

@@ -52,3 +52,12 @@ def test_strided_uv_is_not_decoded_unseen(monkeypatch):
     with pytest.raises(Reached):
         fd._decode_on_device(ids, FakeUv(True), out)
     assert fd._decode_on_device(ids, FakeUv(False), out) is False
+
+
+def test_other_output_types_are_not_decoded_unseen(monkeypatch):
+    """An output type that no decode writes: left to the path that refuses it
+    where there is something to decode, and only there."""
+    fd = _decoder(monkeypatch)
+    fd.out_dtype = torch.bfloat16
+    ids = torch.zeros((8, 8), dtype=torch.int16)
+    assert fd._decode_on_device(ids, FakeUv(True), torch.zeros((8, 8, 4), dtype=torch.bfloat16)) is False

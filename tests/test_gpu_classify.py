@@ -222,3 +222,14 @@ def test_frame_decode_rejects_strided_uv(view):
     t = torch.rand((8, 8, 2), device="cuda").transpose(0, 1)
     ids = torch.zeros((8, 8), dtype=torch.int16, device="cuda")
     assert torch.equal(fd.decode(ids, t), fd.decode(ids, t.contiguous()))
+
+
+def test_frame_without_neural_pixels_keeps_any_output_type():
+    ntc = _ntc()
+    rng = np.random.default_rng(5)
+    lat = ntc.Latents(I.bc1_pyramid(rng, [(16, 16), (8, 8)]), shift=I.PAPER_SHIFT[:2])
+    fd = ntc.FrameDecoder([(lat, ntc.Mlp(*I.xavier_mlp(rng, (8, 16, 4), bias="normal")))], out_dtype=torch.bfloat16)
+    uv = torch.rand((8, 8, 2), device="cuda")
+    assert not fd.decode(torch.full((8, 8), 5, dtype=torch.int16, device="cuda"), uv).any()
+    with pytest.raises(KeyError):
+        fd.decode(torch.zeros((8, 8), dtype=torch.int16, device="cuda"), uv)
