@@ -479,7 +479,9 @@ class FrameDecoder:
     batched launch (FP16 matrix cores), or gather their uv, decode and scatter
     the outputs back. The batch plan is built on the device, so that decode
     waits for nothing; with a cfg of the caller's own (work item size), or
-    gathered, it is built on the host.
+    gathered, it is built on the host. A decode may be captured into a graph
+    once a frame has been decoded with the same materials; the graph reads
+    memory that lives as long as the decoder.
     materials: sequence of (Latents, Mlp) with a common output width."""
 
     def __init__(self, materials, cfg=None, out_dtype=torch.float32, device="cuda"):
@@ -491,6 +493,7 @@ class FrameDecoder:
         self.packed = [pack(m, "f16") for _, m in self.materials]
         self.cfg, self.out_dtype, self.device = cfg, out_dtype, device
         self._table = None  # (signature, host image, device image) of _frame_table
+        self._captured = []  # device images that captured graphs read, kept as long as the decoder
 
     def plan(self, mat_ids: torch.Tensor, uv_image: torch.Tensor, out: Optional[torch.Tensor] = None,
              indexed: bool = True):
@@ -574,7 +577,7 @@ class FrameDecoder:
             return None
         # a copy from pageable memory is complete when it returns; frames in
         # flight on any stream keep the table that this one replaces
-        # (record_stream at each use)
+        # (record_stream at each use), captured ones for good (_captured)
         dev = torch.from_numpy(host).to(self.device)
         self._table = table = (sig, host, dev)
         return table
@@ -613,6 +616,8 @@ class FrameDecoder:
         check(L.ntc_decode_frame_workspace(host.ctypes.data, host.nbytes, ctypes.byref(ps)))
         plan = torch.empty(ps.value, dtype=torch.uint8, device=mat_ids.device)
         dev.record_stream(stream)
+        if torch.cuda.is_current_stream_capturing() and not any(t is dev for t in self._captured):
+            self._captured.append(dev)
         check(L.ntc_decode_frame(host.ctypes.data, _ptr(dev), host.nbytes, lst, off, _ptr(uv), _ptr(out), px,
                                  _ptr(plan), ps.value, sh))
         return True

@@ -233,3 +233,41 @@ def test_frame_without_neural_pixels_keeps_any_output_type():
     assert not fd.decode(torch.full((8, 8), 5, dtype=torch.int16, device="cuda"), uv).any()
     with pytest.raises(KeyError):
         fd.decode(torch.zeros((8, 8), dtype=torch.int16, device="cuda"), uv)
+
+
+def test_frame_decode_captured():
+    """A captured frame decode follows its inputs and keeps its materials when
+    the decoder has gone on to others, over several replays with eager work
+    between them."""
+    ntc = _ntc()
+    rng = np.random.default_rng(6)
+    h, w = 72, 104
+
+    def materials(n):
+        return [(ntc.Latents(I.bc1_pyramid(rng, [(32, 32), (16, 16)]), shift=I.PAPER_SHIFT[:2]),
+                 ntc.Mlp(*I.xavier_mlp(rng, (8, (16, 32, 64)[m % 3], 4), bias="normal"))) for m in range(n)]
+
+    first, second = materials(5), materials(5)
+    fd, ref = ntc.FrameDecoder(first), ntc.FrameDecoder(first)
+    packed = list(fd.packed)
+    frames = [(torch.from_numpy(I.material_frame(rng, w, h, 5, noise=0.02)).cuda(),
+               torch.from_numpy(rng.random((h, w, 2)).astype(np.float32)).cuda()) for _ in range(3)]
+    ids, uv = frames[0][0].clone(), frames[0][1].clone()
+    out = torch.zeros((h, w, 4), device="cuda")
+    fd.decode(ids, uv, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        fd.decode(ids, uv, out=out)
+    table = fd._table[2]
+    fd.materials, fd.packed = second, [ntc.pack(m, "f16") for _, m in second]
+    fd.decode(*frames[0])
+    assert fd._table[2] is not table and fd._captured == [table]
+    for i in range(6):
+        ids.copy_(frames[i % 3][0]), uv.copy_(frames[i % 3][1])
+        out.zero_()
+        torch.full((1 << 20,), 255, dtype=torch.uint8, device="cuda")
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref.decode(*frames[i % 3])), i
+    del packed
