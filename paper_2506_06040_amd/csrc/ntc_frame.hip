@@ -19,6 +19,7 @@
 #include <cstring>
 #include <vector>
 
+#include "ntc.h"
 #include "ntc_internal.hpp"
 
 namespace ntc {
@@ -28,8 +29,9 @@ namespace {
 constexpr int kPlanThreads = 1024;
 constexpr int kCopyMats = 16;  // materials a copying workgroup fills in
 
-// A material in the order of the items: index, shape and cost of a tile.
-constexpr uint32_t kMaxTileCost = 1000;
+// A material in the order of the items: index, shape and cost of a tile, in
+// units of two matrix issue slots.
+constexpr uint32_t kMaxTileCost = 127;
 // Share of sampling, in matrix issue slots, of a tile of listed pixels: one
 // material over 2560 x 1440 takes 88 us at 16 x 2 (width x layers), 92 at
 // 64 x 2, 101 at 64 x 3, 114 at 64 x 4, which is nearly flat. Frame of 64
@@ -79,8 +81,10 @@ __device__ __forceinline__ uint32_t block_prefix(uint32_t v, uint32_t *part, uin
 
 // Workgroup 0: header, work items and the waves' ranges of them. The others:
 // the material table, each word copied and the frame's fields filled in.
-// LDS: 2 (n_mats + 1) words. Sums of costs fit 32 bits: below 2^31 pixels there
-// are at most 2^25 + n_mats tiles, of a cost of at most kMaxTileCost each.
+// LDS: 2 (n_mats + 1) words. Sums of costs fit 32 bits: mat_offsets, being
+// int32, count less than 2^31 pixels, so there are at most 2^25 + n_mats tiles,
+// of a cost of at most kMaxTileCost each.
+static_assert(((1ull << 25) + NTC_MAX_CLASSIFY_MATERIALS) * kMaxTileCost < (1ull << 32), "32-bit sums of costs");
 __global__ __launch_bounds__(kPlanThreads) void frame_plan_kernel(FrameArgs f) {
   const int n_mats = f.t.plan.n_mats;
   if (blockIdx.x > 0) {
@@ -231,7 +235,7 @@ void build_frame_table(const BatchMaterial *mats, int n_mats, int n_waves, int s
     const BatchMaterial &M = mats[by_shape[k]];
     order[k] = order_word(by_shape[k], M.shape_id,
                           std::min<uint32_t>(kMaxTileCost,
-                                                (uint32_t)tile_cost(M.hid, M.n_layers, kListedSampling)));
+                                             (uint32_t)(0.5 * tile_cost(M.hid, M.n_layers, kListedSampling))));
   }
 }
 

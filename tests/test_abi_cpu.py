@@ -283,3 +283,31 @@ def test_frame_entries_reject(A):
     assert call(size=ws.value - 1) == A.E_WORKSPACE
     buf[0] ^= 1
     assert call() == A.E_SHAPE  # not a frame table
+
+
+def test_frame_costs_sum_in_32_bits(A):
+    """The plan kernel adds the materials' tile costs in 32 bits over every
+    list that int32 offsets can count: 2^25 tiles and one begun tile per
+    material, all of the costliest network."""
+    L = A.lib()
+    n = ctypes.c_size_t(0)
+    shapes = [(h, l) for h in (16, 32, 64) for l in (2, 3, 4)]
+    assert L.ntc_frame_table_size(len(shapes), ctypes.byref(n)) == A.OK
+    mats = (A.ntc_material * len(shapes))()
+    for m, (hid, layers) in zip(mats, shapes):
+        m.lat.n_levels, m.lat.format = 1, A.LATENT_BC1
+        m.lat.width[0] = m.lat.height[0] = 16
+        m.lat.data[0] = 0x1000
+        m.mlp.n_layers = layers
+        for i, d in enumerate([5] + [hid] * (layers - 1) + [4]):
+            m.mlp.dims[i] = d
+        m.packed = 0x1000
+    buf = (ctypes.c_uint8 * n.value)()
+    assert L.ntc_frame_table(mats, len(shapes), None, buf, n.value) == A.OK
+    # the last section of the table: material | shape << 12 | cost << 16, by shape
+    order = [int.from_bytes(bytes(buf[n.value - 256 + 4 * k:n.value - 252 + 4 * k]), "little")
+             for k in range(len(shapes))]
+    assert [o & 0xFFF for o in order] == list(range(len(shapes)))
+    cost = [o >> 16 for o in order]
+    assert min(cost) > 0 and cost[0] < cost[-1]
+    assert (2 ** 25 + 4096) * max(cost) < 2 ** 32
