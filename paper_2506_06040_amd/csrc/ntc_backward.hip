@@ -105,7 +105,9 @@ BwdLayout backward_layout(const MlpShape &s, const LatArgs &lat, int64_t n) {
   L.n_params = n_params_of(s);
   L.n_feat = 3 * lat.n_levels;
   L.dx_stride = (L.n_feat + 2 + 3) & ~3;
-  if (n < ((int64_t)1 << 31)) {  // sample indices of the bins are int32
+  // Sample indices of the bins are int32, and so is the end of the run that
+  // follows the last one of a bin holding all samples.
+  if (n <= INT32_MAX - kBinRun) {
     int t = kBinShift;
     const int w = lat.lv[0].w, h = lat.lv[0].h;
     auto bins = [&](int len) { return (len + (1 << t) - 1) >> t; };

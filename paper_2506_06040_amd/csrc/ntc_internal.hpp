@@ -109,7 +109,7 @@ hipError_t launch_zero(const ZeroArgs &z, hipStream_t st);
 struct BwdLayout {
   int32_t n_blocks, n_params, n_feat;
   int32_t dx_stride;                  // floats of a row of dx (a multiple of 4)
-  int32_t bin_shift, bins_x, n_bins;  // bins of 2^bin_shift level-0 texels; n_bins = 0: no binning (2^31 samples or more)
+  int32_t bin_shift, bins_x, n_bins;  // bins of 2^bin_shift level-0 texels; n_bins = 0: no binning (too many samples for int32 runs)
   int32_t n_runs;                     // largest number of sample runs of the bins
   int32_t bin_lds, bin_cells;         // LDS floats and cells of a bin's largest texel window
   size_t wpart_off, dx_off, count_off, cursor_off, perm_off, runs_off, total;

@@ -311,3 +311,28 @@ def test_frame_costs_sum_in_32_bits(A):
     cost = [o >> 16 for o in order]
     assert min(cost) > 0 and cost[0] < cost[-1]
     assert (2 ** 25 + 4096) * max(cost) < 2 ** 32
+
+
+def test_backward_bins_end_before_int32_runs_wrap(A):
+    """Samples are binned as long as every run (1120 samples of a bin) ends
+    within int32, whatever bin they fall into; above that the workspace holds
+    no sample indices."""
+    L = A.lib()
+    lat, mlp = A.ntc_latents(), A.ntc_mlp()
+    lat.n_levels, lat.format = 1, A.LATENT_F32
+    lat.width[0] = lat.height[0] = 16
+    lat.data[0] = 0x1000
+    mlp.n_layers = 2
+    mlp.dims[0], mlp.dims[1], mlp.dims[2] = 5, 16, 4
+
+    def workspace(n):
+        b = ctypes.c_size_t(0)
+        assert L.ntc_decode_backward_workspace(ctypes.byref(lat), ctypes.byref(mlp), n, ctypes.byref(b)) == A.OK
+        return b.value
+
+    row = 4 * 8  # gradients of three features, u, v, padded to eight floats
+    last = 2 ** 31 - 1 - 1120
+    for n in (last, 2 ** 31 - 2000):
+        assert workspace(n) - n * row > 4 * n
+    for n in (last + 1, 2 ** 31 - 1, 2 ** 31):
+        assert workspace(n) - n * row < 4 * n
