@@ -229,7 +229,9 @@ __device__ __forceinline__ float3 direct_level(const TabLevel &L, float u, float
   return numer_values(blend4(at(i0, j0), at(i1, j0), at(i0, j1), at(i1, j1), fx, fy));
 }
 
-// Float latents: the loads of all levels in flight together.
+// Float latents: the loads of all levels in flight together. Levels past
+// n_levels (which mirror level 0) give zeros: their weights are zero, but a
+// texel of theirs may not be finite.
 __device__ __forceinline__ void grid_levels(const LatArgs &lat, float u, float v, float3 (&c)[kMaxLevels]) {
   float fx[kMaxLevels], fy[kMaxLevels];
   int i0[kMaxLevels], i1[kMaxLevels], j0[kMaxLevels], j1[kMaxLevels];
@@ -274,10 +276,12 @@ __device__ __forceinline__ void grid_levels(const LatArgs &lat, float u, float v
       for (int ch = 0; ch < 3; ++ch) t[k][q][ch] = p[ch];
     }
 #pragma unroll
-  for (int k = 0; k < kMaxLevels; ++k)
+  for (int k = 0; k < kMaxLevels; ++k) {
     c[k] = blend4(make_float3(t[k][0][0], t[k][0][1], t[k][0][2]), make_float3(t[k][1][0], t[k][1][1], t[k][1][2]),
                   make_float3(t[k][2][0], t[k][2][1], t[k][2][2]), make_float3(t[k][3][0], t[k][3][1], t[k][3][2]),
                   fx[k], fy[k]);
+    if (k >= lat.n_levels) c[k] = make_float3(0.0f, 0.0f, 0.0f);
+  }
 }
 
 // Outputs of one 32-pixel tile: rows 8 j + 4 h + r of pixel px (keep: of the

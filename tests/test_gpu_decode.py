@@ -679,3 +679,22 @@ def test_short_batches_equal_long(compute, dims):
         print(f"[short] {compute} {dims} {a}:{b}", flush=True)
         assert torch.equal(whole[a:b], run(a, b)), (a, b)
         assert torch.equal(half[a:b], run(a, b, torch.float16)), (a, b)
+
+
+@pytest.mark.parametrize("dims,n", [((11, 32, 32, 32, 32, 4), 300), ((8, 64, 64, 64, 64, 8), 5000),
+                                    ((8, 64, 64, 8), 70000)])
+def test_f32_unused_levels_add_nothing(dims, n):
+    """FP32 decode of fewer than four float levels whose first texels are not
+    finite: pixels that do not sample them match the oracle."""
+    ntc = _ntc()
+    rng = np.random.default_rng(n)
+    levels = (dims[0] - 2) // 3
+    lat_np = I.f32_pyramid(rng, [(64, 64), (32, 32), (16, 16)][:levels])
+    lat_np[0][0, 0], lat_np[0][1, 1] = np.inf, np.nan
+    Ws, bs = I.xavier_mlp(rng, dims, bias="normal")
+    shift = I.PAPER_SHIFT[:levels]
+    uv = (0.1 + 0.9 * rng.random((n, 2))).astype(np.float32)
+    lat, mlp = _gpu_case(lat_np, Ws, bs, shift)
+    out = ntc.decode(lat, mlp, torch.from_numpy(uv).cuda(), compute="f32").cpu().numpy()
+    ref = O.decode(O.Latents(lat_np, shift=shift), O.Mlp(Ws, bs), uv)
+    assert np.all(np.abs(out - ref) <= TOL_F32_REL * np.abs(ref))
