@@ -7,7 +7,7 @@
 // of the one before), a2 b3, a3 b2 and a3 b3 are below 2^-24 |a b|. The six
 // are exact in the FP32 accumulators' inputs and are added there smallest
 // first. Activations are cut (the parts are the number's own bits, so the
-// three add up exactly), weights are rounded (the dropped terms then have no
+// three add up exactly in the normal range), weights are rounded (the dropped terms then have no
 // common sign). Against 64-bit results the error is that of the FP32 chain or
 // smaller: a layer of 64 inputs rounds 24 times, not 64.
 //
@@ -22,9 +22,13 @@
 // as everywhere in the FP32 path.
 //
 // Numbers that could leave FP32's range (or are infinite or NaN) must not be
-// split: infinity minus its leading part is NaN. A bound from the largest
-// weight and bias of every layer and |u|, |v| <= 2^20 decides per network,
-// the coordinates (and float latents) per pixel; what fails it is decoded by a
+// split: infinity minus its leading part is NaN. Nor may small numbers be whose
+// lower parts, below BF16's normal range, matter: that range ends where FP32's
+// does, so a part of at most 2^-126 may be lost, and where a layer's numbers are
+// all that small, and the next layer's weights large, it is many units in the
+// last place. Bounds from the largest weight and bias of every layer and |u|,
+// |v| <= 2^20 decide per network (split_setup), the coordinates (and float
+// latents) per pixel; what fails is decoded by a
 // second walk with the FP32 matrix instructions (exact_pixels), pixel by
 // pixel, so that a pixel's result does not depend on its neighbours.
 #include <hip/hip_runtime.h>
@@ -93,8 +97,11 @@ __device__ __forceinline__ float split_weight(const DecodeArgs &a, const uint8_t
 }
 
 // Weights, biases and level table into LDS; returns whether the network's
-// numbers stay in range (latents are at most 1 in BC1 images, float latents
-// are checked with the coordinates). Rolled loops: a short batch pays for
+// numbers stay in range: no sum of any layer passes 2^120, and the parts lost
+// below the normal range (with products below it, at most 2^-122 per operand)
+// change no output's pre-activation by more than 2^-30, a 64th of what FP32
+// rounds an output by. (Latents are at most 1 in BC1 images, float latents are
+// checked with the coordinates.) Rolled loops: a short batch pays for
 // every instruction line fetched.
 template <int HP, int NL>
 __device__ __forceinline__ bool split_setup(const DecodeArgs &a, uint8_t *lds, int tid) {
@@ -165,14 +172,17 @@ __device__ __forceinline__ bool split_setup(const DecodeArgs &a, uint8_t *lds, i
     note(mx + kMaxLayers + l, fabsf(b));
   }
   __syncthreads();
-  float b = 0x1p20f;  // no sum of layer l passes it
+  float b = 0x1p20f;  // no input of layer l passes it
+  float lost = 0.0f;  // what the inputs' sums may be off by for parts that were lost
   bool in_range = true;
 #pragma unroll 1
   for (int l = 0; l < NL; ++l) {
-    b = 64.0f * __uint_as_float(mx[l]) * b + __uint_as_float(mx[kMaxLayers + l]);
+    const float w = __uint_as_float(mx[l]);
+    lost = 64.0f * (w * (lost + 0x1p-122f) + (b + 1.0f) * 0x1p-122f);
+    b = 64.0f * w * b + __uint_as_float(mx[kMaxLayers + l]);
     in_range = in_range && b < 0x1p120f;
   }
-  return __builtin_amdgcn_readfirstlane(in_range ? 1 : 0) != 0;
+  return __builtin_amdgcn_readfirstlane(in_range && lost <= 0x1p-30f ? 1 : 0) != 0;
 }
 
 // max(z, 0), 0 for NaN (see relu() of the training kernels).

@@ -698,3 +698,31 @@ def test_f32_unused_levels_add_nothing(dims, n):
     out = ntc.decode(lat, mlp, torch.from_numpy(uv).cuda(), compute="f32").cpu().numpy()
     ref = O.decode(O.Latents(lat_np, shift=shift), O.Mlp(Ws, bs), uv)
     assert np.all(np.abs(out - ref) <= TOL_F32_REL * np.abs(ref))
+
+
+@pytest.mark.parametrize("fmt", ["bc1", "f32"])
+@pytest.mark.parametrize("layer", [0, 1])
+@pytest.mark.parametrize("exponent", [-40, -80, -100, -110, -113, -118, -122, 110])
+def test_f32_small_numbers(exponent, layer, fmt):
+    """FP32 decode of networks with one hidden layer scaled by a power of two
+    and the next by its reciprocal (exactly): the result is that of the plain
+    network to FP32 accuracy, also where parts of the split numbers fall
+    below the normal range. FP32 chains of 64 terms stay well below 2e-6."""
+    ntc = _ntc()
+    rng = np.random.default_rng(63)
+    sizes = [(64, 64), (32, 32), (16, 16), (8, 8)]
+    lat_np = I.bc1_pyramid(rng, sizes) if fmt == "bc1" else I.f32_pyramid(rng, sizes)
+    Ws, bs = I.xavier_mlp(rng, (14, 64, 64, 64, 8), bias="normal")
+    # weights of 12 significant bits, so that scaling into the subnormal range is exact
+    Ws = [np.ldexp(np.rint(np.ldexp(w, 12)), -12).astype(np.float32) for w in Ws]
+    bs = [np.ldexp(np.rint(np.ldexp(b, 12)), -12).astype(np.float32) for b in bs]
+    uv = rng.random((40000, 2)).astype(np.float32)
+    olat, omlp = _oracle_case(lat_np, Ws, bs, I.PAPER_SHIFT)
+    ref = O.decode(olat, omlp, uv)
+    Ws[layer], bs[layer] = np.ldexp(Ws[layer], exponent), np.ldexp(bs[layer], exponent)
+    Ws[layer + 1] = np.ldexp(Ws[layer + 1], -exponent)
+    lat, mlp = _gpu_case(lat_np, Ws, bs, I.PAPER_SHIFT)
+    out = ntc.decode(lat, mlp, torch.from_numpy(uv).cuda(), compute="f32").cpu().numpy()
+    err = np.max(np.abs(out - ref) / ref)
+    print(f"[small numbers] {fmt} layer {layer} 2^{exponent}: {err:.1e}", flush=True)
+    assert err <= 2e-6
