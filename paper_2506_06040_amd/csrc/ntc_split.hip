@@ -30,7 +30,13 @@
 // |v| <= 2^20 decide per network (split_setup), the coordinates (and float
 // latents) per pixel; what fails is decoded by a
 // second walk with the FP32 matrix instructions (exact_pixels), pixel by
-// pixel, so that a pixel's result does not depend on its neighbours.
+// pixel, so that a pixel's result does not depend on its neighbours. That walk
+// takes the weights as they stand from LDS, where they replace their parts once
+// the workgroup has finished the first walk: no weight is fetched per tile (a
+// load per product from the image: 1172 in place of 279 us, and registers that
+// the first walk spilled). It is bound by the FP32 products, 112 of 64 cycles per
+// 32 pixels of 14-64-64-8; 1920x1080 pixels of networks that are all out of range:
+// 14-64-64-8 279 us, 14-64-64-64-8 405 (plain FMAs, a lane per pixel: 424, 697).
 #include <hip/hip_runtime.h>
 
 #include "ntc_device.hpp"
@@ -53,8 +59,8 @@ struct SplitMap {
   // byte offsets
   static constexpr int oBias = 3 * F * 1024;             // hidden layers 1 .. NL - 2: [l][m][h][16] floats
   static constexpr int oOut = oBias + (NL - 2) * MT * 128;  // output biases [16]
-  static constexpr int oMax = oOut + 64;                 // largest |weight|, |bias| per layer [2 kMaxLayers]
-  static constexpr int oTab = (oMax + 4 * 2 * kMaxLayers + 15) & ~15;
+  static constexpr int oMax = oOut + 64;                 // largest |weight|, |bias| per layer [2 kMaxLayers], second walk needed
+  static constexpr int oTab = (oMax + 4 * (2 * kMaxLayers + 1) + 15) & ~15;
   static constexpr int oRec = oTab + LevelTab::kLevelEntries * 16;
   static constexpr int oStage = oRec + kSplitWaves * 2 * kMaxLevels * 16;
   static constexpr int total(bool bc1) { return oStage + (bc1 ? kSplitWaves * kSplitStage * 8 : 0); }
@@ -96,33 +102,15 @@ __device__ __forceinline__ float split_weight(const DecodeArgs &a, const uint8_t
   return r == row && (col == -2 || c == col) ? w : 0.0f;
 }
 
-// Weights, biases and level table into LDS; returns whether the network's
-// numbers stay in range: no sum of any layer passes 2^120, and the parts lost
-// below the normal range (with products below it, at most 2^-122 per operand)
-// change no output's pre-activation by more than 2^-30, a 64th of what FP32
-// rounds an output by. (Latents are at most 1 in BC1 images, float latents are
-// checked with the coordinates.) Rolled loops: a short batch pays for
-// every instruction line fetched.
-template <int HP, int NL>
-__device__ __forceinline__ bool split_setup(const DecodeArgs &a, uint8_t *lds, int tid) {
+// Weights into LDS, a fragment (layer l, rows 32 m .., K-step c) per wavefront
+// at a time: the three parts of each, [part][fragment][lane], or as they stand
+// (EXACT), [fragment][half][lane]. note(l, largest magnitude in this lane).
+template <int HP, int NL, bool EXACT, class NOTE>
+__device__ __forceinline__ void fill_weights(const DecodeArgs &a, uint8_t *lds, int tid, NOTE &&note) {
   using M = SplitMap<HP, NL>;
   constexpr int kHidden = M::MT * M::KS;
   const int lane = tid & 63, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  unsigned *mx = reinterpret_cast<unsigned *>(lds + M::oMax);
-  if (tid < 2 * kMaxLayers) mx[tid] = 0u;
-  __syncthreads();
-  if (tid < kMaxLevels) {  // LevelTab::fill, a lane per level
-    const LevelArgs &L = a.lat.lv[tid];
-    const unsigned long long p = (unsigned long long)L.bc1;
-    f32x4 *tab = reinterpret_cast<f32x4 *>(lds + M::oTab) + 3 * tid;
-    tab[0] = (f32x4){L.fw, L.sx - 0.5f, (float)(L.w - 2), __int_as_float(L.w)};
-    tab[1] = (f32x4){L.fh, L.sy - 0.5f, (float)(L.h - 2), __int_as_float(L.h)};
-    tab[2] = (f32x4){__uint_as_float((unsigned)p), __uint_as_float((unsigned)(p >> 32)), __int_as_float(L.bw), 0.0f};
-  }
-  auto note = [&](unsigned *m, float big) {  // NaN counts as infinite
-    atomicMax(m, big == big ? __float_as_uint(big) : 0x7f800000u);
-  };
   u32x4_t *w = reinterpret_cast<u32x4_t *>(lds);
 #pragma unroll 1
   for (int f = wave; f < M::F; f += kSplitWaves) {
@@ -146,6 +134,12 @@ __device__ __forceinline__ bool split_setup(const DecodeArgs &a, uint8_t *lds, i
         for (int e = 0; e < 4; ++e) v[4 * j + e] = row < a.lay.rows_pad[l] && col + 8 * j < cols ? q[e] : 0.0f;
       }
     }
+    if constexpr (EXACT) {
+      f32x4 *q = reinterpret_cast<f32x4 *>(lds) + 2 * f * 64 + lane;
+      q[0] = (f32x4){v[0], v[1], v[2], v[3]};
+      q[64] = (f32x4){v[4], v[5], v[6], v[7]};
+      continue;
+    }
 #pragma unroll
     for (int e = 0; e < 8; ++e) big = fmaxf(big, v[e] == v[e] ? fabsf(v[e]) : __builtin_inff());
 #pragma unroll
@@ -158,8 +152,35 @@ __device__ __forceinline__ bool split_setup(const DecodeArgs &a, uint8_t *lds, i
       }
       w[(p * M::F + f) * 64 + lane] = __builtin_bit_cast(u32x4_t, q);
     }
-    note(mx + l, big);
+    note(l, big);
   }
+}
+
+// Weights, biases and level table into LDS; returns whether the network's
+// numbers stay in range: no sum of any layer passes 2^120, and the parts lost
+// below the normal range (with products below it, at most 2^-122 per operand)
+// change no output's pre-activation by more than 2^-30, a 64th of what FP32
+// rounds an output by. (Latents are at most 1 in BC1 images, float latents are
+// checked with the coordinates.) Rolled loops: a short batch pays for
+// every instruction line fetched.
+template <int HP, int NL>
+__device__ __forceinline__ bool split_setup(const DecodeArgs &a, uint8_t *lds, int tid) {
+  using M = SplitMap<HP, NL>;
+  unsigned *mx = reinterpret_cast<unsigned *>(lds + M::oMax);
+  if (tid <= 2 * kMaxLayers) mx[tid] = 0u;
+  __syncthreads();
+  if (tid < kMaxLevels) {  // LevelTab::fill, a lane per level
+    const LevelArgs &L = a.lat.lv[tid];
+    const unsigned long long p = (unsigned long long)L.bc1;
+    f32x4 *tab = reinterpret_cast<f32x4 *>(lds + M::oTab) + 3 * tid;
+    tab[0] = (f32x4){L.fw, L.sx - 0.5f, (float)(L.w - 2), __int_as_float(L.w)};
+    tab[1] = (f32x4){L.fh, L.sy - 0.5f, (float)(L.h - 2), __int_as_float(L.h)};
+    tab[2] = (f32x4){__uint_as_float((unsigned)p), __uint_as_float((unsigned)(p >> 32)), __int_as_float(L.bw), 0.0f};
+  }
+  auto note = [&](unsigned *m, float big) {  // NaN counts as infinite
+    atomicMax(m, big == big ? __float_as_uint(big) : 0x7f800000u);
+  };
+  fill_weights<HP, NL, false>(a, lds, tid, [&](int l, float big) { note(mx + l, big); });
   // biases (the first layer's is a weight of the constant 1)
 #pragma unroll 1
   for (int i = tid; i < (NL - 2) * M::MT * 32 + 16; i += 64 * kSplitWaves) {
@@ -325,39 +346,51 @@ __device__ __forceinline__ void split_store(const DecodeArgs &a, const f32x16 &z
   }
 }
 
-// Pre-activations of the outputs of one 32-pixel tile by FP32 matrix
-// products on the image as it stands: any numbers, no speed.
+// Pre-activations of the outputs of one 32-pixel tile by FP32 matrix products
+// (w: this lane's weights as they stand, bias: the hidden layers' biases).
+// 32x32x2 products take K-element e of a fragment as the split ones do.
 template <int HP, int NL>
-__device__ __forceinline__ void exact_tile(const DecodeArgs &a, const float (&x)[8], f32x16 &z, int salt) {
-  constexpr int MT = (HP + 31) / 32;
-  // through an opaque offset, or the weights would be held in registers across tiles
-  const uint8_t *packed = a.packed + opaque_zero(salt);
-  const int lane = threadIdx.x & 63, h = lane >> 5, c32 = lane & 31;
+__device__ __forceinline__ void exact_tile(const f32x4 *w, const float *bias, int h, const float (&x)[8], f32x16 &z) {
+  using M = SplitMap<HP, NL>;
+  constexpr int MT = M::MT, KS = M::KS;
   f32x16 in[MT], out[MT];
   const f32x16 zero = {};
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     out[m] = zero;
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      out[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-          split_weight(a, packed, 0, 32 * m + c32, split_col(a.lat.n_levels, 0, 0, h, e)), x[e], out[m], 0, 0, 0);
+    for (int j = 0; j < 2; ++j) {
+      const f32x4 q = w[(2 * M::frag(0, m, 0) + j) * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(q[e], x[4 * j + e], out[m], 0, 0, 0);
+    }
   }
 #pragma unroll 1
   for (int l = 1; l < NL; ++l) {
+    const f32x4 *wl = w + 2 * (MT + (l - 1) * MT * KS) * 64;
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) in[m][i] = fmaxf(out[m][i], 0.0f);
+      for (int i = 0; i < 16; ++i) in[m][i] = relu_f32(out[m][i]);
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
+      if (m > 0 && l == NL - 1) break;
+      out[m] = zero;
+      if (l < NL - 1) {
+        const f32x4 *b = reinterpret_cast<const f32x4 *>(bias + ((l - 1) * MT + m) * 32 + 16 * h);
+        const f32x4 b0 = b[0], b1 = b[1], b2 = b[2], b3 = b[3];
+        out[m] = (f32x16){b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3],
+                          b2[0], b2[1], b2[2], b2[3], b3[0], b3[1], b3[2], b3[3]};
+      }
 #pragma unroll
-      for (int i = 0; i < 16; ++i) out[m][i] = l < NL - 1 ? split_weight(a, packed, l, 32 * m + 8 * (i >> 2) + 4 * h + (i & 3), -2) : 0.0f;
+      for (int c = 0; c < KS; ++c)
 #pragma unroll
-      for (int s = 0; s < 16 * MT; ++s)
-        out[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(
-            split_weight(a, packed, l, 32 * m + c32, 32 * (s >> 4) + 8 * ((s & 15) >> 2) + 4 * h + (s & 3)),
-            in[s >> 4][s & 15], out[m], 0, 0, 0);
+        for (int j = 0; j < 2; ++j) {
+          const f32x4 q = wl[(2 * (m * KS + c) + j) * 64];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            out[m] = __builtin_amdgcn_mfma_f32_32x32x2f32(q[e], in[c >> 1][8 * (c & 1) + 4 * j + e], out[m], 0, 0, 0);
+        }
     }
   }
   z = out[0];
@@ -377,25 +410,28 @@ __device__ __forceinline__ bool may_split(const float (&xl)[8], const float (&xh
 // A second walk over the samples: pixels that may not be split (all: every
 // pixel). Wavefront `it0` of `step` takes the 64-pixel tiles of its spans.
 template <int HP, int NL, bool BC1>
-__device__ __forceinline__ void exact_pixels(const DecodeArgs &a, const f32x4 *ltab, const float *ob, int64_t it0,
+__device__ __forceinline__ void exact_pixels(const DecodeArgs &a, const uint8_t *lds, const float *ob, int64_t it0,
                                              int64_t step, int spx, bool all) {
+  using M = SplitMap<HP, NL>;
+  const f32x4 *ltab = reinterpret_cast<const f32x4 *>(lds + M::oTab);
   const int lane = threadIdx.x & 63, h = lane >> 5, c32 = lane & 31;
   const int per = spx / 64;
+  auto load_uv = [&](int64_t it) { return a.uv[min(it * 64 + lane, a.n - 1)]; };
+  float2 uv_next = load_uv(it0 * per);
+  int64_t next;
 #pragma unroll 1
-  for (int64_t it = it0 * per; it * 64 < a.n; it += it % per == per - 1 ? (step - 1) * per + 1 : 1) {
-    const float2 uv = a.uv[min(it * 64 + lane, a.n - 1)];
+  for (int64_t it = it0 * per; it * 64 < a.n; it = next) {
+    next = it + (it % per == per - 1 ? (step - 1) * per + 1 : 1);
+    const float2 uv = uv_next;
+    uv_next = load_uv(next);
     float xl[8], xh[8];
     float3 c[kMaxLevels];
     if constexpr (BC1) {
-#pragma unroll 1
+#pragma unroll
       for (int k = 0; k < kMaxLevels; ++k) {
         TabLevel L;
         L.read(ltab, k);
-        const float3 t = direct_level(L, uv.x, uv.y, a.lat.address);
-        if (k == 0) c[0] = t;
-        if (k == 1) c[1] = t;
-        if (k == 2) c[2] = t;
-        if (k == 3) c[3] = t;
+        c[k] = direct_level(L, uv.x, uv.y, a.lat.address);
       }
     } else {
       grid_levels(a.lat, uv.x, uv.y, c);
@@ -414,7 +450,9 @@ __device__ __forceinline__ void exact_pixels(const DecodeArgs &a, const f32x4 *l
 #pragma unroll 1
     for (int t = 0; t < 2; ++t) {
       f32x16 z;
-      exact_tile<HP, NL>(a, x0, z, 2 * (int)it + t);
+      const int off = opaque_zero(2 * (int)it + t);  // nothing of LDS is held in registers across tiles
+      exact_tile<HP, NL>(reinterpret_cast<const f32x4 *>(lds) + lane + off,
+                         reinterpret_cast<const float *>(lds + M::oBias) + off, h, x0, z);
       split_store(a, z, ob, it * 64 + 32 * t + c32, h, (any >> (32 * t + c32)) & 1);
 #pragma unroll
       for (int e = 0; e < 8; ++e) x0[e] = x1[e];
@@ -588,7 +626,14 @@ void decode_split_kernel(DecodeArgs a) {
       }
     }
   }
-  if (!bounded || left) exact_pixels<HP, NL, BC1>(a, ltab, ob, it0, step, spx, !bounded);
+  // the second walk, with the weights as they stand in the place of their parts
+  unsigned *again = reinterpret_cast<unsigned *>(lds + M::oMax) + 2 * kMaxLayers;
+  if (left) *again = 1u;
+  __syncthreads();
+  if (bounded && *again == 0u) return;
+  fill_weights<HP, NL, true>(a, lds, tid, [](int, float) {});
+  __syncthreads();
+  if (!bounded || left) exact_pixels<HP, NL, BC1>(a, lds, ob, it0, step, spx, !bounded);
 }
 
 template <int HP, bool BC1>

@@ -726,3 +726,43 @@ def test_f32_small_numbers(exponent, layer, fmt):
     err = np.max(np.abs(out - ref) / ref)
     print(f"[small numbers] {fmt} layer {layer} 2^{exponent}: {err:.1e}", flush=True)
     assert err <= 2e-6
+
+
+@pytest.mark.parametrize("dims,address", [((14, 16, 9), "clamp"), ((11, 32, 32, 3), "wrap"), ((14, 64, 16), "clamp"),
+                                          ((8, 32, 32, 32, 32, 5), "wrap"), ((5, 16, 16, 16, 4), "clamp"),
+                                          ((14, 64, 64, 64, 64, 8), "clamp")])
+@pytest.mark.parametrize("fmt", ["bc1", "f32"])
+@pytest.mark.parametrize("whole", [True, False])
+def test_f32_second_walk_shapes(dims, address, fmt, whole):
+    """The walk over pixels that may not be split, over every width and depth
+    class and the tails of its tiles: all pixels (a hidden layer scaled by
+    2^122, the next by its reciprocal) and single pixels with far
+    coordinates; nothing is written past the end."""
+    ntc = _ntc()
+    rng = np.random.default_rng(len(dims) * 100 + dims[1])
+    levels = (dims[0] - 2) // 3
+    sizes = [(64, 32), (32, 32), (16, 8), (8, 8)][:levels]
+    lat_np = I.bc1_pyramid(rng, sizes) if fmt == "bc1" else I.f32_pyramid(rng, sizes)
+    Ws, bs = I.xavier_mlp(rng, dims, bias="normal")
+    if whole:
+        Ws[0], bs[0], Ws[1] = np.ldexp(Ws[0], 122), np.ldexp(bs[0], 122), np.ldexp(Ws[1], -122)
+    else:
+        Ws[0][:, -2:] *= np.float32(1e-7)
+    shift = I.PAPER_SHIFT[:levels]
+    lat, mlp = _gpu_case(lat_np, Ws, bs, shift, address)
+    # short batches of float latents with up to four layers take another kernel
+    ns = (1, 65, 4099) if fmt == "bc1" or len(dims) > 5 else (2 ** 21 // dims[1] + 65,)
+    for n in ns:
+        uv = (rng.random((n, 2)) * 1.4 - 0.2).astype(np.float32)
+        if not whole:
+            uv[rng.choice(n, max(1, n // 50), replace=False)] += np.float32(2.0 ** 21)
+        # sampling positions are limited to 2^24 texels: under wrap addressing such a pixel's texels are not the oracle's
+        near = np.abs(uv).max(1) < 2.0 ** 20 if address == "wrap" else np.ones(n, bool)
+        buf = torch.full((n + 4, dims[-1]), 7.0, device="cuda")
+        ntc.decode(lat, mlp, torch.from_numpy(uv).cuda(), compute="f32", out=buf[:n])
+        out = buf.cpu().numpy()
+        assert np.all(out[n:] == 7.0)
+        olat, omlp = _oracle_case(lat_np, Ws, bs, shift, address)
+        ref = O.decode(olat, omlp, uv)
+        assert np.isfinite(out).all()
+        assert np.all((np.abs(out[:n] - ref) <= TOL_F32_REL * np.abs(ref))[near]), n
