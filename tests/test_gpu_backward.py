@@ -357,3 +357,32 @@ def test_non_finite_uv_float_latents(levels, address, n):
         _close(f"db{l}", gb[l], rb[l])
     for k in range(levels):
         _close(f"dlat{k}", gl[k], rl[k])
+
+
+@pytest.mark.parametrize("dims", [(8, 16, 16, 3), (8, 64, 64, 64, 8)])  # eight and four wavefronts a workgroup
+@pytest.mark.parametrize("n", [1, 32, 33, 32 * 256, 32 * 256 + 1, 32 * 1024 + 1, 32 * 2048 + 1])
+def test_backward_rows_of_partial_sums(dims, n):
+    """Gradients where the 32-sample steps begin to fill another wavefront, the
+    next of every workgroup, or a second step of one. Every hidden unit is
+    active (small weights, biases of 3), so no ReLU decision depends on
+    rounding."""
+    rng = np.random.default_rng(n + len(dims))
+    lat_np = I.f32_pyramid(rng, [(64, 64), (32, 32)])
+    Ws, bs = I.xavier_mlp(rng, dims, bias="normal")
+    Ws = [(0.05 * w).astype(np.float32) for w in Ws]
+    bs = [b + np.float32(3) for b in bs[:-1]] + [bs[-1]]
+    uv = rng.random((n, 2)).astype(np.float32)
+    olat, omlp = O.Latents(lat_np, shift=I.PAPER_SHIFT[:2]), O.Mlp(Ws, bs)
+    top, low = np.abs(Ws[0]).sum(1) + bs[0], bs[0] - np.abs(Ws[0]).sum(1)
+    for w, b in zip(Ws[1:-1], bs[1:-1]):
+        assert low.min() > 0
+        top, low = b + np.abs(w) @ top, b - np.abs(w) @ top
+    assert low.min() > 0
+    g = rng.standard_normal((n, dims[-1])).astype(np.float32).astype(np.float64)
+    gW, gb, gl = _gpu_direct(lat_np, Ws, bs, uv, g, I.PAPER_SHIFT[:2])
+    oW, ob, ol = O.backward(olat, omlp, uv, g)
+    for l in range(len(Ws)):
+        _close(f"dW{l}", gW[l], oW[l])
+        _close(f"db{l}", gb[l], ob[l])
+    for k in range(2):
+        _close(f"dlat{k}", gl[k], ol[k])
