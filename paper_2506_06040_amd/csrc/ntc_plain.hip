@@ -515,10 +515,10 @@ __global__ void fill_f32_kernel(float *p, int64_t n, float v) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
-// Zeroes several arrays in one launch: thread i of the grid takes every
-// grid-th element of each.
+// Zeroes several arrays in one launch. Memory bound: every workgroup takes a
+// piece of each array in one run (201 and 805 MB: 25.7 and 148 us, 7.8 and 5.4
+// TB/s; the whole grid striding over an array 32.1 and 179; up to 17 MB the same).
 __global__ __launch_bounds__(256) void zero_kernel(ZeroArgs z) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
 #pragma unroll
   for (int k = 0; k < kMaxZero; ++k) {
@@ -527,7 +527,8 @@ __global__ __launch_bounds__(256) void zero_kernel(ZeroArgs z) {
     const int64_t head = min((int64_t)(((16 - ((uintptr_t)p & 15)) & 15) >> 2), z.n[k]);
     const int64_t n4 = (z.n[k] - head) >> 2;
     float4 *q = reinterpret_cast<float4 *>(p + head);
-    for (int64_t i = t; i < n4; i += stride) q[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const int64_t per = (n4 + gridDim.x - 1) / gridDim.x, end = min(per * (blockIdx.x + 1), n4);
+    for (int64_t i = per * blockIdx.x + threadIdx.x; i < end; i += 256) q[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (t < head) p[t] = 0.0f;
     if (t < z.n[k] - head - 4 * n4) p[head + 4 * n4 + t] = 0.0f;
   }

@@ -386,3 +386,37 @@ def test_backward_rows_of_partial_sums(dims, n):
         _close(f"db{l}", gb[l], ob[l])
     for k in range(2):
         _close(f"dlat{k}", gl[k], ol[k])
+
+
+@pytest.mark.parametrize("sizes", [[(4, 4), (5, 7)], [(333, 1001), (64, 64), (4, 5)], [(2048, 1024)]])
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+def test_backward_clears_latent_gradients(sizes, offset):
+    """Latent gradients start from zero whatever the arrays held, at any
+    alignment of four bytes, and nothing beside them is written."""
+    import ctypes
+    from paper_2506_06040_amd import _abi as A
+    ntc = _ntc()
+    rng = np.random.default_rng(offset)
+    lat_np = I.f32_pyramid(rng, sizes)
+    lat = ntc.Latents(lat_np, shift=I.PAPER_SHIFT[:len(sizes)])
+    mlp = ntc.Mlp(*I.xavier_mlp(rng, (3 * len(sizes) + 2, 16, 4), bias="normal"))
+    uv = torch.full((1, 2), 0.5, device="cuda")
+    go = torch.ones((1, 4), device="cuda")
+    gW, gb = [torch.empty_like(w) for w in mlp.W], [torch.empty_like(b) for b in mlp.b]
+    bufs = [torch.full((3 * w * h + 8,), 7.0, device="cuda") for w, h in sizes]
+    need = ntc.api.backward_workspace_size(lat, mlp, 1)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+
+    def ptrs(ts, off=0):
+        return (ctypes.c_void_p * len(ts))(*[t.data_ptr() + 4 * off for t in ts])
+
+    A.check(A.lib().ntc_decode_backward(ctypes.byref(lat.c), ctypes.byref(mlp.c), uv.data_ptr(), 1, go.data_ptr(),
+                                        ptrs(gW), ptrs(gb), ptrs(bufs, offset), ws.data_ptr(), need,
+                                        torch.cuda.current_stream().cuda_stream))
+    _, _, ref = ntc.decode_backward(lat, mlp, uv, go)
+    for b, r, (w, h) in zip(bufs, ref, sizes):
+        got = b.cpu().numpy()
+        n = 3 * w * h
+        assert np.all(got[:offset] == 7.0) and np.all(got[offset + n:] == 7.0)
+        assert np.count_nonzero(got[offset:offset + n]) <= 12
+        assert np.array_equal(got[offset:offset + n], r.cpu().numpy().reshape(-1))
