@@ -199,8 +199,9 @@ ntc_status ntc_decode_backward_workspace(const ntc_latents *lat, const ntc_mlp *
  * recomputed per tile of 32 samples with FP32 matrix-core products. Weight
  * gradients are summed per wavefront in FP32 and across wavefronts in FP64
  * (the same inputs give the same bits); latent gradients are accumulated
- * per spatial bin of samples in LDS and then with FP32 atomics (their
- * summation order is not deterministic). workspace [device, 256-byte
+ * per spatial bin of samples in LDS and then with FP32 atomics, those of
+ * sparse bins with atomics alone (their summation order is not
+ * deterministic). workspace [device, 256-byte
  * aligned] of at least ntc_decode_backward_workspace bytes (it grows with
  * n: 68 bytes per sample with four levels, plus the partial sums). */
 ntc_status ntc_decode_backward(const ntc_latents *lat, const ntc_mlp *mlp, const float *uv, int64_t n,

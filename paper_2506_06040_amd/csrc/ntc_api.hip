@@ -597,6 +597,7 @@ ntc_status ntc_decode_backward(const ntc_latents *lat, const ntc_mlp *mlp, const
   a.n_runs = lay.n_runs;
   a.bin_lds = lay.bin_lds;
   a.bin_cells = lay.bin_cells;
+  a.bin_sparse = lay.bin_sparse;
   hipError_t e = launch_backward(a, s, grad_W, grad_b, hs);
   if (e != hipSuccess) return hip_fail(e, "backward launch");
   return ok();

@@ -15,7 +15,8 @@
 // samples of a bin, spreads dx onto the four bilinear taps of every level,
 // adding into LDS copies of the texels the bin's samples can reach, and then
 // adds those windows to the latent gradients with one atomic per texel and
-// channel (taps outside a window go straight to a global atomic).
+// channel (taps outside a window, and the samples of sparse bins, go straight to
+// global atomics).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -48,13 +49,19 @@ constexpr int kBwdMaxGroups = 256;
 // one per SIMD for their gradient accumulators.
 static constexpr int backward_waves(int mt, int n_layers) { return mt == 2 && n_layers > 3 ? 4 : 8; }
 
-// Chunk c goes to wavefront c / groups of workgroup c % groups, so that a short
-// batch spreads over the compute units first: two wavefronts of a SIMD halve
+// A short batch spreads over the compute units first: two wavefronts of a SIMD halve
 // each other's matrix rate (forward of 300 to 4096 samples: 14-64-64-64-8 16.3 ->
 // 11.3 us, 14-64-64-8 11.3 -> 8.2).
 static int backward_groups(int64_t n) {
   const int64_t chunks = (n + kBwdChunk - 1) / kBwdChunk;
   return (int)(chunks > kBwdMaxGroups ? kBwdMaxGroups : (chunks < 1 ? 1 : chunks));
+}
+
+// First chunk of a wavefront of this workgroup, and its row of partial sums:
+// neighbours in one workgroup where every wavefront has one (`full`; rows 256
+// apart cost 3.5 us for 14-64-64-8), over the workgroups first where not.
+__device__ __forceinline__ int first_chunk(bool full, int waves, int wave) {
+  return full ? (int)blockIdx.x * waves + wave : wave * (int)gridDim.x + (int)blockIdx.x;
 }
 
 // Wavefronts that have a chunk, each of which writes a row of partial sums.
@@ -81,8 +88,17 @@ constexpr int kBinRun = 1120;              // samples of a bin taken by one work
 constexpr int kAccThreads = 512;           // threads of that workgroup
 constexpr int kBinWindowFloats = 12288;    // largest LDS of a bin's texel window (48 KB)
 constexpr int kBinWindowCells = 4096;      // largest number of cells of one window
+// Samples of a bin up to which they are added straight to the gradients (a run
+// costs its window, whatever it holds), and the mean per bin up to which bins are
+// looked at for that (the look costs 10 us at 2^18 samples). Random samples, whole
+// backward in us, runs alone / with sparse bins: 2048^2..256^2 levels, mean of 4 per
+// bin 231 / 108, 16 269 / 206, 32 314 / 316, 64 396 / 402; 1024^2..128^2, 16 90 / 79,
+// 32 93 / 97; up to 16 and 48 samples in place of 32: 226 and 205 in place of 206.
+constexpr int kBinSparse = 32;
+constexpr int kBinSparseMean = 24;
 
-// LDS of one bin: floats and cells of its largest texel window.
+// LDS of one bin: floats and cells of its largest texel window that fits (none
+// where no level's does).
 // A bin spans 2^shift cells of level 0 (one more at a clamped edge, which
 // also has a cell before the first texel), and on the others at most its
 // scaled size and four cells (the ends, the shift, the edge); a window has
@@ -95,11 +111,13 @@ static void bin_window(const LatArgs &lat, int shift, int &floats, int &cells) {
       return std::min<int64_t>(c, n + 1);
     };
     const int64_t nc = axis(lat.lv[k].w, lat.lv[0].w), nr = axis(lat.lv[k].h, lat.lv[0].h);
-    most_f = std::max(most_f, 3 * (nc + 1) * (nr + 1));
-    most_c = std::max(most_c, nc * nr);
+    const int64_t f = 3 * (nc + 1) * (nr + 1), c = nc * nr;
+    if (f > kBinWindowFloats || c > kBinWindowCells) continue;
+    most_f = std::max(most_f, f);
+    most_c = std::max(most_c, c);
   }
-  floats = (int)std::min<int64_t>(most_f, kBinWindowFloats);
-  cells = (int)std::min<int64_t>(most_c, kBinWindowCells);
+  floats = (int)most_f;
+  cells = (int)most_c;
 }
 
 static size_t align256(size_t v) { return (v + 255) / 256 * 256; }
@@ -112,16 +130,20 @@ BwdLayout backward_layout(const MlpShape &s, const LatArgs &lat, int64_t n) {
   L.dx_stride = (L.n_feat + 2 + 3) & ~3;
   // Sample indices of the bins are int32, and so is the end of the run that
   // follows the last one of a bin holding all samples.
+  int t = kBinShift;
   if (n <= INT32_MAX - kBinRun) {
-    int t = kBinShift;
     const int w = lat.lv[0].w, h = lat.lv[0].h;
     auto bins = [&](int len) { return (len + (1 << t) - 1) >> t; };
     while ((int64_t)bins(w) * bins(h) > kMaxBins) ++t;
-    L.bin_shift = t;
-    L.bins_x = bins(w);
-    L.n_bins = bins(w) * bins(h);
-    L.n_runs = L.n_bins + (int32_t)(n / kBinRun);
     bin_window(lat, t, L.bin_lds, L.bin_cells);
+    const int64_t n_bins = (int64_t)bins(w) * bins(h);
+    L.bin_sparse = n <= n_bins * kBinSparseMean ? kBinSparse : 0;
+    if (L.bin_cells > 0 && n > L.bin_sparse) {
+      L.bin_shift = t;
+      L.bins_x = bins(w);
+      L.n_bins = (int32_t)n_bins;
+      L.n_runs = (int32_t)(std::min<int64_t>(n_bins, n / (L.bin_sparse + 1)) + n / kBinRun);
+    }
   }
   size_t off = 0;
   L.wpart_off = off;
@@ -532,7 +554,7 @@ void backward_mfma_kernel(BackwardArgs a) {
 
   const int64_t n_chunks = (a.n + kBwdChunk - 1) / kBwdChunk;
   const int64_t stride = (int64_t)gridDim.x * M::waves;
-  const int64_t first = (int64_t)wave * gridDim.x + blockIdx.x;
+  const int64_t first = first_chunk(a.n_blocks == M::waves * (int)gridDim.x, M::waves, wave);
   auto load_uv = [&](int64_t chunk) {
     const int64_t smp = chunk * kBwdChunk + c32;
     return a.uv[smp < a.n ? smp : a.n - 1];
@@ -711,8 +733,9 @@ void backward_mfma_kernel(BackwardArgs a) {
   }
 
   // ---- this wavefront's partial sums (parameters in unpadded order)
-  if (first >= n_chunks) return;
-  float *part = a.wpart + first * a.n_params;
+  const int part_row = first_chunk(a.n_blocks == M::waves * (int)gridDim.x, M::waves, wave);
+  if (part_row >= a.n_blocks) return;
+  float *part = a.wpart + (int64_t)part_row * a.n_params;
   int off = 0;
   {
     const int f = slot_feature(c16 >> 1, c16 & 1, n_levels);
@@ -818,7 +841,7 @@ __device__ __forceinline__ int2 scan1024(int2 v, int2 *part) {
 }
 
 // Exclusive prefix sum of the counts into the cursors, and the work list of
-// bin_accum_kernel: every bin's samples cut into runs of at most kBinRun,
+// bin_accum_kernel: the samples of every bin of more than bin_sparse cut into runs of at most kBinRun,
 // as (bin, first sample, end) with the run count in front. One workgroup of
 // 1024 threads.
 __global__ __launch_bounds__(1024) void bin_scan_kernel(BackwardArgs a) {
@@ -829,7 +852,7 @@ __global__ __launch_bounds__(1024) void bin_scan_kernel(BackwardArgs a) {
   int2 sum = make_int2(0, 0);
   for (int k = k0; k < k1; ++k) {
     sum.x += a.bin_count[k];
-    sum.y += (a.bin_count[k] + kBinRun - 1) / kBinRun;
+    sum.y += a.bin_count[k] > a.bin_sparse ? (a.bin_count[k] + kBinRun - 1) / kBinRun : 0;
   }
   int2 run = scan1024(sum, part);
   if (t == 1023) a.runs[0] = make_int4(run.y, 0, 0, 0);
@@ -838,7 +861,7 @@ __global__ __launch_bounds__(1024) void bin_scan_kernel(BackwardArgs a) {
   for (int k = k0; k < k1; ++k) {
     const int32_t c = a.bin_count[k];
     a.bin_cursor[k] = run.x;
-    for (int i = 0; i < c; i += kBinRun) a.runs[1 + run.y++] = make_int4(k, run.x + i, run.x + min(i + kBinRun, c), 0);
+    for (int i = 0; i < c && c > a.bin_sparse; i += kBinRun) a.runs[1 + run.y++] = make_int4(k, run.x + i, run.x + min(i + kBinRun, c), 0);
     run.x += c;
   }
 }
@@ -922,6 +945,10 @@ __device__ __forceinline__ int window_coord(int i, int c0, int n, float rn, int 
 // latency: a chain of about ten short steps between barriers, some 1 us each,
 // which is why the levels are workgroups of their own (one workgroup taking
 // all levels in turn: 90 us in place of the 57 below).
+// A level whose windows do not fit (bins of 64 texels and more, levels finer than
+// level 0) has no window: its taps are global atomics, four lanes a sample, and
+// it does not size the LDS (2^14 samples on 4096^2..512^2 levels: backward 485 -> 234
+// us, 112 with its sparse bins added sample by sample).
 // 2^20 random samples on 1024^2..128^2 levels: 57 us (241 us with the LDS
 // float atomics); 2^18 samples, wrapped 512^2..64^2 levels: 23 us (660 us
 // with a global atomic per tap and channel).
@@ -959,8 +986,37 @@ __device__ __forceinline__ void cell_add(float *p, int tc, const float (&g)[4][3
     for (int ch = 0; ch < 3; ++ch) p[3 * ((q & 1) + (q >> 1) * tc) + ch] += g[q][ch];
 }
 
-__global__ __launch_bounds__(kAccThreads) void bin_accum_kernel(BackwardArgs a) {
+// Adds tap q of sample s on level k straight to the gradients.
+__device__ __forceinline__ void tap_direct(const BackwardArgs &a, int64_t s, int k, int q) {
+  const LevelArgs &L = a.lat.lv[k];
+  const float *g = a.dx + s * a.dx_stride;
+  const Cell c = cell_of(L, make_float2(g[a.n_feat], g[a.n_feat + 1]));
+  const int i = address_coord(c.ix + (q & 1), L.w, a.lat.address);
+  const int j = address_coord(c.iy + (q >> 1), L.h, a.lat.address);
+  const float w = ((q & 1) ? c.fx : 1.0f - c.fx) * ((q >> 1) ? c.fy : 1.0f - c.fy);
+  float *p = a.grad_lat[k] + ((int64_t)j * L.w + i) * 3;
+#pragma unroll
+  for (int ch = 0; ch < 3; ++ch) unsafeAtomicAdd(p + ch, w * g[3 * k + ch]);
+}
+
+// Samples of sparse bins: 16 lanes each, a level and tap per lane, global
+// atomics.
+constexpr int kDirectSamples = kAccThreads / 16;
+__device__ __forceinline__ void sparse_samples(const BackwardArgs &a, int64_t block) {
+  const int64_t s = block * kDirectSamples + (threadIdx.x >> 4);
+  const int k = (int)(threadIdx.x >> 2) & 3, q = (int)threadIdx.x & 3;
+  if (s >= a.n || k >= a.lat.n_levels) return;
+  if (a.n_bins > 0 && a.bin_count[bin_of(a, a.uv[s])] > a.bin_sparse) return;
+  tap_direct(a, s, k, q);
+}
+
+template <bool SPARSE>
+__global__ __launch_bounds__(kAccThreads) void bin_accum_kernel(BackwardArgs a, unsigned run_blocks) {
   constexpr int kT = kAccThreads, kWaves = kT / 64;
+  if (SPARSE && blockIdx.x >= run_blocks) {
+    sparse_samples(a, blockIdx.x - run_blocks);
+    return;
+  }
   extern __shared__ float win[];
   float *pay = win + a.bin_lds;                                   // [5][kBinRun]
   int32_t *cnt = reinterpret_cast<int32_t *>(pay + 5 * kBinRun);  // [bin_cells + 1]
@@ -1022,24 +1078,18 @@ __global__ __launch_bounds__(kAccThreads) void bin_accum_kernel(BackwardArgs a) 
       direct = true;
     }
   }
+  if (!fits) {  // no window: every tap goes straight to the gradients
+    for (int i = tid; i < 4 * m; i += kT) tap_direct(a, a.perm[run.y + (i >> 2)], k, i & 3);
+    return;
+  }
   if (direct) {  // samples outside the window go straight to the gradients
-#pragma unroll 1
-    for (int j = tid; j < m; j += kT) {
-      const float *g = a.dx + (int64_t)a.perm[run.y + j] * a.dx_stride;
-      const Cell c = cell_of(L, make_float2(g[a.n_feat], g[a.n_feat + 1]));
-      const int col = window_coord(c.ix, wk.c0, lw, rw, mode), row = window_coord(c.iy, wk.r0, lh, rh, mode);
-      if (fits && (unsigned)col < (unsigned)wk.nc && (unsigned)row < (unsigned)wk.nr) continue;
-#pragma unroll 1
-      for (int q = 0; q < 4; ++q) {
-        const int ti = address_coord(c.ix + (q & 1), lw, mode), tj = address_coord(c.iy + (q >> 1), lh, mode);
-        const float w = ((q & 1) ? c.fx : 1.0f - c.fx) * ((q >> 1) ? c.fy : 1.0f - c.fy);
-        float *p = a.grad_lat[k] + ((int64_t)tj * lw + ti) * 3;
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) unsafeAtomicAdd(p + ch, w * g[3 * k + ch]);
-      }
+    for (int i = 0; i < kPer; ++i) {
+      if (cell[i] >= 0 || tid + kT * i >= m) continue;
+#pragma unroll 1
+      for (int q = 0; q < 4; ++q) tap_direct(a, a.perm[run.y + tid + kT * i], k, q);
     }
   }
-  if (!fits) return;
   __syncthreads();
   // exclusive scan of the counts
   const int per = (cells + kT - 1) / kT;
@@ -1130,31 +1180,9 @@ __global__ __launch_bounds__(kAccThreads) void bin_accum_kernel(BackwardArgs a) 
   }
 }
 
-// Too many samples for the bins' 32-bit indices: every tap of every sample is
-// a global atomic.
-__global__ __launch_bounds__(256) void scatter_direct_kernel(BackwardArgs a) {
-  const int64_t s = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (s >= a.n) return;
-  const float2 uv = a.uv[s];
-  const float *g = a.dx + s * a.dx_stride;
-#pragma unroll
-  for (int k = 0; k < kMaxLevels; ++k) {
-    if (k < a.lat.n_levels) {
-      const LevelArgs &L = a.lat.lv[k];
-      const Taps t = tap_coords(uv.x, uv.y, L, a.lat.address);
-      const float gx = 1.0f - t.fx, gy = 1.0f - t.fy;
-      const float w[4] = {gx * gy, t.fx * gy, gx * t.fy, t.fx * t.fy};
-      const int ii[4] = {t.i0, t.i1, t.i0, t.i1};
-      const int jj[4] = {t.j0, t.j0, t.j1, t.j1};
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        float *p = a.grad_lat[k] + ((int64_t)jj[q] * L.w + ii[q]) * 3;
-        unsafeAtomicAdd(p + 0, w[q] * g[3 * k]);
-        unsafeAtomicAdd(p + 1, w[q] * g[3 * k + 1]);
-        unsafeAtomicAdd(p + 2, w[q] * g[3 * k + 2]);
-      }
-    }
-  }
+// No bins: every sample's taps are global atomics.
+__global__ __launch_bounds__(kAccThreads) void scatter_direct_kernel(BackwardArgs a) {
+  for (int64_t b = blockIdx.x; b * kDirectSamples < a.n; b += gridDim.x) sparse_samples(a, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -1192,7 +1220,7 @@ void forward_mfma_kernel(DecodeArgs a) {
 
   const int64_t n_chunks = (a.n + kBwdChunk - 1) / kBwdChunk;
   const int64_t stride = (int64_t)gridDim.x * kFwdWaves;
-  const int64_t first = (int64_t)wave * gridDim.x + blockIdx.x;
+  const int64_t first = first_chunk(n_chunks >= stride, kFwdWaves, wave);
   auto load_uv = [&](int64_t chunk) {
     const int64_t smp = chunk * kBwdChunk + c32;
     return a.uv[smp < a.n ? smp : a.n - 1];
@@ -1307,8 +1335,9 @@ hipError_t launch_backward(const BackwardArgs &a, const MlpShape &s, float *cons
   hipLaunchKernelGGL(reduce_f64_kernel, dim3((a.n_params + 63) / 64), dim3(64 * kReduceWaves), 0, st, r);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // latent gradients from dx
+  const unsigned sparse = (unsigned)std::min<int64_t>((a.n + kDirectSamples - 1) / kDirectSamples, 1 << 20);
   if (a.n_bins == 0) {
-    hipLaunchKernelGGL(scatter_direct_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(scatter_direct_kernel, dim3(sparse), dim3(kAccThreads), 0, st, a);
     return hipGetLastError();
   }
   const unsigned grid = (unsigned)((a.n + kBinSamplesPerBlock - 1) / kBinSamplesPerBlock);
@@ -1318,8 +1347,12 @@ hipError_t launch_backward(const BackwardArgs &a, const MlpShape &s, float *cons
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(bin_scatter_kernel, dim3(grid), dim3(kBinThreads), 2 * a.n_bins * sizeof(int32_t), st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(bin_accum_kernel, dim3((unsigned)((a.n_runs + 7) / 8 * 8 * a.lat.n_levels)), dim3(kAccThreads),
-                     (size_t)(a.bin_lds + 5 * kBinRun + a.bin_cells + 1) * sizeof(float), st, a);
+  const unsigned run_blocks = (unsigned)((a.n_runs + 7) / 8 * 8 * a.lat.n_levels);
+  const size_t lds = (size_t)(a.bin_lds + 5 * kBinRun + a.bin_cells + 1) * sizeof(float);
+  if (a.bin_sparse > 0)
+    hipLaunchKernelGGL(bin_accum_kernel<true>, dim3(run_blocks + sparse), dim3(kAccThreads), lds, st, a, run_blocks);
+  else
+    hipLaunchKernelGGL(bin_accum_kernel<false>, dim3(run_blocks), dim3(kAccThreads), lds, st, a, run_blocks);
   return hipGetLastError();
 }
 

@@ -99,8 +99,9 @@ constexpr int kMaxZero = kMaxLevels + 1;
 struct ZeroArgs {
   float *p[kMaxZero];
   int64_t n[kMaxZero];
+  int64_t per[kMaxZero];  // groups of four of a workgroup (set by launch_zero)
 };
-hipError_t launch_zero(const ZeroArgs &z, hipStream_t st);
+hipError_t launch_zero(ZeroArgs z, hipStream_t st);
 
 // Backward. Workspace (256-byte aligned sections): per-block FP32 partial
 // sums of the weight gradients, the feature gradient dL/dx of every sample,
@@ -109,9 +110,10 @@ hipError_t launch_zero(const ZeroArgs &z, hipStream_t st);
 struct BwdLayout {
   int32_t n_blocks, n_params, n_feat;
   int32_t dx_stride;                  // floats of a row of dx (a multiple of 4)
-  int32_t bin_shift, bins_x, n_bins;  // bins of 2^bin_shift level-0 texels; n_bins = 0: no binning (too many samples for int32 runs)
+  int32_t bin_shift, bins_x, n_bins;  // bins of 2^bin_shift level-0 texels; n_bins = 0: no binning
   int32_t n_runs;                     // largest number of sample runs of the bins
   int32_t bin_lds, bin_cells;         // LDS floats and cells of a bin's largest texel window
+  int32_t bin_sparse;                 // bins of at most this many samples are not taken in runs
   size_t wpart_off, dx_off, count_off, cursor_off, perm_off, runs_off, total;
 };
 BwdLayout backward_layout(const MlpShape &s, const LatArgs &lat, int64_t n);
@@ -133,7 +135,7 @@ struct BackwardArgs {
   int32_t n_params;
   int32_t n_blocks;
   int32_t n_feat, dx_stride;
-  int32_t bin_shift, bins_x, n_bins, n_runs, bin_lds, bin_cells;
+  int32_t bin_shift, bins_x, n_bins, n_runs, bin_lds, bin_cells, bin_sparse;
   int32_t dims[kMaxLayers + 1];
   int32_t n_layers;
 };

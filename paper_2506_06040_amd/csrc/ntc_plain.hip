@@ -527,17 +527,18 @@ __global__ __launch_bounds__(256) void zero_kernel(ZeroArgs z) {
     const int64_t head = min((int64_t)(((16 - ((uintptr_t)p & 15)) & 15) >> 2), z.n[k]);
     const int64_t n4 = (z.n[k] - head) >> 2;
     float4 *q = reinterpret_cast<float4 *>(p + head);
-    const int64_t per = (n4 + gridDim.x - 1) / gridDim.x, end = min(per * (blockIdx.x + 1), n4);
-    for (int64_t i = per * blockIdx.x + threadIdx.x; i < end; i += 256) q[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    const int64_t end = min(z.per[k] * (blockIdx.x + 1), n4);
+    for (int64_t i = z.per[k] * blockIdx.x + threadIdx.x; i < end; i += 256) q[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     if (t < head) p[t] = 0.0f;
     if (t < z.n[k] - head - 4 * n4) p[head + 4 * n4 + t] = 0.0f;
   }
 }
 
-hipError_t launch_zero(const ZeroArgs &z, hipStream_t st) {
+hipError_t launch_zero(ZeroArgs z, hipStream_t st) {
   int64_t n = 1;
   for (int k = 0; k < kMaxZero; ++k) n = std::max(n, z.n[k]);
   const int64_t blocks = std::min<int64_t>((n / 4 + 255) / 256 + 1, 2048);
+  for (int k = 0; k < kMaxZero; ++k) z.per[k] = (z.n[k] / 4 + blocks - 1) / blocks;
   hipLaunchKernelGGL(zero_kernel, dim3((unsigned)blocks), dim3(256), 0, st, z);
   return hipGetLastError();
 }

@@ -420,3 +420,45 @@ def test_backward_clears_latent_gradients(sizes, offset):
         assert np.all(got[:offset] == 7.0) and np.all(got[offset + n:] == 7.0)
         assert np.count_nonzero(got[offset:offset + n]) <= 12
         assert np.array_equal(got[offset:offset + n], r.cpu().numpy().reshape(-1))
+
+
+@pytest.mark.parametrize("sizes,address,n,hot", [
+    ([(128, 96), (64, 48), (32, 24), (16, 12)], "clamp", 250, (33, 32, 31, 120)),  # runs and single samples, levels alike
+    ([(128, 96), (64, 48), (32, 24)], "wrap", 288, (33, 32, 100)),                 # the largest mean that is looked at
+    ([(128, 96), (64, 48), (32, 24)], "wrap", 289, (33, 32, 100)),                 # the next: runs alone
+    ([(128, 96), (64, 48)], "clamp", 32, ()),                                      # no bin can be more than sparse
+    ([(128, 96), (64, 48)], "clamp", 33, (33,)),                                   # one can
+    ([(2304, 2112)], "wrap", 3000, (1200,)),                                       # no level's window fits
+    ([(64, 64), (512, 640)], "clamp", 2500, (1200, 40)),                           # one level's does not
+])
+def test_backward_sparse_bins(sizes, address, n, hot):
+    """Latent gradients of bins on both sides of the limit under which samples
+    are added one by one, together with bins taken in runs, and of levels
+    without a window. hot: samples in bins of their own, the rest anywhere.
+    Every hidden unit is active for every sample, so no ReLU decision depends
+    on rounding."""
+    rng = np.random.default_rng(n + len(hot))
+    lat_np = I.f32_pyramid(rng, sizes)
+    Ws, bs = I.xavier_mlp(rng, (3 * len(sizes) + 2, 16, 16, 3), bias="normal")
+    Ws = [(0.1 * w).astype(np.float32) for w in Ws]
+    bs = [bs[0] + np.float32(3), bs[1] + np.float32(3), bs[2]]
+    top = np.abs(Ws[0]).sum(1)
+    assert np.all(bs[0] - top > 0) and np.all(bs[1] - np.abs(Ws[1]) @ (bs[0] + top) > 0)
+    w0, h0 = sizes[0]
+    uv = rng.random((n, 2))
+    at = 0
+    for i, m in enumerate(hot):  # texels 33 .. 60 of a column of bins, then of the next column
+        x, y = 32 * (1 + i % 3) + 1, 32 * (i // 3) + 1
+        uv[at:at + m] = (np.array([x, y]) + 1 + rng.random((m, 2)) * 27) / np.array([w0, h0])
+        at += m
+    # the others away from those bins (rows from 64 on, or anywhere on a single large level)
+    if h0 == 96:
+        uv[at:, 1] = (65 + rng.random(n - at) * 30) / h0
+    uv = uv[rng.permutation(n)].astype(np.float32)
+    shift = I.PAPER_SHIFT[:len(sizes)]
+    olat = O.Latents(lat_np, shift=shift, address=O.WRAP if address == "wrap" else O.CLAMP)
+    g = rng.standard_normal((n, 3)).astype(np.float32).astype(np.float64)
+    _, _, gl = _gpu_direct(lat_np, Ws, bs, uv, g, shift, address=address)
+    _, _, ol = O.backward(olat, O.Mlp(Ws, bs), uv, g)
+    for k in range(len(sizes)):
+        _close(f"sparse dlat{k}", gl[k], ol[k])
