@@ -21,9 +21,13 @@ constexpr int kWrapTiles = 2;  // 64-pixel tiles per span with wrap addressing (
 // One kernel per address mode: the wrapped one is rolled and small, the
 // clamped one keeps the registers and the schedule that it has alone (both
 // with staging in one kernel: 1 to 3% slower clamped decodes). The mode stays a
-// run-time value in the clamped spans of FP32 texels (as a constant: 1% slower).
+// run-time value in the clamped spans of FP32 texels (as a constant: 1% slower)
+// and of the 64-wide FP16 networks of four and more layers (as a constant the
+// five-layer ones spill 28 registers in place of 17, the four-layer ones 1 in place
+// of none; 14-64-64-64-64-8: 2048x1024 pixels 68 -> 65 us, 1501x999 54 -> 52).
 template <class P, int HID, int NL, int VEC4, int ADDR>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PER_SIMD, NTC_WAVES_PER_SIMD))) void decode_mfma_kernel(DecodeArgs a) {
+  constexpr int kMode = P::kF16Tex && !(HID == 64 && NL >= 4) ? kClampOnly : kEitherMode;
   constexpr int ST = ADDR == kWrapOnly ? kWrapTiles : span_tiles_for(HID, NL, P::kF16Tex);
   constexpr int SPX = 64 * ST;
   extern __shared__ f32x4 smem[];
@@ -60,7 +64,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
     if constexpr (ADDR == kWrapOnly)
       decode_span_wrap<P, HID, NL, ST, VEC4>(a, it * SPX, a.n, stage, bias, ltab, W, uvs, next, a.n, obuf);
     else
-      decode_span<P, HID, NL, ST, VEC4, false, P::kF16Tex ? kClampOnly : kEitherMode>(a, it * SPX, a.n, stage, bias, ltab, W, uvs, next, a.n, obuf);
+      decode_span<P, HID, NL, ST, VEC4, false, kMode>(a, it * SPX, a.n, stage, bias, ltab, W, uvs, next, a.n, obuf);
   }
 }
 
