@@ -281,7 +281,7 @@ ntc_status ntc_decode(const ntc_latents *lat, const ntc_mlp *mlp, int32_t comput
   else if (compute == NTC_F32)
     e = launch_decode_f32(a, s, cus, (hipStream_t)stream);
   else
-    e = launch_decode_mfma(a, s, compute, cus * waves_per_cu, (hipStream_t)stream);
+    e = launch_decode_mfma(a, s, compute, cus, waves_per_cu, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "decode launch");
   return ok();
 }

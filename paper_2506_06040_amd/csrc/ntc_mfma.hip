@@ -10,6 +10,8 @@
 // described in ntc_mfma_tile.hpp.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "ntc_device.hpp"
 #include "ntc_internal.hpp"
 #include "ntc_mfma_tile.hpp"
@@ -111,8 +113,9 @@ int decode_span_tiles(int hid, int n_layers, int compute) {
   return span_tiles_for(hid, n_layers, compute == 1 ? PrecF16::kF16Tex : (compute == 2 ? PrecBF16::kF16Tex : PrecF8::kF16Tex));
 }
 
-hipError_t launch_decode_mfma(const DecodeArgs &a, const MlpShape &s, int compute, int grid_waves, hipStream_t st) {
-  int64_t grid = grid_waves;
+hipError_t launch_decode_mfma(const DecodeArgs &a, const MlpShape &s, int compute, int n_cus, int waves_per_cu,
+                              hipStream_t st) {
+  int64_t grid = (int64_t)n_cus * waves_per_cu;
   const int span = a.lat.address == 0 ? decode_span_tiles(s.hid, s.n_layers, compute) : kWrapTiles;
   // Spans of one tile where long ones would leave more than half of the first
   // or of the second pass of the waves empty. Measured (us, one tile / spans
@@ -125,9 +128,13 @@ hipError_t launch_decode_mfma(const DecodeArgs &a, const MlpShape &s, int comput
   //   22 / 31, 6 19 / 16 and 21 / 31, 8 24 / 16, 9 26 / 27 and 29 / 56,
   //   10 29 / 42, 11.4 35 / 42 (odd).
   if (a.lat.address == 0) {
-    const int64_t pass = span * grid, rest = a.n_tiles % pass;
+    // a pass is that of the waves that run at once, however many are to be
+    // launched (1024x1024 pixels of 14-32-32-8, 32 per compute unit: long spans 16 us,
+    // one tile 27)
+    const int64_t waves = std::min(grid, (int64_t)n_cus * 4 * NTC_WAVES_PER_SIMD);
+    const int64_t pass = span * waves, rest = a.n_tiles % pass;
     if (a.n_tiles < 2 * pass && rest > 0 && 2 * rest <= pass)
-      return launch_decode_short(a, s, compute, (int)(a.n_tiles < grid ? a.n_tiles : grid), st);
+      return launch_decode_short(a, s, compute, (int)std::min(a.n_tiles, waves), st);
   }
   const int64_t n_iter = (a.n_tiles + span - 1) / span;
   // a multiple of 8 for the XCD numbering: rounded up where the spans are

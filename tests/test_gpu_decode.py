@@ -766,3 +766,21 @@ def test_f32_second_walk_shapes(dims, address, fmt, whole):
         ref = O.decode(olat, omlp, uv)
         assert np.isfinite(out).all()
         assert np.all((np.abs(out[:n] - ref) <= TOL_F32_REL * np.abs(ref))[near]), n
+
+
+@pytest.mark.parametrize("compute,dims", [("f16", (14, 64, 64, 64, 8)), ("f16", (14, 32, 32, 5)), ("bf16", (14, 16, 9))])
+def test_launched_waves_do_not_change_results(compute, dims):
+    """waves_per_cu decides the launch and the span length, not the result."""
+    ntc = _ntc()
+    rng = np.random.default_rng(dims[-1])
+    lat = ntc.Latents(I.bc1_pyramid(rng, [(64, 64), (32, 32), (16, 16), (8, 8)]), shift=I.PAPER_SHIFT)
+    mlp = ntc.Mlp(*I.xavier_mlp(rng, dims, bias="normal"))
+    packed = ntc.pack(mlp, compute)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    for tiles in (8 * cus + 1, 8 * cus * 4, 8 * cus * 5 + 3, 8 * cus * 9 + 1):
+        i = torch.arange(64 * tiles - 7, device="cuda")
+        uv = torch.stack([(i % 1013) / 1013.0, (i // 1013) / 1200.0], 1).float().contiguous()
+        ref = ntc.decode(lat, mlp, uv, compute=compute, packed=packed)
+        for w in (1, 3, 16, 64, 1024):
+            got = ntc.decode(lat, mlp, uv, compute=compute, packed=packed, cfg=ntc.tile_cfg(waves_per_cu=w))
+            assert torch.equal(ref, got), (tiles, w)
