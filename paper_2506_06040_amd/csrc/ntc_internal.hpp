@@ -87,7 +87,8 @@ hipError_t launch_calibrate(const DecodeArgs &a, const MlpShape &s, float *act_a
 hipError_t launch_decode_mfma(const DecodeArgs &a, const MlpShape &s, int compute, int n_cus, int waves_per_cu,
                               hipStream_t st);
 // Short batches of it (ntc_short.hip).
-hipError_t launch_decode_short(const DecodeArgs &a, const MlpShape &s, int compute, int grid, hipStream_t st);
+hipError_t launch_decode_short(const DecodeArgs &a, const MlpShape &s, int compute, int grid, bool with_head,
+                               hipStream_t st);
 // FP32 decode on the BF16 matrix cores with split operands (ntc_split.hip).
 hipError_t launch_decode_f32(DecodeArgs a, const MlpShape &s, int n_cus, hipStream_t st);
 // FP32 decode of float latents on the FP32 matrix cores (up to 4 layers).

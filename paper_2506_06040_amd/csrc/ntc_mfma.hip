@@ -117,24 +117,32 @@ hipError_t launch_decode_mfma(const DecodeArgs &a, const MlpShape &s, int comput
                               hipStream_t st) {
   int64_t grid = (int64_t)n_cus * waves_per_cu;
   const int span = a.lat.address == 0 ? decode_span_tiles(s.hid, s.n_layers, compute) : kWrapTiles;
-  // Spans of one tile where long ones would leave more than half of the first
-  // or of the second pass of the waves empty. Measured (us, one tile / spans
-  // of 4 or 8; FP16, pixels in rows of whole spans, and in odd rows, whose
-  // wrapped spans seldom fit the staging region); tiles a wave:
-  //   14-64-64-64-8, spans of 4: 1/2 8 / 13 to 15, 2 12 / 13, 2 1/2 14 / 13
-  //   and 15 to 22, 4 18 / 14 and 20 to 23, 5 24 / 28 and 29 / 34, 6 26 / 26
-  //   and 27 / 40, 7 29 / 27 and 29 / 38, 10 38 / 37;
-  //   14-32-32-8, spans of 8: 1/2 7 / 19, 2 10 / 21, 3 15 / 21, 5 16 / 16 and
-  //   22 / 31, 6 19 / 16 and 21 / 31, 8 24 / 16, 9 26 / 27 and 29 / 56,
-  //   10 29 / 42, 11.4 35 / 42 (odd).
+  // Batches that long spans would fill badly: tiles (64 pixels) one by one, all
+  // of them or after a long span per wave. A pass is that of the waves that run at
+  // once, however many are to be launched (1024x1024 pixels of 14-32-32-8, 32 per
+  // compute unit: long spans 16 us, one tile 27). The lines are where the two meet
+  // for pixels in 8x8 tiles or rows of whole spans, which long spans favour (for odd
+  // rows and random order they lie further up); the less matrix work a tile has, the
+  // more of its time is what a long span shares. Measured (us, long spans / tiles /
+  // one long span, then tiles; pixels in 8x8 tiles, then in odd rows), tiles a wave:
+  //   spans of 8, FP16: 14-16-8      3: 14/14 21/14; 4: 13/15 21/16;
+  //                     14-32-32-8   1/2: 20/8 20/8; 3.5: 13/13 21/13; 4: 13/14 21/15;
+  //       8.25: 22/24/16 40/28/31; 9: 25/26/18 56/29/34; 10: 25/28/20 56/33/37;
+  //       12: 25/33/25 56/37/42; 14: 25/38/30 57/42/48;
+  //                     14-64-64-8   4: 16/16 24/17; 9: 33/30/24 64/33/38;
+  //   spans of 4, FP16: 14-64-64-64-8  1/2: 15/9 15/8; 2: 13/12 16/13; 3: 15/15
+  //       20/16; 5: 25/21 33/22; 6: 24/24 33/26; 7: 25/27 33/30;
+  //               BF16: 14-64-8      5: 19/19 27/20; 6: 19/22 27/23;
+  //               E4M3: 14-64-64-8   5: 23/20 30/21; 6: 22/23 30/24.
+  // BF16 and E4M3 meet at the same lines, within half a tile.
   if (a.lat.address == 0) {
-    // a pass is that of the waves that run at once, however many are to be
-    // launched (1024x1024 pixels of 14-32-32-8, 32 per compute unit: long spans 16 us,
-    // one tile 27)
     const int64_t waves = std::min(grid, (int64_t)n_cus * 4 * NTC_WAVES_PER_SIMD);
     const int64_t pass = span * waves, rest = a.n_tiles % pass;
-    if (a.n_tiles < 2 * pass && rest > 0 && 2 * rest <= pass)
-      return launch_decode_short(a, s, compute, (int)std::min(a.n_tiles, waves), st);
+    // the line in sixteenths of a pass (three 64-wide layers have spans of 4 with FP32 texels only)
+    const int line = s.n_layers == 2 ? 6 : (s.hid < 64 || (span == NTC_SPAN_TILES && s.n_layers == 3) ? 7 : 8);
+    const bool head = span == NTC_SPAN_TILES_SMALL && a.n_tiles > pass;
+    if (a.n_tiles < 2 * pass && rest > 0 && (head ? 2 * rest <= pass : 16 * rest <= line * pass))
+      return launch_decode_short(a, s, compute, (int)std::min(a.n_tiles, waves), head, st);
   }
   const int64_t n_iter = (a.n_tiles + span - 1) / span;
   // a multiple of 8 for the XCD numbering: rounded up where the spans are

@@ -1,5 +1,6 @@
 // Short batches of the matrix-core decode: the same walk as ntc_mfma.hip with
-// spans of one 64-pixel tile.
+// spans of one 64-pixel tile, for the networks with spans of 8 tiles after one
+// long span per wavefront where a batch fills them once and a little more.
 //
 // A batch of fewer spans of 256 or 512 pixels than the card has wavefronts to
 // run leaves SIMDs idle, and its time is that of one wavefront working through
@@ -14,7 +15,8 @@
 namespace ntc {
 
 template <class P, int HID, int NL, int VEC4>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PER_SIMD, NTC_WAVES_PER_SIMD))) void decode_short_kernel(DecodeArgs a) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PER_SIMD, NTC_WAVES_PER_SIMD))) void decode_short_kernel(DecodeArgs a, int head) {
+  constexpr int ST = span_tiles_for(HID, NL, P::kF16Tex);
   extern __shared__ f32x4 smem[];
   f32x4 *stage = smem;
   f32x4 *bias = smem + a.stage_cap;
@@ -30,10 +32,26 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
   W.ready();
   __syncthreads();
 
+  // head: the first ST tiles of every wavefront are one span, of neighbours on an
+  // XCD as in ntc_mfma.hip
+  int64_t it = blockIdx.x;
+  if constexpr (ST == NTC_SPAN_TILES_SMALL) {
+    if (head) {
+      const int nb = gridDim.x;
+      const int vb = (nb & 7) == 0 ? (blockIdx.x & 7) * (nb >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+      SpanUv<ST> uvs;
+      uvs.load(a.uv, (int64_t)vb * (64 * ST), a.n);
+      uvs.ready();
+      decode_span<P, HID, NL, ST, VEC4, false, P::kF16Tex ? kClampOnly : kEitherMode>(
+          a, (int64_t)vb * (64 * ST), a.n, stage, bias, ltab, W, uvs, -1, a.n, obuf);
+      it += (int64_t)ST * nb;
+    }
+  }
+  if (it >= a.n_tiles) return;
   SpanUv<1> uvs;
-  uvs.load(a.uv, (int64_t)blockIdx.x * 64, a.n);
+  uvs.load(a.uv, it * 64, a.n);
   uvs.ready();
-  for (int64_t it = blockIdx.x; it < a.n_tiles; it += gridDim.x) {
+  for (; it < a.n_tiles; it += gridDim.x) {
     const int64_t nx = it + gridDim.x;
     decode_span<P, HID, NL, 1, VEC4, false, kClampOnly>(a, it * 64, a.n, stage, bias, ltab, W, uvs,
                                                         nx < a.n_tiles ? nx * 64 : -1, a.n, obuf);
@@ -41,43 +59,46 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
 }
 
 template <class P, int HID, int VEC4>
-static hipError_t launch_short_v(const DecodeArgs &a, int n_layers, int grid, hipStream_t st) {
+static hipError_t launch_short_v(const DecodeArgs &a, int n_layers, int grid, int head, hipStream_t st) {
   const size_t lds =
       (size_t)(a.stage_cap + BiasLds<HID, 5>::kCount + LevelTab::kCount + (VEC4 ? 0 : 32 * 16 / 4)) * sizeof(f32x4);
   switch (n_layers) {
-    case 2: hipLaunchKernelGGL((decode_short_kernel<P, HID, 2, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
-    case 3: hipLaunchKernelGGL((decode_short_kernel<P, HID, 3, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
-    case 4: hipLaunchKernelGGL((decode_short_kernel<P, HID, 4, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
-    case 5: hipLaunchKernelGGL((decode_short_kernel<P, HID, 5, VEC4>), dim3(grid), dim3(64), lds, st, a); break;
+    case 2: hipLaunchKernelGGL((decode_short_kernel<P, HID, 2, VEC4>), dim3(grid), dim3(64), lds, st, a, head); break;
+    case 3: hipLaunchKernelGGL((decode_short_kernel<P, HID, 3, VEC4>), dim3(grid), dim3(64), lds, st, a, head); break;
+    case 4: hipLaunchKernelGGL((decode_short_kernel<P, HID, 4, VEC4>), dim3(grid), dim3(64), lds, st, a, head); break;
+    case 5: hipLaunchKernelGGL((decode_short_kernel<P, HID, 5, VEC4>), dim3(grid), dim3(64), lds, st, a, head); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
 template <class P, int HID>
-static hipError_t launch_short_hid(const DecodeArgs &a, int n_layers, int grid, hipStream_t st) {
+static hipError_t launch_short_hid(const DecodeArgs &a, int n_layers, int grid, int head, hipStream_t st) {
   switch (out_class(a.n_out)) {
-    case kOut4: return launch_short_v<P, HID, kOut4>(a, n_layers, grid, st);
-    case kOut4x2: return launch_short_v<P, HID, kOut4x2>(a, n_layers, grid, st);
-    default: return launch_short_v<P, HID, kOutAny>(a, n_layers, grid, st);
+    case kOut4: return launch_short_v<P, HID, kOut4>(a, n_layers, grid, head, st);
+    case kOut4x2: return launch_short_v<P, HID, kOut4x2>(a, n_layers, grid, head, st);
+    default: return launch_short_v<P, HID, kOutAny>(a, n_layers, grid, head, st);
   }
 }
 
 template <class P>
-static hipError_t launch_short_prec(const DecodeArgs &a, const MlpShape &s, int grid, hipStream_t st) {
+static hipError_t launch_short_prec(const DecodeArgs &a, const MlpShape &s, int grid, int head, hipStream_t st) {
   switch (s.hid) {
-    case 16: return launch_short_hid<P, 16>(a, s.n_layers, grid, st);
-    case 32: return launch_short_hid<P, 32>(a, s.n_layers, grid, st);
-    case 64: return launch_short_hid<P, 64>(a, s.n_layers, grid, st);
+    case 16: return launch_short_hid<P, 16>(a, s.n_layers, grid, head, st);
+    case 32: return launch_short_hid<P, 32>(a, s.n_layers, grid, head, st);
+    case 64: return launch_short_hid<P, 64>(a, s.n_layers, grid, head, st);
     default: return hipErrorInvalidValue;
   }
 }
 
-// Clamp addressing; 1 <= grid <= a.n_tiles.
-hipError_t launch_decode_short(const DecodeArgs &a, const MlpShape &s, int compute, int grid, hipStream_t st) {
-  if (compute == 1) return launch_short_prec<PrecF16>(a, s, grid, st);
-  if (compute == 2) return launch_short_prec<PrecBF16>(a, s, grid, st);
-  if (compute == 3) return launch_short_prec<PrecF8>(a, s, grid, st);
+// Clamp addressing; 1 <= grid <= a.n_tiles. head: a span of 8 tiles per wavefront
+// first (networks with such spans, grid * 8 <= a.n_tiles).
+hipError_t launch_decode_short(const DecodeArgs &a, const MlpShape &s, int compute, int grid, bool with_head,
+                               hipStream_t st) {
+  const int head = with_head;
+  if (compute == 1) return launch_short_prec<PrecF16>(a, s, grid, head, st);
+  if (compute == 2) return launch_short_prec<PrecBF16>(a, s, grid, head, st);
+  if (compute == 3) return launch_short_prec<PrecF8>(a, s, grid, head, st);
   return hipErrorInvalidValue;
 }
 

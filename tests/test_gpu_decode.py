@@ -784,3 +784,31 @@ def test_launched_waves_do_not_change_results(compute, dims):
         for w in (1, 3, 16, 64, 1024):
             got = ntc.decode(lat, mlp, uv, compute=compute, packed=packed, cfg=ntc.tile_cfg(waves_per_cu=w))
             assert torch.equal(ref, got), (tiles, w)
+
+
+# One long span per wave, then single tiles: first tile after the spans, last
+# waves without one, two per wave, a last tile that is not full, and the batch
+# sizes next to where that begins and ends.
+@pytest.mark.parametrize("compute,dims", [("f16", (14, 16, 8)), ("f16", (14, 64, 64, 5)), ("bf16", (14, 32, 32, 9)),
+                                          ("fp8", (14, 32, 32, 32, 32, 8))])
+def test_long_span_then_tiles_equals_long(compute, dims):
+    ntc = _ntc()
+    rng = np.random.default_rng(dims[-1])
+    lat = ntc.Latents(I.bc1_pyramid(rng, [(64, 64), (32, 32), (16, 16), (8, 8)]), shift=I.PAPER_SHIFT)
+    mlp = ntc.Mlp(*I.xavier_mlp(rng, dims, bias="normal"))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    amax = ntc.calibrate_fp8(lat, mlp, torch.rand((65536, 2), device="cuda")) if compute == "fp8" else None
+    packed = ntc.pack(mlp, compute, act_amax=amax)
+    for wpc in (1, 8):
+        waves = cus * wpc
+        n = 64 * 8 * waves * 16 + 5  # long spans alone
+        i = torch.arange(n, device="cuda")
+        uv = torch.stack([(i % 1013) / 1013.0, (i // 1013) / (n / 1013.0)], 1).float().contiguous()
+        cfg = ntc.tile_cfg(waves_per_cu=wpc)
+        whole = ntc.decode(lat, mlp, uv, compute=compute, packed=packed, cfg=cfg)
+        for px in (64 * 8 * waves, 64 * 8 * waves + 1, 64 * (9 * waves - 1) + 63, 64 * 9 * waves, 64 * 9 * waves + 64,
+                   64 * 12 * waves, 64 * 12 * waves + 1):
+            buf = torch.full((px + 4, dims[-1]), 7.0, device="cuda")
+            ntc.decode(lat, mlp, uv[:px], compute=compute, packed=packed, cfg=cfg, out=buf[:px])
+            assert torch.equal(whole[:px], buf[:px]), (wpc, px)
+            assert bool((buf[px:] == 7.0).all())
