@@ -614,13 +614,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
             }
             return sample_direct16<kEitherMode>(mip_level(f, k, m), tap_coord(x), tap_coord(y), 0);
           };
-          // every lane reads mip m_lo (alone, or blended with m_lo + 1), those
-          // are staged and every position is an interior one: the samples
-          // take the regions' values as wave-uniform parameters (the same
-          // values as smp gives them)
-          const bool at_lo = s0 && in0 && __builtin_amdgcn_ballot_w64(sel[k].m0 != mlo) == 0;
+          // every lane reads mip m_lo and it is staged, alone or blended with
+          // m_lo + 1 (then every position is an interior one of both): the
+          // samples take the regions' values as wave-uniform parameters (the
+          // same values as smp gives them)
+          const bool at_lo = s0 && __builtin_amdgcn_ballot_w64(sel[k].m0 != mlo) == 0;
           const bool lo_only = at_lo && __builtin_amdgcn_ballot_w64(sel[k].t > 0.0f) == 0;
-          const bool pair = at_lo && s1 && in1;
+          const bool pair = at_lo && in0 && s1 && in1;
+          auto smp_lo_any = [&](float x, float y) -> Tex16 {
+            return staged_sample(stage, fw0, fh0, cx, cy, kbw0, kb0, x, y, in0);
+          };
           auto smp_lo = [&](float x, float y) -> Tex16 {
             return staged_sample(stage, fw0, fh0, cx, cy, kbw0, kb0, x, y, true);
           };
@@ -629,14 +632,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
           };
           if constexpr (FILTER == 1) {
             if (lo_only)
-              c16[k] = smp_lo(u, v);
+              c16[k] = smp_lo_any(u, v);
             else if (pair)
               c16[k] = blend16(smp_lo(u, v), smp_hi(u, v), sel[k].t);
             else
               c16[k] = trilinear16(sel[k], u, v, smp);
           } else {
             if (lo_only)
-              c = filter_level_staged<false>(sel[k], u, v, smp_lo, smp_hi);
+              c = filter_level_staged<false>(sel[k], u, v, smp_lo_any, smp_hi);
             else if (pair)
               c = filter_level_staged<true>(sel[k], u, v, smp_lo, smp_hi);
             else
