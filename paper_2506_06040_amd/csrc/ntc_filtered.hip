@@ -615,33 +615,37 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
             return sample_direct16<kEitherMode>(mip_level(f, k, m), tap_coord(x), tap_coord(y), 0);
           };
           // every lane reads mip m_lo and it is staged, alone or blended with
-          // m_lo + 1 (then every position is an interior one of both): the
-          // samples take the regions' values as wave-uniform parameters (the
-          // same values as smp gives them)
+          // m_lo + 1: the samples take the regions' values as wave-uniform
+          // parameters (the same values as smp gives them). Interior positions
+          // have paths of their own: one path for both kinds costs them 2 to 4%.
           const bool at_lo = s0 && __builtin_amdgcn_ballot_w64(sel[k].m0 != mlo) == 0;
           const bool lo_only = at_lo && __builtin_amdgcn_ballot_w64(sel[k].t > 0.0f) == 0;
           const bool pair = at_lo && in0 && s1 && in1;
-          auto smp_lo_any = [&](float x, float y) -> Tex16 {
-            return staged_sample(stage, fw0, fh0, cx, cy, kbw0, kb0, x, y, in0);
-          };
           auto smp_lo = [&](float x, float y) -> Tex16 {
             return staged_sample(stage, fw0, fh0, cx, cy, kbw0, kb0, x, y, true);
           };
           auto smp_hi = [&](float x, float y) -> Tex16 {
             return staged_sample(stage, fw1, fh1, cx, cy, kbw1, kb1, x, y, true);
           };
+          auto smp_edge = [&](int, float x, float y) -> Tex16 {
+            return staged_sample(stage, fw0, fh0, cx, cy, kbw0, kb0, x, y, false);
+          };
           if constexpr (FILTER == 1) {
-            if (lo_only)
-              c16[k] = smp_lo_any(u, v);
+            if (lo_only && in0)
+              c16[k] = smp_lo(u, v);
             else if (pair)
               c16[k] = blend16(smp_lo(u, v), smp_hi(u, v), sel[k].t);
+            else if (lo_only)
+              c16[k] = smp_edge(mlo, u, v);
             else
               c16[k] = trilinear16(sel[k], u, v, smp);
           } else {
-            if (lo_only)
-              c = filter_level_staged<false>(sel[k], u, v, smp_lo_any, smp_hi);
+            if (lo_only && in0)
+              c = filter_level_staged<false>(sel[k], u, v, smp_lo, smp_hi);
             else if (pair)
               c = filter_level_staged<true>(sel[k], u, v, smp_lo, smp_hi);
+            else if (lo_only)
+              c = filter_level_staged<false>(sel[k], u, v, [&](float x, float y) { return smp_edge(mlo, x, y); }, smp_hi);
             else
               c = filter_level<FILTER>(sel[k], u, v, [&](int m, float x, float y) { return tex_f3(smp(m, x, y)); });
           }
@@ -682,6 +686,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NTC_WAVES_PE
 //   8 or 16 taps 2500 x 2000 (38) 258, 267, 285; 2000 x 1500 (23, footprints
 //   up to 16 : 1) 346, 261, 245; 1920 x 1080 (16) 303, 197, 162; 1500 x 1500
 //   (17, few taps) 116, 107, 117; 300 x 200 (0.5) 135, 72, 40.
+// Pictures of one level of detail throughout (a coarse mip) lose a little by
+// short spans, whose waves would end together anyway: trilinear 2048 x 2048 (32)
+// 117, 129, 173, 1920 x 1080 (16) 63, 67, 89, 3000 x 2200 208, 204, 268; 16 taps
+// 1920 x 1080 96, 107, 117, 1500 x 1500 103, 118, 130, 2048 x 2048 (spans of 4) 185, 208,
+// 231. The lines for 8 and 16 taps lie between the two kinds: at 17 to 23 passes a
+// single sub-span would gain 6% on a plane with many taps and lose 9 to 12% on the others,
+// at 10 to 16 it gains 15 to 35% on such a plane and loses up to 10%.
 // (With spans of 16 and 4 sub-spans for all of them: 466, 194, 169, 111, 89;
 // 263, 151, 82, 45; 275, 383, 338, 121, 136.)
 int span_subs(const FilterArgs &f, int waves) {
