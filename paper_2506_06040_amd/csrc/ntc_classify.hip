@@ -118,16 +118,32 @@ __device__ __forceinline__ void step_keys(const ClassifyArgs &a, int chunk, int 
   }
 }
 
-// f(k, same): every key k among the wavefront's lanes, with the lanes that have it.
+// f(k, same, pending): every key k among the wavefront's lanes, with the lanes that
+// have it, and those with it or a key to come.
 template <class F>
 __device__ __forceinline__ void each_key(int key, F f) {
   uint64_t pending = __ballot(key >= 0);
   while (pending) {
     const int k = __builtin_amdgcn_readlane(key, __builtin_ctzll(pending));
     const uint64_t same = __ballot(key == k);
-    f(k, same);
+    f(k, same, pending);
     pending &= ~same;
   }
+}
+
+// Adds the wavefront's keys to their counts: a few keys as groups, what is left
+// (noise) lane by lane (4096 x 4096 pixels of 1000 materials at random, the whole
+// classification: 1389 -> 738 us; a frame of 64 materials 12 and 16 us as with groups alone).
+__device__ __forceinline__ void count_keys(int key, int lane, int32_t *cnt) {
+  int groups = 0;
+  each_key(key, [&](int k, uint64_t same, uint64_t &pending) {
+    if (++groups <= 4) {
+      if (lane == 0) atomicAdd(&cnt[k], __popcll(same));
+    } else {
+      if ((pending >> lane) & 1) atomicAdd(&cnt[key], 1);
+      pending = same;  // the last
+    }
+  });
 }
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
@@ -150,10 +166,7 @@ __global__ __launch_bounds__(64 * WAVES) void classify_count_kernel(ClassifyArgs
     int32_t idx[kPrefetch];
     step_keys(a, chunk, s0, lane, a.tile_class != nullptr, key, idx);
 #pragma unroll
-    for (int i = 0; i < kPrefetch; ++i)
-      each_key(key[i], [&](int k, uint64_t same) {
-        if (lane == 0) atomicAdd(&cnt[k], __popcll(same));
-      });
+    for (int i = 0; i < kPrefetch; ++i) count_keys(key[i], lane, cnt);
   }
   __syncthreads();
   for (int k = threadIdx.x; k < n_keys; k += 64 * WAVES) a.counts[(int64_t)k * a.n_chunks + chunk] = cnt[k];
@@ -231,10 +244,7 @@ __global__ __launch_bounds__(64 * WAVES) void classify_write_kernel(ClassifyArgs
     step_keys(a, chunk, wave * kSteps, lane, false, key, idx);
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kPrefetch; ++i)
-      each_key(key[i], [&](int k, uint64_t same) {
-        if (lane == 0) run[k] += __popcll(same);
-      });
+    for (int i = 0; i < kPrefetch; ++i) count_keys(key[i], lane, run);
     __syncthreads();
   }
   for (int k = threadIdx.x; k < n_keys; k += 64 * WAVES) {
@@ -252,7 +262,7 @@ __global__ __launch_bounds__(64 * WAVES) void classify_write_kernel(ClassifyArgs
     if (WAVES == 1) step_keys(a, chunk, s0, lane, false, key, idx);
 #pragma unroll
     for (int i = 0; i < kPrefetch; ++i)
-      each_key(key[i], [&](int k, uint64_t same) {
+      each_key(key[i], [&](int k, uint64_t same, uint64_t &) {
         const int base = run[k];
         if (key[i] == k) a.list[base + (int)lanes_below(same)] = idx[i];
         // every lane has read run[k] before lane 0 moves it (one wavefront,
