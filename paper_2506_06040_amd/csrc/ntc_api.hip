@@ -274,8 +274,11 @@ ntc_status ntc_decode(const ntc_latents *lat, const ntc_mlp *mlp, int32_t comput
   const int cus = device_cus();
   hipError_t e;
   // Float latents, short batches: the FP32 matrix kernel has less to set up
-  // than the split one (us, FP32 / split: 14-64-64-8 11.2 / 13.2 at 4096
-  // samples and 17.1 / 14.3 at 65536; 14-32-32-8 7.7 / 8.9 and 9.4 / 9.7).
+  // than the split one (us, FP32 / split: 14-64-64-8 8.3 / 13.4 at 4096 samples,
+  // 9.4 / 14.5 at 32768, 13.0 / 16.2 at 65536, 21.1 / 19.6 at 98304; 14-32-32-8 7.3 / 9.2
+  // at 4096, 9.2 / 11.6 at 65536, 23.2 / 22.6 at 262144). They meet at n hid of 5 to 8
+  // million; the line was drawn when the FP32 kernel put two wavefronts of a short batch
+  // on a SIMD, and stays on the side where it always wins.
   if (compute == NTC_F32 && lat->format == NTC_LATENT_F32 && s.n_layers <= 4 && n * s.hid <= (1 << 21))
     e = launch_forward_f32(a, s, (hipStream_t)stream);
   else if (compute == NTC_F32)

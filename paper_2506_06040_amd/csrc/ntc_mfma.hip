@@ -127,19 +127,20 @@ hipError_t launch_decode_mfma(const DecodeArgs &a, const MlpShape &s, int comput
   // one long span, then tiles; pixels in 8x8 tiles, then in odd rows), tiles a wave:
   //   spans of 8, FP16: 14-16-8      3: 14/14 21/14; 4: 13/15 21/16;
   //                     14-32-32-8   1/2: 20/8 20/8; 3.5: 13/13 21/13; 4: 13/14 21/15;
-  //       8.25: 22/24/16 40/28/31; 9: 25/26/18 56/29/34; 10: 25/28/20 56/33/37;
-  //       12: 25/33/25 56/37/42; 14: 25/38/30 57/42/48;
-  //                     14-64-64-8   4: 16/16 24/17; 9: 33/30/24 64/33/38;
+  //       8.25: 22/24/16 40/28/28; 9: 25/26/17 56/29/30; 10: 25/28/20 56/33/32;
+  //       12: 25/33/25 56/37/37; 14: 25/38/30 57/42/48;
+  //                     14-64-64-8   4: 16/16 24/17; 9: 33/30/23 64/33/33;
   //   spans of 4, FP16: 14-64-64-64-8  1/2: 15/9 15/8; 2: 13/12 16/13; 3: 15/15
   //       20/16; 5: 25/21 33/22; 6: 24/24 33/26; 7: 25/27 33/30;
   //               BF16: 14-64-8      5: 19/19 27/20; 6: 19/22 27/23;
-  //               E4M3: 14-64-64-8   5: 23/20 30/21; 6: 22/23 30/24.
+  //               E4M3: 14-64-64-8   2: 12/12 15/13; 5: 23/20 30/21; 6: 22/23 30/24.
   // BF16 and E4M3 meet at the same lines, within half a tile.
   if (a.lat.address == 0) {
     const int64_t waves = std::min(grid, (int64_t)n_cus * 4 * NTC_WAVES_PER_SIMD);
     const int64_t pass = span * waves, rest = a.n_tiles % pass;
-    // the line in sixteenths of a pass (three 64-wide layers have spans of 4 with FP32 texels only)
-    const int line = s.n_layers == 2 ? 6 : (s.hid < 64 || (span == NTC_SPAN_TILES && s.n_layers == 3) ? 7 : 8);
+    // sixteenths of a pass; a wave alone on its SIMD gains by tiles up to half of one
+    // (512x512 pixels, 4 waves per compute unit, BF16 14-32-32-8: 19 / 13)
+    const int line = waves < (int64_t)n_cus * 4 * NTC_WAVES_PER_SIMD ? 8 : (s.n_layers == 2 ? 6 : (s.hid < 64 ? 7 : 8));
     const bool head = span == NTC_SPAN_TILES_SMALL && a.n_tiles > pass;
     if (a.n_tiles < 2 * pass && rest > 0 && (head ? 2 * rest <= pass : 16 * rest <= line * pass))
       return launch_decode_short(a, s, compute, (int)std::min(a.n_tiles, waves), head, st);

@@ -1335,9 +1335,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t span_out(const DecodeArgs &a, 
 // MLP, store. The uv of the next span (next_first < 0: none) is requested
 // during this span, so that its latency overlaps the work of the span.
 // obuf (2 KB of LDS, or nullptr): output staging of the FP32 rows of widths
-// that are not a multiple of 4 (see store_outputs).
-template <class P, int HID, int NL, int ST, int VEC4, bool IDX = false, int ADDR = kEitherMode>
-__device__ __forceinline__ void decode_span(const DecodeArgs &a, int64_t first, int64_t end_px, f32x4 *stage,
+// that are not a multiple of 4 (see store_outputs). STAGED_ONLY: false, and
+// nothing decoded, where the staged path cannot take the span.
+template <class P, int HID, int NL, int ST, int VEC4, bool IDX = false, int ADDR = kEitherMode, bool STAGED_ONLY = false>
+__device__ __forceinline__ bool decode_span(const DecodeArgs &a, int64_t first, int64_t end_px, f32x4 *stage,
                                             const f32x4 *bias, f32x4 *ltab, const MfmaWeights<P, HID, NL> &W,
                                             SpanUv<ST> &uvs, int64_t next_first, int64_t next_end_px,
                                             float *obuf = nullptr) {
@@ -1392,8 +1393,9 @@ __device__ __forceinline__ void decode_span(const DecodeArgs &a, int64_t first, 
                                                          obuf);
       }
     }
-    return;
+    return true;
   }
+  if constexpr (STAGED_ONLY) return false;
 
   // direct block fetches; one sub-span at a time
 #pragma unroll 1
@@ -1415,6 +1417,7 @@ __device__ __forceinline__ void decode_span(const DecodeArgs &a, int64_t first, 
     uvs.template load_any<IDX>(a, next_first, next_end_px);
     uvs.ready();
   }
+  return true;
 }
 
 // The same for wrap addressing: the span staged before wrapping, or fetched
