@@ -102,11 +102,16 @@ __device__ __forceinline__ float split_weight(const DecodeArgs &a, const uint8_t
   return r == row && (col == -2 || c == col) ? w : 0.0f;
 }
 
+// *m to at least big; NaN counts as infinite.
+__device__ __forceinline__ void note_max(unsigned *m, float big) {
+  atomicMax(m, big == big ? __float_as_uint(big) : 0x7f800000u);
+}
+
 // Weights into LDS, a fragment (layer l, rows 32 m .., K-step c) per wavefront
 // at a time: the three parts of each, [part][fragment][lane], or as they stand
-// (EXACT), [fragment][half][lane]. note(l, largest magnitude in this lane).
-template <int HP, int NL, bool EXACT, class NOTE>
-__device__ __forceinline__ void fill_weights(const DecodeArgs &a, uint8_t *lds, int tid, NOTE &&note) {
+// (EXACT), [fragment][half][lane]. The parts note the largest weight of each layer.
+template <int HP, int NL, bool EXACT>
+__device__ __forceinline__ void fill_weights(const DecodeArgs &a, uint8_t *lds, int tid) {
   using M = SplitMap<HP, NL>;
   constexpr int kHidden = M::MT * M::KS;
   const int lane = tid & 63, h = lane >> 5;
@@ -152,7 +157,7 @@ __device__ __forceinline__ void fill_weights(const DecodeArgs &a, uint8_t *lds, 
       }
       w[(p * M::F + f) * 64 + lane] = __builtin_bit_cast(u32x4_t, q);
     }
-    note(l, big);
+    note_max(reinterpret_cast<unsigned *>(lds + M::oMax) + l, big);
   }
 }
 
@@ -177,10 +182,7 @@ __device__ __forceinline__ bool split_setup(const DecodeArgs &a, uint8_t *lds, i
     tab[1] = (f32x4){L.fh, L.sy - 0.5f, (float)(L.h - 2), __int_as_float(L.h)};
     tab[2] = (f32x4){__uint_as_float((unsigned)p), __uint_as_float((unsigned)(p >> 32)), __int_as_float(L.bw), 0.0f};
   }
-  auto note = [&](unsigned *m, float big) {  // NaN counts as infinite
-    atomicMax(m, big == big ? __float_as_uint(big) : 0x7f800000u);
-  };
-  fill_weights<HP, NL, false>(a, lds, tid, [&](int l, float big) { note(mx + l, big); });
+  fill_weights<HP, NL, false>(a, lds, tid);
   // biases (the first layer's is a weight of the constant 1)
 #pragma unroll 1
   for (int i = tid; i < (NL - 2) * M::MT * 32 + 16; i += 64 * kSplitWaves) {
@@ -190,7 +192,7 @@ __device__ __forceinline__ bool split_setup(const DecodeArgs &a, uint8_t *lds, i
     const int row = out ? i - (NL - 2) * M::MT * 32 : 32 * (g % M::MT) + 8 * ((e & 15) >> 2) + 4 * (e >> 4) + (e & 3);
     const float b = split_weight(a, a.packed, l, row, -2);
     reinterpret_cast<float *>(lds + M::oBias)[i] = b;
-    note(mx + kMaxLayers + l, fabsf(b));
+    note_max(mx + kMaxLayers + l, fabsf(b));
   }
   __syncthreads();
   float b = 0x1p20f;  // no input of layer l passes it
@@ -631,7 +633,7 @@ void decode_split_kernel(DecodeArgs a) {
   if (left) *again = 1u;
   __syncthreads();
   if (bounded && *again == 0u) return;
-  fill_weights<HP, NL, true>(a, lds, tid, [](int, float) {});
+  fill_weights<HP, NL, true>(a, lds, tid);
   __syncthreads();
   if (!bounded || left) exact_pixels<HP, NL, BC1>(a, lds, ob, it0, step, spx, !bounded);
 }
