@@ -110,7 +110,11 @@ typedef struct {
  *                   (64..4096, default 1024; twice as many of the FP16
  *                   decode's 8-byte texels); spans whose footprint is larger
  *                   fall back to direct block fetches.
- * With wrap addressing spans are 128 pixels whatever tiles_per_iter says. */
+ * tiles_per_iter does not decide the span with wrap addressing (128 pixels), nor
+ * in clamped batches that long spans would fill badly (about half of a first or
+ * second pass of the waves that run at once, two per SIMD): those are decoded
+ * wholly or partly in spans of one tile, and stage_capacity then holds for a tile.
+ * Results do not depend on any of these. */
 typedef struct {
     int32_t waves_per_cu;
     int32_t tiles_per_iter;
@@ -172,8 +176,10 @@ ntc_status ntc_calibrate_fp8(const ntc_latents *lat, const ntc_mlp *mlp, const v
 /* Fused decode (Sec. 3.1 + Sec. 3.3 + Sec. 4): out[s] = f(x(uv[s])) for
  * s < n. compute selects the arithmetic: NTC_F32 (FP32: every product of two
  * FP32 numbers is formed from three-part BF16 splits on the BF16 matrix cores
- * with FP32 accumulation, to FP32 accuracy; numbers near the ends of FP32's
- * range, and short batches of float latents, take the FP32 matrix cores),
+ * with FP32 accumulation, to FP32 accuracy; networks whose sums could pass 2^120
+ * or whose parts lost below 2^-126 could show in an output, samples with |u|, |v|
+ * or a float latent above 2^20, and short batches of float latents take the
+ * FP32 matrix cores),
  * NTC_F16 (FP16 matrix cores, FP32
  * accumulation),
  * NTC_BF16 (BF16 matrix cores, FP32 accumulation) or NTC_FP8_E4M3 (E4M3
@@ -414,7 +420,8 @@ ntc_status ntc_decode_frame_workspace(const void *table_host, size_t table_bytes
 
 /* Decode a frame: material m reads uv[p] and writes out[p] for the pixels p of
  * pixel_list[mat_offsets[m] .. mat_offsets[m + 1]), as written by ntc_classify
- * [device]. uv [image_pixels][2], out [image_pixels][C] with the limits of
+ * [device] (offsets from 0 up, never falling; entries outside the image are
+ * dropped). uv [image_pixels][2], out [image_pixels][C] with the limits of
  * ntc_material. table_host is the host image (read for sizes only), table_dev
  * its device copy. workspace [device, 256-byte aligned] holds the plan until
  * the launch has run: one per call in flight. */

@@ -30,8 +30,9 @@ FLAGS = [
 
 
 # Matrix-core results in arch VGPRs, where the decode epilogues read them
-# directly; the backward (one wavefront per SIMD, 512 registers) keeps its
-# gradient accumulators in the accumulation registers instead.
+# directly. The backward is left to the compiler: its gradient accumulators live
+# across the loop, and with one wavefront per SIMD (64-wide networks of four
+# layers, 512 registers) they go to the accumulation registers.
 PER_FILE = {s: ["-mllvm", "-amdgpu-mfma-vgpr-form=1"] for s in SOURCES if s != "ntc_backward.hip"}
 
 

@@ -1273,7 +1273,8 @@ __device__ __forceinline__ void staged_operands(const DecodeArgs &a, const f32x4
 }
 
 // Operands of the pixel (uq, vq) with direct block fetches (footprint beyond
-// the LDS region, or wrap addressing).
+// the LDS region, wrapped positions too far out to be staged, or wrap
+// addressing in a kernel for either mode).
 template <class P, int ADDR>
 __device__ __forceinline__ void direct_operands(const DecodeArgs &a, const f32x4 *ltab, float uq, float vq,
                                                 float in_scale, int salt, typename P::Frag (&bx)[2]) {
